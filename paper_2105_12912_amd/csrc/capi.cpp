@@ -710,8 +710,10 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
         d.rl_units = cdiv(d.n_runs_hdr, kBlock), d.rl_base = rl.add(d.rl_units);
         d.sc_units = cst ? 0 : cdiv(H.n_out, kBlock), d.sc_base = sc.add(d.sc_units);
-        // 3D: at most one fix-up chunk per outlier, a wave each
-        d.fx_units = (cst || H.rank != 3) ? 0 : cdiv(H.n_out, kWavesPerBlock);
+        // 3D with outliers: every wave block of the reconstruction is looked at
+        uint32_t t3[3];
+        recon3_tiles(g, t3);
+        d.fx_units = (cst || H.rank != 3 || H.n_out == 0) ? 0 : t3[0] * t3[1] * kWavesPerBlock * t3[2];
         d.fx_base = fx.add(d.fx_units);
         d.range_units = cst ? g.range_units : 0, d.range_base = range.add(d.range_units);
         if (cst) {
@@ -790,18 +792,18 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
                  : (d.arc ? (const uint16_t*)(d.arc + H.off_val) : nullptr);
         d.sink = bp.take<float>(256);
         const bool r3 = g.rank == 3 && !cst;
-        d.oflag = bp.take<uint32_t>(r3 ? 4ull * d.nxb * d.nyb * kWavesPerBlock * d.nzb : 0);
-        d.fixl = bp.take<uint32_t>(r3 ? 4ull * H.n_out : 0);
+        d.oflag = bp.take<uint64_t>(r3 ? 8ull * d.nxb * d.nyb * kWavesPerBlock * d.nzb : 0);
+        d.zslot = bp.take<uint32_t>(cst ? 0 : 4ull * kZeroSlots * kZeroStride);
     }
     B.ws_bytes = bp.off;
     if (B.overflow) return fail(EBC_ERR_DIMS, "batch too large: a work-unit total reaches 2^32");
     return EBC_OK;
 }
 
-// Outlier scatter and reconstruction.  The 3D reconstruction reads no
-// deltas and clears the chunk flags, so it runs before the scatter, which
-// queues the chunks holding outliers for the fix-up; 1D/2D reconstruction
-// fuses the scattered deltas itself.
+// Outlier scatter and reconstruction.  The 3D reconstruction reads no deltas:
+// it flags the chunks that hold an outlier code and leaves them to the fix-up,
+// which needs the scattered deltas; 1D/2D reconstruction fuses the scattered
+// deltas itself.
 int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
 {
     bool has3 = false, has12 = false;

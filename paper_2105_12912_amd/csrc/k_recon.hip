@@ -259,8 +259,8 @@ __device__ __forceinline__ void rtile_process(const FieldDesc& fd, uint32_t tl, 
     }
 }
 
-// Zero codes seen by this workgroup for field fd, added to the field's count
-// (checked against the outlier count by k_recon_check).
+// Zero codes seen by this workgroup for field fd, added to one of the field's
+// counters (their sum is checked against the outlier count by k_recon_check).
 __device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t& zeros, uint32_t* s_z)
 {
     const uint32_t zs = wave_sum_u32(zeros);
@@ -270,7 +270,7 @@ __device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t& zeros
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t z = s_z[0] + s_z[1] + s_z[2] + s_z[3];
-        if (z) atomicAdd((unsigned long long*)&fd.dyn->zero_count, (unsigned long long)z);
+        if (z) atomicAdd(&fd.zslot[(blockIdx.x % kZeroSlots) * kZeroStride], z);
     }
 }
 
@@ -327,25 +327,27 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restr
     if (cur >= 0) flush_zeros(F[cur], zeros, s_z);
 }
 
-// Bit 15 (bit 31) set iff the low (high) 16-bit code packed in w is 0: with
-// each half's top bit forced on, subtracting 1 clears it only in a half that
-// was 0, and never borrows across halves (codes are below 2^15).
-__device__ __forceinline__ uint32_t zero_half(uint32_t w)
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// running minimum of the two codes packed in each word (a zero half stays)
+__device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b)
 {
-    return ~((w | 0x80008000u) - 0x00010001u) & 0x80008000u;
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
+                                                                  __builtin_bit_cast(u16x2, b)));
 }
+__device__ __forceinline__ bool has_zero_half(uint32_t w) { return (w & 0xFFFFu) == 0 || (w >> 16) == 0; }
 
 // Chunk rows of one wave of the 3D reconstruction (see k_reconstruct3).
 // FULL: the wave's 256 x 8 x 8 block lies inside the field and its rows are
 // 16-byte aligned, so every row is one load and one store with no per-lane or
 // per-row condition, addressed as a wave-uniform row pointer plus the lane's
 // offset.  Otherwise rows outside the field are skipped, absent codes read as
-// 1 and absent elements are not stored.  Outlier codes (0) enter as 0 - r
-// and are only counted here: k_recon3_fix rewrites every chunk that holds
-// one.
+// 1 and absent elements are not stored.  Chunks with outlier codes (0) are not
+// reconstructed here: a lane stops storing at the first plane in which its
+// chunk showed one, and a wave with nothing left to store stops.  Returns the
+// lanes (4 x each) that met an outlier code.
 template <bool FULL, bool VEC, class OT>
-__device__ __forceinline__ void recon3_wave(const FieldDesc& fd, uint32_t x0w, uint32_t y0, uint32_t z0,
-                                            double ebx2, uint32_t& zeros)
+__device__ __forceinline__ uint64_t recon3_wave(const FieldDesc& fd, uint32_t x0w, uint32_t y0, uint32_t z0,
+                                                double ebx2)
 {
     const int l = lane_id();
     const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
@@ -376,6 +378,8 @@ __device__ __forceinline__ void recon3_wave(const FieldDesc& fd, uint32_t x0w, u
             }
         }
     };
+    uint32_t low = 0xFFFFFFFFu;  // smallest code halves met
+    uint64_t met = 0;            // lanes that met an outlier code
     load_plane(0);
 #pragma unroll
     for (int iz = 0; iz < 8; ++iz) {
@@ -383,19 +387,21 @@ __device__ __forceinline__ void recon3_wave(const FieldDesc& fd, uint32_t x0w, u
         // the compiler hoists every plane's loads and runs out of registers
         __builtin_amdgcn_sched_barrier(0);
         if (iz + 1 < 8) load_plane(iz + 1);
+#pragma unroll
+        for (int y = 0; y < 8; ++y) low = min_halves(low, min_halves(raw[iz][y].x, raw[iz][y].y));
+        met = ballot(has_zero_half(low));
+        // both lanes of a chunk's pair, and lanes past the field, are done
+        const uint64_t pairs = met | ((met >> 1) & 0x5555555555555555ull) | ((met & 0x5555555555555555ull) << 1);
+        const bool live = (FULL || nvx > 0) && ((pairs >> l) & 1u) == 0;
+        if (!__any(live)) break;
         uint32_t yprev[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int y = 0; y < 8; ++y) {
             if (!FULL && !row_ok(iz, y)) continue;  // wave-uniform
             uint32_t c[4], sv[4];
-            const u32x2 t = raw[iz][y];
-            unpack4(t, c);
+            unpack4(raw[iz][y], c);
 #pragma unroll
             for (int k = 0; k < 4; ++k) sv[k] = c[k] - r;
-            zeros += __builtin_popcount(zero_half(t.x)) + __builtin_popcount(zero_half(t.y));
-            // accumulate in place: a reassociated sum would hold every
-            // row's count in a register of its own until the end
-            asm volatile("" : "+v"(zeros));
             sv[1] += sv[0], sv[2] += sv[1], sv[3] += sv[2];  // x pass within the quad
             uint32_t left = dpp_shr_u<1>(sv[3]);            // the pair lane's total
             if ((l & 1) == 0) left = 0;
@@ -410,12 +416,13 @@ __device__ __forceinline__ void recon3_wave(const FieldDesc& fd, uint32_t x0w, u
             OT v[4];
             dequant4(sv, ebx2, v);
             if constexpr (FULL && sizeof(OT) == 4) {
-                st_nt_f4(out + row(iz, y) + 4 * l, f32x4{v[0], v[1], v[2], v[3]});
+                if (live) st_nt_f4(out + row(iz, y) + 4 * l, f32x4{v[0], v[1], v[2], v[3]});
             } else {
-                store_quad<VEC>(out, row(iz, y) + 4 * l, FULL ? 4 : nvx, v);
+                if (live) store_quad<VEC>(out, row(iz, y) + 4 * l, FULL ? 4 : nvx, v);
             }
         }
     }
+    return met;
 }
 
 // 3D: a wave owns 256 x (one quad per lane) by one 8x8 chunk layer in y and
@@ -428,13 +435,12 @@ __device__ __forceinline__ void recon3_wave(const FieldDesc& fd, uint32_t x0w, u
 // and one 1 KiB store per wave.
 //
 // Outliers are not read here: a wait for a delta loaded in the middle of the
-// stream would also wait for every load and store issued before it.  Instead
-// each wave clears its block's chunk flags, which the outlier scatter sets
-// afterwards, and k_recon3_fix recomputes the flagged chunks exactly.
+// stream would also wait for every load and store issued before it.  Each
+// wave records which of its lanes met an outlier code, and k_recon3_fix
+// reconstructs those chunks (and counts their outliers).
 template <bool VEC, class OT>
 __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __restrict__ F, int nf)
 {
-    __shared__ uint32_t s_z[kWavesPerBlock];
     const uint32_t t = blockIdx.x;
     const int f = find_field<&FieldDesc::wg_base>(F, nf, t);
     const FieldDesc& fd = F[f];
@@ -446,27 +452,126 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __rest
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t x0w = xb * 256, y0 = yb * 32 + w * 8, z0 = zb * 8;
     const double ebx2 = dy->ebx2;
-    uint32_t zeros = 0;
-    if (lane_id() == 0) fd.oflag[(zb * (nyb * kWavesPerBlock) + yb * kWavesPerBlock + w) * nxb + xb] = 0;
+    uint64_t met;
     if (VEC && x0w + 256 <= fd.nx && y0 + 8 <= fd.ny && z0 + 8 <= fd.nz)
-        recon3_wave<true, VEC, OT>(fd, x0w, y0, z0, ebx2, zeros);
+        met = recon3_wave<true, VEC, OT>(fd, x0w, y0, z0, ebx2);
     else
-        recon3_wave<false, VEC, OT>(fd, x0w, y0, z0, ebx2, zeros);
-    const uint32_t zs = wave_sum_u32(zeros);
-    if (lane_id() == 0) s_z[w] = zs;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t z = s_z[0] + s_z[1] + s_z[2] + s_z[3];
-        if (z) atomicAdd((unsigned long long*)&fd.dyn->zero_count, (unsigned long long)z);
+        met = recon3_wave<false, VEC, OT>(fd, x0w, y0, z0, ebx2);
+    if (lane_id() == 0) {
+        fd.oflag[(zb * (nyb * kWavesPerBlock) + yb * kWavesPerBlock + w) * nxb + xb] = met;
+        // no fix-up runs for a field without listed outliers: any count will
+        // do for the check to refuse its outlier codes
+        if (met && fd.n_out_hdr == 0) atomicAdd(&fd.zslot[0], 1u);
     }
 }
 
-// Outlier fix-up of the 3D reconstruction: one wave per 8x8x8 chunk that
-// holds an outlier (queued by the outlier scatter), recomputed from its codes
-// with the exact deltas substituted.  Lane (yl, zl) = (l % 8, l / 8) owns the
-// chunk row of 8 x; the x pass is in-lane, the y pass a scan over the 8 lanes
-// of a z layer and the z pass a scan over the 8 layers.  Elements outside
-// the field enter as 0 and are not stored.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+// eight consecutive elements of a chunk row
+__device__ __forceinline__ void store_row8(EBC_G float* o, const uint32_t s[8], double ebx2)
+{
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (float)((double)(int32_t)s[e] * ebx2);
+    *(EBC_G f32x4_a4*)o = f32x4{v[0], v[1], v[2], v[3]};
+    *(EBC_G f32x4_a4*)(o + 4) = f32x4{v[4], v[5], v[6], v[7]};
+}
+__device__ __forceinline__ void store_row8(EBC_G double* o, const uint32_t s[8], double ebx2)
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2)
+        *(EBC_G f64x2_a8*)(o + e) = f64x2{(double)(int32_t)s[e] * ebx2, (double)(int32_t)s[e + 1] * ebx2};
+}
+
+// One wave's share of the fix-up: the flagged ones of eight 8x8x8 chunks along
+// x.  Lane (z, chunk) = (l % 8, l / 8) owns the rows of 8 x of one plane of
+// its chunk and walks y: the x pass is in-lane, the y pass a running sum, the
+// z pass a scan over the 8 lanes of a chunk.  All codes and deltas are loaded
+// before any is used (the kernel is bound by that one round trip when few
+// chunks are flagged, by the traffic when many are).  Returns the lane's
+// outlier count.
+template <class OT>
+__device__ __forceinline__ uint32_t fix_wave(const FieldDesc& fd, bool flagged, uint32_t x0, uint32_t y0,
+                                             uint32_t z0, double ebx2)
+{
+    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
+    const uint32_t zl = lane_id() & 7, zz = z0 + zl;
+    const uint32_t nv = flagged && zz < nz && x0 < nx ? min<uint32_t>(8, nx - x0) : 0u;
+    const uint32_t r = fd.n_bins / 2;
+    const EBC_G uint16_t* __restrict__ q = fd.q;
+    const EBC_G int32_t* __restrict__ dsc = fd.dsc;
+    EBC_G OT* __restrict__ out = field_out<OT>(fd);
+    const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0;
+    u32x4 c[8], da[8], db[8];
+#pragma unroll
+    for (uint32_t y = 0; y < 8; ++y) {
+        c[y] = u32x4{0x00010001u, 0x00010001u, 0x00010001u, 0x00010001u};
+        da[y] = db[y] = u32x4{0u, 0u, 0u, 0u};
+        if (y0 + y >= ny) continue;  // uniform
+        const uint64_t i = i0 + (uint64_t)y * nx;
+        if (nv == 8) {
+            c[y] = *(const EBC_G u32x4_a2*)(q + i);
+            da[y] = *(const EBC_G u32x4_a4*)(dsc + i);
+            db[y] = *(const EBC_G u32x4_a4*)(dsc + i + 4);
+        } else {
+            // the field's last, partial chunk along x
+            for (uint32_t e = 0; e < nv; ++e) {
+                const uint32_t sh = 16 * (e & 1), cv = q[i + e], dv = (uint32_t)dsc[i + e];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k)
+                    if (k == e) {
+                        c[y][k / 2] = (c[y][k / 2] & ~(0xFFFFu << sh)) | (cv << sh);
+                        if (k < 4) da[y][k & 3] = dv;
+                        else db[y][k & 3] = dv;
+                    }
+            }
+        }
+    }
+    uint32_t yprev[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t zeros = 0;
+    const uint32_t m1 = zl >= 1 ? ~0u : 0u, m2 = zl >= 2 ? ~0u : 0u, m4 = zl >= 4 ? ~0u : 0u;
+#pragma unroll
+    for (uint32_t y = 0; y < 8; ++y) {
+        if (y0 + y >= ny) continue;  // uniform
+        uint32_t s[8];
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e) {
+            const uint32_t cv = (c[y][e / 2] >> (16 * (e & 1))) & 0xFFFFu;
+            const uint32_t dv = e < 4 ? da[y][e & 3] : db[y][e & 3];
+            zeros += cv == 0;
+            s[e] = cv == 0 ? dv : cv - r;
+        }
+#pragma unroll
+        for (int e = 1; e < 8; ++e) s[e] += s[e - 1];  // x pass
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            s[e] += yprev[e];  // y pass
+            yprev[e] = s[e];
+            // z pass: inclusive scan over the chunk's 8 lanes
+            s[e] += dpp_shr_u<1>(s[e]) & m1;
+            s[e] += dpp_shr_u<2>(s[e]) & m2;
+            s[e] += dpp_shr_u<4>(s[e]) & m4;
+        }
+        const uint64_t i = i0 + (uint64_t)y * nx;
+        if (nv == 8) {
+            store_row8(out + i, s, ebx2);
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < 8; ++e)
+                if (e < nv) out[i + e] = (OT)((double)(int32_t)s[e] * ebx2);
+        }
+    }
+    return zeros;
+}
+
+// Outlier fix-up of the 3D reconstruction: a workgroup per wave block of
+// k_reconstruct3, a wave per 64 x of it; waves without a flagged chunk leave at
+// once.  With one queue entry per flagged chunk instead, the queue's counter
+// alone took 2.5 ms for the 5e4 chunks of a batch of rough fields (2.5e7
+// elements, nearly every chunk flagged) and the chunks, a wave each with
+// 2-byte loads, 0.37 ms.
 __global__ __launch_bounds__(kBlock) void k_recon3_fix(const FieldDesc* __restrict__ F, int nf)
 {
     const uint32_t t = blockIdx.x;
@@ -474,79 +579,41 @@ __global__ __launch_bounds__(kBlock) void k_recon3_fix(const FieldDesc* __restri
     const FieldDesc& fd = F[f];
     const auto* dy = kconst(fd.dyn);
     if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
-    const uint32_t g = (t - fd.fx_base) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    // the queue entry is fetched alongside the count (clamped into the queue)
-    const uint32_t cnt = dy->fix_count;
-    const uint64_t i = kconst(fd.fixl)[min<uint64_t>(g, fd.n_out_hdr - 1)];
-    if (g >= cnt) return;
-    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    const uint32_t cx = (uint32_t)(i % nx) & ~7u;
-    const uint64_t yz = i / nx;
-    const uint32_t cy = (uint32_t)(yz % ny) & ~7u, cz = (uint32_t)(yz / ny) & ~7u;
-    const int l = lane_id();
-    const uint32_t yl = l & 7, zl = l >> 3;
-    const uint32_t yy = cy + yl, zz = cz + zl;
-    const bool ok = yy < ny && zz < nz;
-    const uint32_t nv = ok ? min<uint32_t>(8, nx - cx) : 0;
-    const uint64_t i0 = ok ? ((uint64_t)zz * ny + yy) * nx + cx : 0;
-    const uint32_t r = fd.n_bins / 2;
-    // codes and deltas loaded together (one round trip)
-    uint32_t c[8], dv[8], sv[8];
-#pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) {
-        c[e] = 1, dv[e] = 0;
-        if (e < nv) c[e] = fd.q[i0 + e], dv[e] = (uint32_t)fd.dsc[i0 + e];
-    }
-#pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) sv[e] = e < nv ? (c[e] == 0 ? dv[e] : c[e] - r) : 0u;
-#pragma unroll
-    for (int e = 1; e < 8; ++e) sv[e] += sv[e - 1];  // x pass
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        // y pass: inclusive scan over the 8 lanes of this z layer
-        uint32_t a = dpp_shr_u<1>(sv[e]);
-        sv[e] += yl >= 1 ? a : 0u;
-        a = dpp_shr_u<2>(sv[e]);
-        sv[e] += yl >= 2 ? a : 0u;
-        a = dpp_shr_u<4>(sv[e]);
-        sv[e] += yl >= 4 ? a : 0u;
-        // z pass: inclusive scan over the 8 layers (lane strides of 8)
-        a = (uint32_t)__shfl_up((int)sv[e], 8);
-        sv[e] += zl >= 1 ? a : 0u;
-        a = (uint32_t)__shfl_up((int)sv[e], 16);
-        sv[e] += zl >= 2 ? a : 0u;
-        a = (uint32_t)__shfl_up((int)sv[e], 32);
-        sv[e] += zl >= 4 ? a : 0u;
-    }
-    const double ebx2 = dy->ebx2;
-    if (fd.dtype == 1) {
-#pragma unroll
-        for (uint32_t e = 0; e < 8; ++e)
-            if (e < nv) fd.outd[i0 + e] = (double)(int32_t)sv[e] * ebx2;
-    } else {
-#pragma unroll
-        for (uint32_t e = 0; e < 8; ++e)
-            if (e < nv) fd.outf[i0 + e] = (float)((double)(int32_t)sv[e] * ebx2);
-    }
+    const uint32_t b = t - fd.fx_base;  // wave block, in the order of oflag
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t bits = (uint32_t)(kconst(fd.oflag)[b] >> (16 * w)) & 0xFFFFu;
+    if (bits == 0) return;
+    const uint32_t nxb = fd.nxb, nyw = fd.nyb * kWavesPerBlock;
+    const uint32_t xb = b % nxb, yw = (b / nxb) % nyw, zb = b / (nxb * nyw);
+    const uint32_t ch = lane_id() >> 3;
+    const bool flagged = ((bits >> (2 * ch)) & 3u) != 0;
+    const uint32_t x0 = xb * 256 + w * 64 + ch * 8;
+    const uint32_t zeros = fd.dtype == 1 ? fix_wave<double>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2)
+                                         : fix_wave<float>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2);
+    const uint32_t zs = wave_sum_u32(zeros);
+    if (lane_id() == 0 && zs)
+        atomicAdd(&fd.zslot[((t * kWavesPerBlock + w) % kZeroSlots) * kZeroStride], zs);
 }
 
-// decompression epilogue: the code-0 count must equal the outlier count
-__global__ void k_recon_check(const FieldDesc* __restrict__ F, int nf)
+// decompression epilogue: the code-0 count must equal the outlier count (one
+// wave per field)
+static_assert(kZeroSlots == kWave, "one lane per counter");
+__global__ __launch_bounds__(kWave) void k_recon_check(const FieldDesc* __restrict__ F)
 {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const FieldDesc& fd = F[f];
+    const FieldDesc& fd = F[blockIdx.x];
     EBC_G FieldDyn* dy = fd.dyn;
     if (dy->status != ST_OK || fd.codec_hdr == ARC_CONST) return;
-    if (dy->zero_count != fd.n_out_hdr) dy->status = ST_ERR_ARCHIVE;
+    const uint64_t z = wave_sum_u64(fd.zslot[lane_id() * kZeroStride]);
+    if (lane_id() == 0 && z != fd.n_out_hdr) dy->status = ST_ERR_ARCHIVE;
 }
 
-// decompression prologue: per-field device scalars from the header values
-__global__ void k_dinit(const FieldDesc* __restrict__ F, int nf)
+// decompression prologue: per-field device scalars from the header values, and
+// the code-0 counters cleared (one wave per field)
+__global__ __launch_bounds__(kWave) void k_dinit(const FieldDesc* __restrict__ F)
 {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const FieldDesc& fd = F[f];
+    const FieldDesc& fd = F[blockIdx.x];
+    if (fd.codec_hdr != ARC_CONST) fd.zslot[lane_id() * kZeroStride] = 0;
+    if (lane_id() != 0) return;
     FieldDyn d = {};
     d.status = ST_OK;
     d.codec = fd.codec_hdr;
@@ -607,13 +674,13 @@ hipError_t launch_recon_fix(const FieldDesc* F, int nf, uint32_t units, hipStrea
 
 hipError_t launch_recon_check(const FieldDesc* F, int nf, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_recon_check, dim3((nf + 63) / 64), dim3(64), 0, s, F, nf);
+    hipLaunchKernelGGL(k_recon_check, dim3(nf), dim3(kWave), 0, s, F);
     return hipGetLastError();
 }
 
 hipError_t launch_dinit(const FieldDesc* F, int nf, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dinit, dim3((nf + 63) / 64), dim3(64), 0, s, F, nf);
+    hipLaunchKernelGGL(k_dinit, dim3(nf), dim3(kWave), 0, s, F);
     return hipGetLastError();
 }
 
