@@ -72,28 +72,34 @@ __device__ __forceinline__ int dpp_keep(int v)
     return v;
 }
 
+// Inclusive scan across the 64 lanes of a wave, in six DPP additions: shifts
+// inside the 16-lane rows, then the last lane of a row into the next row and
+// of the lower half into the upper (a lane permute through LDS per step took
+// about ten times the latency).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v)
+{
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);  // row_shr:2
+    v = dpp_add<0x114, 0xF>(v);  // row_shr:4
+    v = dpp_add<0x118, 0xF>(v);  // row_shr:8
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// Sum over the wave, in every lane (all lanes of the wave take part).
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(v), 63);
 }
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
 {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// Inclusive scan across the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v)
-{
-    const int l = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t t = __shfl_up(v, d);
-        if (l >= d) v += t;
-    }
     return v;
 }
 

@@ -134,7 +134,7 @@ struct FieldDesc {
     uint32_t range_units, range_base;  // value range / fill: kRangeUnit elements per WG
     uint32_t wg_tiles, wg_base;        // construct / reconstruct WG tiles (rank group relative)
     uint32_t n_seg, seg_base;          // outlier segments: count-array entries
-    uint32_t ow_units, ow_base;        // outlier write: 1024 segments per WG
+    uint32_t ow_units, ow_base;        // outlier write: 64 segments per WG
     uint32_t n_hch, hch_base;          // Huffman chunks: word-count array entries
     uint32_t hs;                       // Huffman sub-chunk symbols: min(hc, 256)
     uint32_t n_sub, sub_base;          // Huffman sub-chunks: in-chunk start offsets
