@@ -165,7 +165,7 @@ struct Geo {
     uint32_t wx, xs, nxb, nyb, nzb, n_wave_tiles, wg_tiles;
     uint32_t grid;  // persistent construction grid (workgroups)
     uint32_t scan;  // scan schedule: direct down-sweep up to this many tiles (0: default)
-    uint32_t n_seg, range_units, ow_units, n_hch, hwg_units, hdwg_units, n_rt;
+    uint32_t n_seg, range_units, ow_units, n_hch, hwg_units, n_rt;
     uint32_t hs, n_sub, hpwg_units;
 };
 
@@ -202,7 +202,6 @@ Geo make_geo(int rank, const uint64_t dims[3], uint32_t hc)
     g.hwg_units = cdiv(g.n_hch, huff_cpw(hc));
     g.hs = std::min(hc, kSubMax);
     g.n_sub = cdiv(g.n, g.hs);
-    g.hdwg_units = cdiv(g.n_sub, kDecLanes);
     g.hpwg_units = cdiv(g.n_hch, kBlock);
     g.n_rt = cdiv(g.n, kRleTile);
     return g;
@@ -246,6 +245,7 @@ struct Batch {
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
+    uint32_t dec_lanes = 0, dec_groups = 0;  // decompress: lanes and 64-sub-chunk groups per decode workgroup
     uint64_t* d_result = nullptr;
     EstDev* d_est = nullptr;
     uint64_t ws_bytes = 0;
@@ -304,7 +304,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
     B.groups.clear();
     B.overflow = false;
     bool* ov = &B.overflow;
-    Tot range{0, ov}, seg{0, ov}, ow{0, ov}, hch{0, ov}, hwg{0, ov}, hdwg{0, ov}, rt{0, ov}, wg{0, ov},
+    Tot range{0, ov}, seg{0, ov}, ow{0, ov}, hch{0, ov}, hwg{0, ov}, rt{0, ov}, wg{0, ov},
         sub{0, ov}, hpwg{0, ov};
     for (int k = 0; k < nf; ++k) {
         const Geo& g = geo[idx[k]];
@@ -326,7 +326,6 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         d.ow_base = ow.add(g.ow_units), d.ow_units = g.ow_units;
         d.hch_base = hch.add(g.n_hch), d.n_hch = g.n_hch;
         d.hwg_base = hwg.add(g.hwg_units), d.hwg_units = g.hwg_units;
-        d.hdwg_base = hdwg.add(g.hdwg_units), d.hdwg_units = g.hdwg_units;
         d.hs = g.hs;
         d.sub_base = sub.add(g.n_sub), d.n_sub = g.n_sub;
         d.hpwg_base = hpwg.add(g.hpwg_units), d.hpwg_units = g.hpwg_units;
@@ -334,7 +333,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         B.max_rle_units = std::max(B.max_rle_units, cdiv(g.n, kBlock));
     }
     B.tot_range = (uint32_t)range.v, B.tot_seg = (uint32_t)seg.v, B.tot_ow = (uint32_t)ow.v;
-    B.tot_hch = (uint32_t)hch.v, B.tot_hwg = (uint32_t)hwg.v, B.tot_hdwg = (uint32_t)hdwg.v;
+    B.tot_hch = (uint32_t)hch.v, B.tot_hwg = (uint32_t)hwg.v;
     B.tot_rt = (uint32_t)rt.v, B.tot_sub = (uint32_t)sub.v, B.tot_hpwg = (uint32_t)hpwg.v;
     B.scan = 0;
     for (int k = 0; k < nf; ++k) B.scan = std::max(B.scan, geo[k].scan);
@@ -691,6 +690,12 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
     bool* ov = &B.overflow;
     Tot hch{0, ov}, hdwg{0, ov}, rt{0, ov}, runs{0, ov}, sc{0, ov}, rl{0, ov}, fx{0, ov}, range{0, ov},
         sub{0, ov}, hpwg{0, ov};
+    // symbols of a Huffman stream: the N codes, or the run values of RLE+VLE
+    auto stream = [&](int i) { return din[i].H.codec == EBC_ARC_RLE_VLE ? din[i].H.n_a : geo[i].n; };
+    uint64_t all_grp = 0;
+    for (int i = 0; i < B.nf; ++i)
+        if (huff_codec(din[i].H.codec)) all_grp += cdiv(stream(i), (uint64_t)geo[i].hs * kWave);
+    huff_decode_split(all_grp, &B.dec_lanes, &B.dec_groups);
     for (int k = 0; k < B.nf; ++k) {
         const DecompressIn& D = din[B.order[k]];
         const Header& H = D.H;
@@ -698,13 +703,12 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         const Geo& g = geo[B.order[k]];
         d.codec_hdr = H.codec;
         const bool huff = huff_codec(H.codec), rle = rle_codec(H.codec), cst = H.codec == EBC_ARC_CONST;
-        // the Huffman stream: the N codes, or the run values of RLE+VLE
-        const uint64_t hm = H.codec == EBC_ARC_RLE_VLE ? H.n_a : g.n;
+        const uint64_t hm = stream(B.order[k]);
         d.hn = huff ? hm : 0;
         d.hs = g.hs;
         d.n_hch = huff ? cdiv(hm, H.hc) : 0, d.hch_base = hch.add(d.n_hch);
         d.n_sub = huff ? cdiv(hm, g.hs) : 0, d.sub_base = sub.add(d.n_sub);
-        d.hdwg_units = cdiv(d.n_sub, kDecLanes), d.hdwg_base = hdwg.add(d.hdwg_units);
+        d.hdwg_units = cdiv(cdiv(d.n_sub, kWave), B.dec_groups), d.hdwg_base = hdwg.add(d.hdwg_units);
         d.hpwg_units = cdiv(d.n_hch, kBlock), d.hpwg_base = hpwg.add(d.hpwg_units);
         d.n_rt = rle ? g.n_rt : 0, d.rt_base = rt.add(d.n_rt);
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
@@ -838,7 +842,7 @@ int enqueue_decompress(Batch& B, hipStream_t s, Timer& T)
         T.mark("dectab");
         HIP_TRY(launch_dectab(B.d_fd, nf, B.d_tabs, B.tab_stride, B.max_bins, s));
         T.mark("huffman_decode");
-        HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.d_wcnt, B.d_soff, B.d_tabs, B.tab_stride, s));
+        HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.dec_lanes, B.d_wcnt, B.d_soff, B.d_tabs, B.tab_stride, s));
     }
     if (B.tot_runs) {
         T.mark("rle_decode");

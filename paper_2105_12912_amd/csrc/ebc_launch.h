@@ -54,9 +54,10 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
 hipError_t launch_words_check(const FieldDesc* F, int nf, const uint32_t* woff, hipStream_t s);
 hipError_t launch_huff_prep(const FieldDesc* F, int nf, uint32_t units, uint32_t* wcnt, uint32_t* soff,
                             hipStream_t s);
-hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, const uint32_t* woff,
-                              const uint32_t* soff, const uint8_t* tabs, size_t tab_stride,
-                              hipStream_t s);
+void huff_decode_split(uint64_t n_grp, uint32_t* lanes, uint32_t* groups);
+hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t lanes,
+                              const uint32_t* woff, const uint32_t* soff, const uint8_t* tabs,
+                              size_t tab_stride, hipStream_t s);
 
 // RLE
 hipError_t launch_rle_count(const FieldDesc* F, int nf, uint32_t units, uint32_t* rcnt, hipStream_t s);

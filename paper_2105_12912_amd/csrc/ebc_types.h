@@ -45,7 +45,6 @@ constexpr uint32_t kSubMax = 256;          // Huffman sub-chunk symbols (hs = mi
 // 12k workgroups all hold an outlier).
 constexpr uint32_t kZeroSlots = 64;
 constexpr uint32_t kZeroStride = 32;       // words between slots (128 bytes)
-constexpr uint32_t kDecLanes = 768;        // decode workgroup: one lane per sub-chunk
 
 enum : int32_t { ARC_HUFFMAN = 0, ARC_RLE = 1, ARC_CONST = 2, ARC_RLE_VLE = 3 };
 enum : int32_t { REQ_AUTO = 0, REQ_HUFFMAN = 1, REQ_RLE = 2, REQ_RLE_VLE = 3, REQ_AUTO_VLE = 4 };
@@ -139,7 +138,7 @@ struct FieldDesc {
     uint32_t hs;                       // Huffman sub-chunk symbols: min(hc, 256)
     uint32_t n_sub, sub_base;          // Huffman sub-chunks: in-chunk start offsets
     uint32_t hwg_units, hwg_base;      // Huffman encode: huff_cpw(hc) chunks per WG
-    uint32_t hdwg_units, hdwg_base;    // Huffman decode: kDecLanes sub-chunks per WG
+    uint32_t hdwg_units, hdwg_base;    // Huffman decode: Batch::dec_groups * 64 sub-chunks per WG
     uint32_t hpwg_units, hpwg_base;    // Huffman decode prologue: kBlock chunks per WG
     uint32_t n_rt, rt_base;            // RLE tiles of kRleTile elements (count array / WG)
     uint32_t n_runs_hdr, rle_base;     // decompress: runs in the archive (start array entries)
@@ -170,13 +169,16 @@ struct EstDev {
 
 // Canonical Huffman decoder tables of one field (built by k_dectab).
 // lut[p] decodes the next kLutBits stream bits p into up to three whole
-// codewords: bits 0-15/16-31/32-47 the symbols (zero when absent), 48-49 how
-// many (0 = the first codeword is longer than kLutBits), 50-55 their total
-// length, 56-59 and 60-63 the lengths of the first two.  When the first
-// codeword is longer, bits 0-15 hold the start of this prefix's block of
-// 2^l2k entries in l2 (0xFFFF: none), indexed by the next l2k bits; an l2
-// entry is (length << 16) | symbol, or 0 for a codeword longer still.
+// codewords: bits 0-15/16-31/32-47 the symbols (zero when absent), 48-53 their
+// total length, 54-56 twice their number (the rest zero, so that the top
+// halfwords of a few entries add up without carries between the fields).  An
+// entry is 0 when the first codeword is longer than kLutBits.  Such prefixes
+// are the top ones and each owns a block of 2^l2k entries in l2, in prefix
+// order, indexed by the next l2k bits; an l2 entry is (length << 16) | symbol,
+// or 0 for a codeword longer still.
 struct DecTab {
+    uint64_t lut[1u << kLutBits];
+    uint32_t l2[kL2Size];
     uint64_t first[65];   // first code of each length
     uint64_t endv[65];    // (first[L] + count[L]) << (64 - L): a left-aligned window w holds a
                           // code of length <= L iff w < endv[L] (defined for L < max_len)
@@ -186,8 +188,6 @@ struct DecTab {
     uint32_t l2k;             // bits resolved by the second level (0: no second level)
     uint32_t l2n;             // second-level entries in use
     uint32_t pad;
-    uint64_t lut[1u << kLutBits];
-    uint32_t l2[kL2Size];
     uint16_t perm[2];         // symbols ordered by (length, symbol): n_bins entries (the
                               // table occupies dectab_bytes(n_bins))
 };

@@ -689,7 +689,6 @@ __device__ __forceinline__ void dectab_tables(DecTab* T, const uint32_t* cntL, c
     // top nlong ones and the numbering in prefix order makes a block's start
     // (p - (2^kLutBits - nlong)) << k: the decoder computes the second-level
     // index from the stream bits alone and relies on this order.
-    __shared__ uint16_t lslot[1u << kLutBits];
     __shared__ uint16_t lpref[1u << kLutBits];
     __shared__ uint32_t s_wsum[kCbWaves];
     constexpr uint32_t kPer = (1u << kLutBits) / kCb;
@@ -704,11 +703,8 @@ __device__ __forceinline__ void dectab_tables(DecTab* T, const uint32_t* cntL, c
         for (uint32_t i = 0; i < kPer; ++i) {
             const uint32_t p = threadIdx.x * kPer + i;
             if (t1[p] == 0) {
-                lslot[p] = (uint16_t)base;
                 lpref[base] = (uint16_t)p;
                 ++base;
-            } else {
-                lslot[p] = 0xFFFF;
             }
         }
     }
@@ -744,14 +740,10 @@ __device__ __forceinline__ void dectab_tables(DecTab* T, const uint32_t* cntL, c
             const uint32_t L = v >> 16;
             if (L == 0 || L > (uint32_t)kLutBits - pos) break;
             e |= (uint64_t)(v & 0xFFFFu) << (16 * n);
-            if (n < 2) e |= (uint64_t)L << (56 + 4 * n);
             pos += L;
             ++n;
         }
-        if (n == 0) e = l2k && lslot[p] != 0xFFFF ? (uint64_t)lslot[p] << l2k : 0xFFFFull;
-        e |= (uint64_t)n << 48;
-        e |= (uint64_t)pos << 50;
-        T->lut[p] = e;
+        T->lut[p] = e | ((uint64_t)pos << 48) | ((uint64_t)(2 * n) << 54);
     }
 }
 

@@ -11,8 +11,9 @@
 //
 // Encode: one wavefront per chunk (k_huff_bits counts bits; after a scan of
 // the word counts k_huff_write packs with LDS atomic ORs and copies out).
-// Decode: one lane per chunk; a kLutBits-wide table yields up to three short
-// codewords per lookup, longer codewords use the canonical limit test.
+// Decode: one lane per sub-chunk; a kLutBits-wide table yields up to three short
+// codewords per lookup, longer codewords use a second table or the canonical
+// limit test.
 #include "ebc_dev.h"
 #include "ebc_launch.h"
 
@@ -526,79 +527,20 @@ __device__ __forceinline__ uint64_t window_at(const EBC_G uint32_t* __restrict__
     return a;
 }
 
-// Per-lane ring of a stream's 32-bit words in LDS, in two halves of one
-// 16-byte block each.  The next block is always in flight in registers: at a
-// wave-uniform refill point, every kRefillEvery steps, a lane whose reader
-// has entered the newer half writes the loaded block over the older half and
-// issues the load of the following one, so a load has a whole refill period
-// to land and bit top-ups read LDS only.  A step takes at most one word, so
-// between two refill points a reader advances at most kRefillEvery <=
-// kHalfWords words and never leaves the ring.
-constexpr uint32_t kRingWords = 8;
-constexpr uint32_t kHalfWords = kRingWords / 2;
-constexpr uint32_t kRingStride = kRingWords + 1;  // odd stride: no bank conflicts across lanes
-constexpr uint32_t kRefillEvery = 4;              // steps between refill points (<= kHalfWords)
-static_assert(kRefillEvery <= kHalfWords, "a reader must not outrun the ring between refills");
-
-struct WordRing {
-    uint32_t* ring;                       // this lane's slots in LDS
-    const EBC_G uint4* __restrict__ blk;  // aligned 16-byte blocks of the stream
-    uint32_t o, nblk;  // offset of the lane's word 0 inside block 0, blocks
-    uint32_t rd;       // next stream word to hand out
-    uint32_t wr;       // block-coordinate words [wr - kRingWords, wr) are in the ring
-    uint4 p;           // block wr / 4, in flight
-    __device__ __forceinline__ uint4 fetch(uint32_t j) const
-    {
-        if (j < nblk) {
-            const uint4 v = blk[j];
-            return v;
-        }
-        return make_uint4(0u, 0u, 0u, 0u);
-    }
-    // stream word rd (in the ring by the refill schedule); past the stream's
-    // end the slot holds zeros or stale words, which a valid stream never uses
-    __device__ __forceinline__ uint32_t peek() const { return ring[(rd + o) % kRingWords]; }
-    __device__ __forceinline__ void put(uint32_t* d, uint4 v)
-    {
-        d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
-    }
-    __device__ __forceinline__ void init(uint32_t* r, const EBC_G uint32_t* __restrict__ w, uint32_t nw)
-    {
-        ring = r;
-        const uintptr_t a = (uintptr_t)w;
-        o = (uint32_t)((a & 15u) >> 2);
-        blk = (const EBC_G uint4*)(a & ~(uintptr_t)15u);
-        nblk = (o + nw + 3) / 4;
-        put(ring, fetch(0));
-        put(ring + 4, fetch(1));
-        wr = kRingWords;
-        p = fetch(2);
-        rd = 0;
-    }
-    // wave-uniform refill point
-    __device__ __forceinline__ void refill()
-    {
-        if (wr < 4 * nblk && rd + o >= wr - kHalfWords) {
-            put(ring + (wr % kRingWords), p);
-            wr += kHalfWords;
-            p = fetch(wr / 4);
-        }
-    }
-};
-
-// One codeword longer than kLutBits at the head of a window: its length is
-// kLutBits + 1 plus the number of code-space ends the window lies at or above.
-// Returns the length (0 if the bits are not a codeword) and the symbol.
+// The canonical search for the codeword at the head of a window, among the
+// lengths from `from` on: its length is `from` plus the number of code-space
+// ends the window lies at or above.  Returns the length (0 if the bits are not a
+// codeword) and the symbol.
 struct LongCode {
     uint32_t maxl;
     const uint64_t* s_endv;
     const uint64_t* s_first;
     const uint32_t* s_off;
     const uint16_t* perm;  // global: only codewords longer than both table levels get here
-    __device__ __forceinline__ uint32_t decode(uint64_t w, uint32_t& sym) const
+    __device__ __forceinline__ uint32_t decode(uint64_t w, uint32_t from, uint32_t& sym) const
     {
-        uint32_t L = kLutBits + 1;
-        for (uint32_t l = kLutBits + 1; l < maxl; ++l) L += w >= s_endv[l] ? 1u : 0u;
+        uint32_t L = from;
+        for (uint32_t l = from; l < maxl; ++l) L += w >= s_endv[l] ? 1u : 0u;
         // the window is at or above the first length-L code by construction;
         // it must also be below the end of the length-L codes
         const uint64_t d = (w >> (64 - L)) - s_first[L];
@@ -615,263 +557,304 @@ struct LongCode {
 // the wave moves them to HBM in blocks of kFlush symbols per lane.  A block
 // leaves when every lane still decoding holds one; the copy is transposed
 // (four consecutive threads write one lane's 64-byte block), so a store
-// instruction writes sixteen whole 64-byte segments.  A lane that runs
-// kCap - 3 symbols ahead of its last flush waits (its steps are empty)
-// until the slower lanes have caught up, which never delays the wave: the
-// waiting lane is ahead of the slowest one.
+// instruction writes sixteen whole 64-byte segments.  A lane too far ahead of
+// its last flush skips groups of steps until the slower lanes have caught up,
+// which never delays the wave: the waiting lane is ahead of the slowest one.
 constexpr uint32_t kFlush = 32;
-constexpr uint32_t kCap = kFlush + 14;            // symbols a row holds; a step needs 3 free slots
-constexpr uint32_t kStageWords = ((kCap + 4) / 2) | 1;  // row stride (odd): kCap + 3 slots and more
-constexpr uint32_t kParts = kFlush / 8;           // 16-byte pieces of a flushed block
-constexpr uint32_t kCheckEvery = 4;               // steps between flush checks
-static_assert(2 * kStageWords >= kCap + 3, "the three slots of a step stay inside the row");
-static_assert(kCap - 2 > kFlush, "a waiting lane always holds a whole block");
-static_assert(kRefillEvery == kCheckEvery, "refill and flush checks share the step loop");
+constexpr uint32_t kParts = kFlush / 8;    // 16-byte pieces of a flushed block
+constexpr uint32_t kSteps = 4;             // table steps per group
+constexpr uint32_t kRowWords = 29;         // row stride (odd: no bank conflicts across lanes)
+constexpr uint32_t kGroupSyms = 1 + 3 * kSteps;  // symbols a group adds at most
+// symbols up to which a lane goes on: a group's last step writes three slots
+// from its start, at most kGroupSyms - 3 symbols after the group's
+constexpr uint32_t kRowGo = 2 * kRowWords - (kGroupSyms - 3) - 3;
+static_assert(kRowGo >= kFlush, "a waiting lane always holds a whole block");
+constexpr uint32_t kTailWords = (kRowGo + kGroupSyms - kFlush + 1) / 2;  // kept past a block, at most
+static_assert(kFlush / 2 + kTailWords <= kRowWords, "the kept words lie in the row");
+
+// LDS of a decode workgroup: the tables, then a row per lane.  The first-level
+// table sits at LDS address 0 (its index needs no base).
+struct DecLds {
+    uint64_t lut[1u << kLutBits];
+    uint32_t l2s[kL2Size + 2];  // entry l2n: 0
+    uint64_t first[65];
+    uint64_t endv[65];
+    uint32_t off[65];
+    uint32_t next;     // work groups of this workgroup handed out
+    uint32_t rows[1];  // lanes * kRowWords
+};
+uint32_t huff_decode_lds_bytes(uint32_t lanes) { return (uint32_t)offsetof(DecLds, rows) + lanes * kRowWords * 4; }
+
+// LDS at a byte address (the workgroup's dynamic LDS starts at 0: the kernel
+// has no static LDS), without an addition of a base.  The rows are written as
+// halfwords and words and read as words: the types may alias.
+typedef uint16_t __attribute__((may_alias)) u16_lds;
+typedef uint32_t __attribute__((may_alias)) u32_lds;
+typedef uint64_t __attribute__((may_alias)) u64_lds;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#if defined(__HIP_DEVICE_COMPILE__)
+#define EBC_LDS(T, a) (*(__attribute__((address_space(3))) T*)(uint32_t)(a))
+#else
+#define EBC_LDS(T, a) (*(T*)(uintptr_t)(a))
+#endif
 
 // One lane per sub-chunk (hs = min(hc, 256) symbols, its bit count and its
-// start from the archive's sub-chunk counts), kDecLanes lanes per workgroup.
+// start from the archive's sub-chunk counts), blockDim.x lanes per workgroup.
 // The decoded stream is the field's quant-codes, or its run values (RLE+VLE).
-// The main loop runs passes of kCheckEvery steps behind one refill point and
-// one flush check.  A step tops the bit buffer up to at least 32 bits
-// (branch-free, with the next stream word read from the ring one step
-// ahead), takes one kLutBits table entry (up to three codewords) and writes
-// its three symbol slots into the lane's row; only the decoded ones count.
-// Codewords longer than the table go through a second-level table or the
-// canonical limit test; longer than 32 bits, the lane leaves for an exact
-// path that reads windows straight from the stream.
-__global__ __launch_bounds__(kDecLanes) void k_huff_decode(const FieldDesc* __restrict__ F, int nf,
-                                                          const uint32_t* __restrict__ woff,
-                                                          const uint32_t* __restrict__ soff,
-                                                          const uint8_t* __restrict__ tabs,
-                                                          size_t tab_stride)
+//
+// The loop runs groups of kSteps table steps.  A group starts with the 64-bit
+// window at the lane's position, cut from the two 16-byte blocks of the stream
+// that the lane holds in registers (a third is in flight).  A step shifts the
+// window by the bits used so far, reads one table entry (up to three whole
+// codewords), stores its three symbol slots at the row's end (only the decoded
+// ones count) and adds the counts up: 13 vector instructions and three LDS
+// ones.  The slots go as one aligned dword and the halfword before or after
+// it: an LDS access across its alignment costs 64 cycles, a lane at a time,
+// against 8 for these two together.  kSteps * kLutBits bits never exceed the window.  A codeword longer than the
+// table makes its lane stand still to the end of the group (its entry counts
+// nothing); the next group first decodes it through the second-level table or
+// the canonical search.  A lane that passes its last symbol stops; the bits of
+// the at most kGroupSyms - 1 symbols too many are taken back after the loop.
+// Codewords longer than 32 bits leave for an exact path that reads windows
+// straight from the stream.  Flushed blocks are stored non-temporally: they
+// are not read before the kernel ends, and kept in the L2 they push out the
+// stream's lines, each of which a lane comes back to eight times (209 us
+// against 185 us on the 512^3 field).
+//
+// With the former step (bit buffer topped up from an LDS ring, exact clipping
+// and both table levels in every step: about 60 vector instructions) a wave
+// needed 900 cycles per step by itself and the kernel 257-290 us on a 512^3
+// field at 3.8 bits per symbol, 82 us on 256x256; now 185 and 59 us.  What
+// bounds it now is latency: a wave waits half of its time (table reads that
+// depend on each other, stream blocks), and the LDS rows allow 16 waves per CU.
+// Three, four or five steps per group make no difference on the large field.
+__global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restrict__ F, int nf,
+                                                      const uint32_t* __restrict__ woff,
+                                                      const uint32_t* __restrict__ soff,
+                                                      const uint8_t* __restrict__ tabs, size_t tab_stride)
 {
-    // one block so that the table sits at LDS address 0 (its index needs no base)
-    struct Lds {
-        uint64_t lut[1u << kLutBits];
-        uint64_t first[65];
-        uint64_t endv[65];
-        uint32_t l2s[kL2Size];
-        uint32_t off[65];
-        uint32_t ring[kDecLanes * kRingStride];
-        uint32_t stage[kDecLanes * kStageWords];
-    };
-    __shared__ Lds sm;
-    uint64_t* const lut = sm.lut;
-    uint32_t* const l2s = sm.l2s;
-    uint64_t* const s_first = sm.first;
-    uint64_t* const s_endv = sm.endv;
-    uint32_t* const s_off = sm.off;
-    uint32_t* const s_ring = sm.ring;
-    uint32_t* const s_stage = sm.stage;
+    extern __shared__ uint64_t lds64[];
+    DecLds& sm = *(DecLds*)lds64;
+    const uint32_t lanes = blockDim.x;
     const uint32_t t = blockIdx.x;
     const int f = find_field<&FieldDesc::hdwg_base>(F, nf, t);
     const FieldDesc& fd = F[f];
     EBC_G FieldDyn* dy = fd.dyn;
     if (dy->status != ST_OK || !huff_codec(dy->codec)) return;
     const DecTab* __restrict__ T = (const DecTab*)(tabs + (size_t)f * tab_stride);
-    for (uint32_t i = threadIdx.x; i < (1u << kLutBits); i += kDecLanes) lut[i] = T->lut[i];
     const uint32_t l2k = T->l2k, l2n = T->l2n;
     const uint32_t l2sub = (1u << (kLutBits + l2k)) - l2n;  // first long prefix << l2k
-    for (uint32_t i = threadIdx.x; i < l2n; i += kDecLanes) l2s[i] = T->l2[i];
-    if (threadIdx.x < 65) {
-        s_first[threadIdx.x] = T->first[threadIdx.x];
-        s_endv[threadIdx.x] = T->endv[threadIdx.x];
-        s_off[threadIdx.x] = T->offset[threadIdx.x];
+    {
+        const uint4* src = (const uint4*)T->lut;
+        uint4* dst = (uint4*)sm.lut;
+#pragma unroll 8
+        for (uint32_t i = threadIdx.x; i < (1u << kLutBits) / 2; i += lanes) dst[i] = src[i];
+        for (uint32_t i = threadIdx.x; i <= l2n; i += lanes) sm.l2s[i] = i < l2n ? T->l2[i] : 0u;
+        for (uint32_t i = threadIdx.x; i < 65; i += lanes) {
+            sm.first[i] = T->first[i];
+            sm.endv[i] = T->endv[i];
+            sm.off[i] = T->offset[i];
+        }
     }
+    if (threadIdx.x == 0) sm.next = 0;
     const uint32_t maxl = T->max_len;
     __syncthreads();
+    // from here on LDS is also reached by byte address (EBC_LDS)
+    asm volatile("" ::"v"((uint32_t)(uintptr_t)lds64) : "memory");
     const uint32_t lane = lane_id();
-    const uint32_t sub0 = (t - fd.hdwg_base) * kDecLanes + (threadIdx.x & ~(uint32_t)(kWave - 1));
-    if (sub0 >= fd.n_sub) return;  // whole wave past the field's sub-chunks
-    const uint32_t sub = sub0 + lane;
-    const bool live = sub < fd.n_sub;
     const uint32_t hs = fd.hs, per = fd.hc / hs;
-    const uint32_t c = live ? sub / per : 0;
     const EBC_G uint8_t* arc = fd.arc;
-    const uint32_t nbits = live ? ((const EBC_G uint16_t*)(arc + fd.off_sbits))[sub] : 0u;
-    // start bit of the sub-chunk inside the field's word stream
-    const uint64_t b0 = live ? (uint64_t)(woff[fd.hch_base + c] - woff[fd.hch_base]) * 32 +
-                                   soff[fd.sub_base + sub]
-                             : 0ull;
-    const uint64_t lo = (uint64_t)sub * hs;
-    const uint32_t want = live ? (uint32_t)min<uint64_t>(hs, fd.hn - lo) : 0u;
-    const uint32_t w0 = (uint32_t)(b0 >> 5);
-    const uint32_t skip = (uint32_t)(b0 & 31);
-    const uint32_t nwl = live ? (skip + nbits + 31) / 32 : 0u;  // words the lane may read
-    // the chunk words were checked against the archive's word count, and a
-    // sub-chunk ends inside its chunk by construction of the offsets
-    const EBC_G uint32_t* __restrict__ words = (const EBC_G uint32_t*)(arc + fd.off_words) + w0;
-    EBC_G uint16_t* __restrict__ out = fd.hsym + lo;
-    const LongCode lc{maxl, s_endv, s_first, s_off, T->perm};
-    uint32_t* row = s_stage + threadIdx.x * kStageWords;
-    uint16_t* row16 = (uint16_t*)row;
-    const uint32_t* wave_rows = s_stage + (threadIdx.x - lane) * kStageWords;
-
-    WordRing wr;
-    wr.init(s_ring + threadIdx.x * kRingStride, words, nwl);
-    uint64_t buf = (uint64_t)wr.peek() << 32;
-    ++wr.rd;
-    buf |= wr.peek();
-    ++wr.rd;
-    buf <<= skip;
-    uint32_t valid = 64 - skip;
-    uint32_t j = 0, sp = 0, flushed = 0;
-    uint32_t nflush = 0;  // flushes the wave has made
-    bool slow = false;
-    bool act = want > 0;
-    uint32_t nxt = wr.peek();
-    // a block of kFlush symbols leaves when every lane still decoding has one
-    auto flush = [&]() {
-        if (__all(sp >= kFlush || !act)) {
-            // every lane holding a block has taken part in every flush so far
-            // (a lane left out had stopped decoding with fewer than kFlush
-            // symbols and never gains more), so its offset is wave-uniform
-            const uint64_t has = ballot(sp >= kFlush);
-            const uint32_t flw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(nflush * kFlush));
-#pragma unroll
-            for (uint32_t k = 0; k < kParts; ++k) {
-                const uint32_t piece = k * kWave + lane;
-                const uint32_t L = piece / kParts, part = piece % kParts;
-                if ((has >> L) & 1u) {
-                    const uint32_t* src = wave_rows + L * kStageWords + part * 4;
-                    const uint4 v = make_uint4(src[0], src[1], src[2], src[3]);
-                    *(EBC_G uint4*)(fd.hsym + (uint64_t)(sub0 + L) * hs + flw + part * 8) = v;
-                }
-            }
-            ++nflush;
-            if (sp >= kFlush) {
-                // the symbols past the block (at most kCap - kFlush) move to
-                // the front of the row
-#pragma unroll
-                for (uint32_t w = 0; w < (kCap - kFlush + 1) / 2; ++w) row[w] = row[kFlush / 2 + w];
-                sp -= kFlush;
-                flushed += kFlush;
-            }
-        }
+    const EBC_G uint32_t* stream = (const EBC_G uint32_t*)(arc + fd.off_words);
+    const LongCode lc{maxl, sm.endv, sm.first, sm.off, T->perm};
+    // LDS byte addresses of the lane's row
+    const uint32_t row = (uint32_t)offsetof(DecLds, rows) + threadIdx.x * (kRowWords * 4);
+    const uint32_t lim_go = row + 2 * kRowGo, lim_flush = row + 2 * kFlush;
+    // this lane's 16-byte piece of a flushed block: row lane / 4 of each
+    // sixteen, part lane % 4
+    const uint32_t fsrc = (uint32_t)offsetof(DecLds, rows) +
+                          ((threadIdx.x - lane + lane / kParts) * kRowWords + (lane % kParts) * 4) * 4;
+    auto row16b = [](uint32_t a) {
+        return u32x4{EBC_LDS(const u32_lds, a), EBC_LDS(const u32_lds, a + 4), EBC_LDS(const u32_lds, a + 8),
+                     EBC_LDS(const u32_lds, a + 12)};
     };
-    while (__any(act)) {
-        wr.refill();
-#pragma unroll
-        for (uint32_t u = 0; u < kCheckEvery; ++u) {
-            {
-                const bool need = valid < 32;
-                buf |= need ? ((uint64_t)nxt << ((32u - valid) & 63u)) : 0ull;
-                valid += need ? 32u : 0u;
-                wr.rd += need ? 1u : 0u;
-                // only lanes that took a word read the next one (fewer LDS bank
-                // accesses; the word at rd is in the ring by the refill schedule)
-                if (need) nxt = wr.peek();
+    // The field's groups of 64 sub-chunks go to its workgroups in turn (so that
+    // each has a mix of dense and sparse parts), and a workgroup's waves take
+    // its groups as they finish: waves differ by a factor of three in steps.
+    const uint32_t n_grp = (fd.n_sub + kWave - 1) / kWave;
+    for (;;) {
+        uint32_t gi = 0;
+        if (lane == 0) gi = atomicAdd(&sm.next, 1u);
+        gi = __builtin_amdgcn_readfirstlane(gi);
+        const uint32_t g = gi * fd.hdwg_units + (t - fd.hdwg_base);
+        if (gi >= n_grp || g >= n_grp) break;
+        const uint32_t sub0 = g * kWave;
+        const uint32_t sub = sub0 + lane;
+        const bool live = sub < fd.n_sub;
+        const uint32_t c = live ? sub / per : 0;
+        const uint32_t nbits = live ? ((const EBC_G uint16_t*)(arc + fd.off_sbits))[sub] : 0u;
+        // start bit of the sub-chunk inside the field's word stream
+        const uint64_t b0 = live ? (uint64_t)(woff[fd.hch_base + c] - woff[fd.hch_base]) * 32 +
+                                       soff[fd.sub_base + sub]
+                                 : 0ull;
+        const uint64_t lo = (uint64_t)sub * hs;
+        const uint32_t want = live ? (uint32_t)min<uint64_t>(hs, fd.hn - lo) : 0u;
+        const uint32_t w0 = (uint32_t)(b0 >> 5);
+        const uint32_t skip = (uint32_t)(b0 & 31);
+        const uint32_t nwl = live ? (skip + nbits + 31) / 32 : 0u;  // words the lane may read
+        // the chunk words were checked against the archive's word count, and a
+        // sub-chunk ends inside its chunk by construction of the offsets
+        const EBC_G uint32_t* __restrict__ words = stream + w0;
+
+        // Stream position: pm = (bit position) - 1, counted from the first bit
+        // of block A, so that the window from the next bit on is two funnel
+        // shifts by ~pm.  The blocks are 16-byte aligned and start one word
+        // before the lane's first (the archive's header and sections lie before
+        // the words), which keeps pm from going below zero.  Blocks past the
+        // lane's words are not read (the last one is read again instead; its
+        // bits count for nothing).
+        const uintptr_t wa = (uintptr_t)words - 4;
+        const uint32_t ob = (uint32_t)((wa & 15u) >> 2);
+        const EBC_G uint4* __restrict__ blk = (const EBC_G uint4*)(wa & ~(uintptr_t)15u);
+        const uint32_t last = (ob + 1 + nwl + 3) / 4 - 1;
+        uint4 A = make_uint4(0u, 0u, 0u, 0u), B = A, P = A;
+        if (live) A = blk[0], B = blk[min(1u, last)], P = blk[min(2u, last)];
+        uint32_t jb = 0;  // A is block jb
+        uint32_t pm = 32 * (ob + 1) + skip - 1;
+
+        uint32_t sp = row;              // the next symbol's place
+        uint32_t endp = row + 2 * want; // where the last symbol ends (moves with the flushes)
+        uint32_t over = 0;    // symbols decoded past the last one
+        uint32_t nflush = 0;  // flushes the wave has made
+        bool stuck = false;   // a codeword longer than the table is next
+        bool slow = false;
+        bool act = want > 0;
+        EBC_G uint16_t* const fdst = fd.hsym + (uint64_t)(sub0 + lane / kParts) * hs + (lane % kParts) * 8;
+
+        while (__any(act)) {
+            if (pm >= 128) {
+                A = B;
+                B = P;
+                pm -= 128;
+                ++jb;
+                P = blk[min(jb + 2, last)];
             }
-            // the prefixes that start a codeword longer than the table are the
-            // top nlong ones and own consecutive blocks in prefix order, so the
-            // second-level index follows from the bits alone and its read
-            // overlaps the table's (clamped: other lanes read entry 0)
-            uint32_t i2 = ((uint32_t)(buf >> 32) >> (32 - kLutBits - l2k)) - l2sub;
-            i2 = i2 < l2n ? i2 : 0u;
-            const uint32_t v2 = l2s[i2];
-            const uint64_t e = lut[(uint32_t)(buf >> (64 - kLutBits))];
-            const uint32_t eh = (uint32_t)(e >> 32);
-            // keeps the read above the branch; LDS reads return in order, so
-            // the wait for the table entry covers it
-            asm volatile("" ::"v"(v2), "v"(eh));
-            uint32_t n = (eh >> 16) & 3u;
-            uint32_t tl = (eh >> 18) & 63u;
-            uint32_t s01 = (uint32_t)e, s2 = eh & 0xFFFFu;
-            if (act && n == 0) {
-                // second level, then the canonical search for longer codewords
-                uint32_t sym = 0, L = 0;
-                const uint32_t base = (uint32_t)e & 0xFFFFu;
-                if (base != 0xFFFFu) {
-                    const uint32_t v = v2;
-                    L = v >> 16;
-                    sym = v & 0xFFFFu;
-                }
-                if (L == 0) L = lc.decode(buf, sym);
-                if (L == 0 || L > 32) {
+            // words pm / 32 .. pm / 32 + 3 of A and B
+            const bool k2 = (pm & 64u) != 0, k1 = (pm & 32u) != 0;
+            const uint32_t u0 = k2 ? A.z : A.x, u1 = k2 ? A.w : A.y, u2 = k2 ? B.x : A.z, u3 = k2 ? B.y : A.w;
+            const uint32_t x0 = k1 ? u1 : u0, x1 = k1 ? u2 : u1, x2 = k1 ? u3 : u2;
+            uint32_t hi = __builtin_amdgcn_alignbit(x0, x1, ~pm), lw = __builtin_amdgcn_alignbit(x1, x2, ~pm);
+            bool go = act && sp <= lim_go;
+            if (go && stuck) {
+                // the prefixes that start a codeword longer than the table are
+                // the top ones and own consecutive blocks in prefix order, so
+                // the second-level index follows from the bits (entry l2n,
+                // which is 0, for any other)
+                const uint32_t v = sm.l2s[min((hi >> (32 - kLutBits - l2k)) - l2sub, l2n)];
+                uint32_t sym = v, L = v >> 16;
+                if (L == 0) L = lc.decode(((uint64_t)hi << 32) | lw, kLutBits + 1, sym);
+                EBC_LDS(u16_lds, sp) = (uint16_t)sym;
+                sp += 2;
+                // the window moves on by L bits (13 to 32)
+                const uint32_t u4 = k2 ? B.z : B.x, x3 = k1 ? u4 : u3;
+                const uint32_t l2w = __builtin_amdgcn_alignbit(x2, x3, ~pm);
+                hi = __builtin_amdgcn_alignbit(hi, lw, 32 - L);
+                lw = __builtin_amdgcn_alignbit(lw, l2w, 32 - L);
+                pm += L;
+                if (__builtin_expect(L == 0 || L > 32, 0)) {
+                    sp -= 2;
+                    pm -= L;
                     slow = true;
-                    act = false;
+                    act = go = false;
                 }
-                n = 1;
-                tl = L;
-                s01 = sym;
             }
-            // the step's three symbol slots (only the decoded ones are kept;
-            // sp <= kCap) in two LDS stores: the dword at halfword
-            // (sp + 1) & ~1 and the halfword left over.  The LDS pipe, not the
-            // VALU, bounds this loop: three halfword stores took 14% longer at
-            // rel 1e-4, and one store of two dwords (with the previous symbol
-            // kept in a register) was no faster than three.
-            {
-                const bool odd = (sp & 1u) != 0;
-                // the halfword sits just before (odd sp) or just after the dword
-                uint32_t* const dw = (uint32_t*)((char*)row + ((2 * sp + 2) & ~3u));
-                *dw = odd ? (s01 >> 16) | (s2 << 16) : s01;
-                *(uint16_t*)((char*)dw + (odd ? -2 : 4)) = (uint16_t)(odd ? s01 : s2);
+            if (go) {
+                const uint64_t buf = ((uint64_t)hi << 32) | lw;
+                uint32_t acc = 0;  // low six bits: bits used in this group
+                uint32_t n2 = 0;
+#pragma unroll
+                for (uint32_t u = 0; u < kSteps; ++u) {
+                    const uint32_t wh = (uint32_t)((buf << (acc & 63u)) >> 32);
+                    const uint64_t e =
+                        EBC_LDS(const u64_lds, (wh >> (32 - kLutBits - 3)) & (((1u << kLutBits) - 1) << 3));
+                    const uint32_t eh = (uint32_t)(e >> 32);
+                    // odd places (sp % 4 == 2): the halfword s0 at sp, the dword
+                    // s1 s2 after it; even ones: the dword s0 s1 at sp, then s2
+                    const uint32_t odd = sp & 2u;
+                    EBC_LDS(u32_lds, sp + odd) = __builtin_amdgcn_alignbit(eh, (uint32_t)e, sp << 3);
+                    EBC_LDS(u16_lds, sp + 4 - 2 * odd) = (uint16_t)(odd ? (uint32_t)e : eh);
+                    acc += eh >> 16;
+                    n2 = (eh >> 22) & 7u;
+                    sp += n2;
+                }
+                pm += acc & 63u;
+                stuck = n2 == 0;
             }
-            const uint32_t left = want - j;
-            if (__builtin_expect(act && n > left, 0)) {
-                // the lane's last symbols take only the leading codewords (the
-                // bit count is checked against the sub-chunk's); a branch taken
-                // once per lane, kept out of the step by the empty asm
-                tl = ((eh >> 24) & 15u) + (left == 2 ? eh >> 28 : 0u);
-                n = left;
-                asm volatile("" ::: "memory");
+            if (act && sp >= endp) {
+                over = (sp - endp) / 2;
+                sp = endp;
+                act = false;
             }
-            const bool go = act && sp + 3 <= kCap;
-            n = go ? n : 0u;
-            tl = go ? tl : 0u;
-            j += n;
-            sp += n;
-            buf <<= tl;
-            valid -= tl;
-            act = act && j < want;
-        }
-        flush();
-    }
-    // exact path, one codeword at a time from a window read straight from the
-    // stream (lanes that met a codeword longer than 32 bits)
-    bool bad = false;
-    uint32_t pos = 32 * wr.rd - valid;  // bits consumed, counted from word w0
-    while (slow && j < want) {
-        const uint64_t w = window_at(words, nwl, pos);
-        const uint64_t e = lut[(uint32_t)(w >> (64 - kLutBits))];
-        uint32_t sym = (uint32_t)e & 0xFFFFu;
-        uint32_t L = (uint32_t)(e >> 56) & 15u;
-        if (((e >> 48) & 3u) == 0) {
-            L = 0;
-            const uint32_t base = (uint32_t)e & 0xFFFFu;
-            if (base != 0xFFFFu) {
-                const uint32_t v = l2s[base + (uint32_t)((w << kLutBits) >> (64 - l2k))];
-                L = v >> 16;
-                sym = v & 0xFFFFu;
-            }
-            if (L == 0) L = lc.decode(w, sym);
-            if (L == 0) {
-                bad = true;
-                break;
+            // a block of kFlush symbols leaves when every lane still decoding
+            // has one
+            if (__all(sp >= lim_flush || !act)) {
+                // every lane holding a block has taken part in every flush so
+                // far (a lane left out had stopped decoding with fewer than
+                // kFlush symbols and never gains more), so its offset is
+                // wave-uniform
+                const uint64_t has = ballot(sp >= lim_flush);
+                EBC_G uint16_t* dst = fdst + nflush * kFlush;
+#pragma unroll
+                for (uint32_t k = 0; k < kParts; ++k) {
+                    if ((has >> (k * (kWave / kParts) + lane / kParts)) & 1u)
+                        __builtin_nontemporal_store(row16b(fsrc + k * (kWave / kParts) * kRowWords * 4),
+                                                    (EBC_G u32x4*)(dst + k * (kWave / kParts) * hs));
+                }
+                ++nflush;
+                if (sp >= lim_flush) {
+                    // the symbols past the block move to the front of the row
+#pragma unroll
+                    for (uint32_t w = 0; w < kTailWords; ++w)
+                        EBC_LDS(u32_lds, row + 4 * w) = EBC_LDS(const u32_lds, row + 2 * kFlush + 4 * w);
+                    sp -= 2 * kFlush;
+                    endp -= 2 * kFlush;
+                }
             }
         }
-        row16[sp++] = (uint16_t)sym;
-        ++j;
-        pos += L;
-        if (sp >= kCap) {
-            // a full row: its leading block goes straight to HBM
-            for (uint32_t k = 0; k < kFlush; ++k) out[flushed + k] = row16[k];
-            for (uint32_t w = 0; w < kStageWords - kFlush / 2; ++w) row[w] = row[kFlush / 2 + w];
-            sp -= kFlush;
-            flushed += kFlush;
+        // position after the lane's last symbol, counted from word w0
+        uint32_t pos = 128 * jb + pm + 1 - 32 * (ob + 1);
+        const EBC_G uint8_t* lens = arc + kHdr;  // code lengths, one byte per symbol
+        for (uint32_t i = 0; i < over; ++i) pos -= lens[EBC_LDS(const u16_lds, sp + 2 * i)];
+        // exact path, one codeword at a time from a window read straight from
+        // the stream (lanes that met a codeword longer than 32 bits)
+        uint32_t spi = (sp - row) / 2;
+        uint32_t left = (endp - sp) / 2;  // symbols still to decode (0 unless slow)
+        uint32_t flushed = want - left - spi;
+        EBC_G uint16_t* __restrict__ out = fd.hsym + lo;
+        bool bad = false;
+        if (slow) {
+            for (uint32_t k = 0; k < spi; ++k) out[flushed + k] = EBC_LDS(const u16_lds, row + 2 * k);
+            flushed += spi;
+            spi = 0;
+            for (; left > 0; --left) {
+                uint32_t sym = 0;
+                const uint32_t L = lc.decode(window_at(words, nwl, pos), 1, sym);
+                if (L == 0) {
+                    bad = true;
+                    break;
+                }
+                out[flushed++] = (uint16_t)sym;
+                pos += L;
+            }
         }
+        if (live) {
+            // what is left in the row: whole 16-byte groups, then single symbols
+            uint32_t k = 0;
+            for (; k + 8 <= spi; k += 8) *(EBC_G u32x4*)(out + flushed + k) = row16b(row + 2 * k);
+            for (; k < spi; ++k) out[flushed + k] = EBC_LDS(const u16_lds, row + 2 * k);
+        }
+        // the sub-chunk must take exactly its stored bit count
+        if (live && (bad || pos != skip + nbits)) atomicMin(&dy->status, ST_ERR_ARCHIVE);
     }
-    if (!bad && live) {
-        // what is left in the row: whole 16-byte groups, then single symbols
-        uint32_t k = 0;
-        for (; k + 8 <= sp; k += 8)
-            *(EBC_G uint4*)(out + flushed + k) = make_uint4(row[k / 2], row[k / 2 + 1], row[k / 2 + 2],
-                                                             row[k / 2 + 3]);
-        for (; k < sp; ++k) out[flushed + k] = row16[k];
-    }
-    // the sub-chunk must take exactly its stored bit count
-    if (live && (bad || pos != skip + nbits)) atomicMin(&dy->status, ST_ERR_ARCHIVE);
 }
 
 // Huffman decompression prologue, one thread per chunk: the in-chunk start
@@ -978,13 +961,28 @@ hipError_t launch_huff_prep(const FieldDesc* F, int nf, uint32_t units, uint32_t
     return hipGetLastError();
 }
 
-hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, const uint32_t* woff,
-                              const uint32_t* soff, const uint8_t* tabs, size_t tab_stride,
-                              hipStream_t s)
+// Decode workgroups of a call whose streams make n_grp groups of 64
+// sub-chunks: lanes per workgroup, and groups that a workgroup takes.  The
+// tables take 42 KB of LDS per workgroup and a lane 116 bytes, so a CU holds
+// one workgroup of 1024 lanes (16 waves), two of 256 or three of 64.  A call
+// that leaves CUs idle with wide workgroups is split finer; a large one gets
+// one workgroup per CU, so that the tables are loaded once and the waves even
+// out.
+void huff_decode_split(uint64_t n_grp, uint32_t* lanes, uint32_t* groups)
+{
+    constexpr uint32_t kCus = 256;
+    if (n_grp <= 3 * kCus) *lanes = 64, *groups = 1;
+    else if (n_grp <= 2 * kCus * 4) *lanes = 256, *groups = 4;
+    else *lanes = 1024, *groups = n_grp <= kCus * 16 ? 16 : (uint32_t)((n_grp + kCus - 1) / kCus);
+}
+
+hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t lanes,
+                              const uint32_t* woff, const uint32_t* soff, const uint8_t* tabs,
+                              size_t tab_stride, hipStream_t s)
 {
     if (!units) return hipSuccess;
-    hipLaunchKernelGGL(k_huff_decode, dim3(units), dim3(kDecLanes), 0, s, F, nf, woff, soff, tabs,
-                       tab_stride);
+    hipLaunchKernelGGL(k_huff_decode, dim3(units), dim3(lanes), huff_decode_lds_bytes(lanes), s, F, nf, woff,
+                       soff, tabs, tab_stride);
     return hipGetLastError();
 }
 
