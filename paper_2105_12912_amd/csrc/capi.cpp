@@ -840,7 +840,7 @@ int enqueue_decompress(Batch& B, hipStream_t s, Timer& T)
         HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
         HIP_TRY(launch_words_check(B.d_fd, nf, B.d_wcnt, s));
         T.mark("dectab");
-        HIP_TRY(launch_dectab(B.d_fd, nf, B.d_tabs, B.tab_stride, B.max_bins, s));
+        HIP_TRY(launch_dectab(B.d_fd, nf, B.d_tabs, B.tab_stride, s));
         T.mark("huffman_decode");
         HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.dec_lanes, B.d_wcnt, B.d_soff, B.d_tabs, B.tab_stride, s));
     }

@@ -37,8 +37,7 @@ hipError_t launch_hist_reduce(const FieldDesc* F, int nf, uint32_t n_bins, hipSt
 // codebook
 size_t codebook_lds_bytes(uint32_t n_bins);
 hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, hipStream_t s);
-hipError_t launch_dectab(const FieldDesc* F, int nf, uint8_t* tabs, size_t stride, uint32_t max_bins,
-                         hipStream_t s);
+hipError_t launch_dectab(const FieldDesc* F, int nf, uint8_t* tabs, size_t stride, hipStream_t s);
 size_t codebook_wide_scratch_bytes(uint32_t n_bins);
 
 // compressibility estimates (histogram bounds; madogram over `samples` pairs)
