@@ -235,18 +235,17 @@ struct Batch {
     std::vector<Group> groups;
     uint32_t tot_range = 0, tot_seg = 0, tot_ow = 0, tot_hch = 0, tot_hwg = 0, tot_hdwg = 0,
              tot_rt = 0, tot_runs = 0, tot_sc = 0, tot_rl = 0, tot_fx = 0, tot_sub = 0, tot_hpwg = 0;
-    uint32_t max_rle_units = 0;
     bool overflow = false;  // some work-unit total of the batch reached 2^32
     uint32_t scan = 0;      // scan schedule of the call (largest tuned value of its fields)
     FieldDesc* d_fd = nullptr;
     FieldDyn* d_dyn = nullptr;
     uint32_t *d_seg = nullptr, *d_wcnt = nullptr, *d_rcnt = nullptr, *d_starts = nullptr, *d_tmap = nullptr,
              *d_tmp = nullptr, *d_soff = nullptr;
+    uint32_t tot_scan = 0;  // compress: entries of the array that starts at d_seg
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
     uint32_t dec_lanes = 0, dec_groups = 0;  // decompress: lanes and 64-sub-chunk groups per decode workgroup
-    uint64_t* d_result = nullptr;
     EstDev* d_est = nullptr;
     uint64_t ws_bytes = 0;
 };
@@ -330,7 +329,6 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         d.sub_base = sub.add(g.n_sub), d.n_sub = g.n_sub;
         d.hpwg_base = hpwg.add(g.hpwg_units), d.hpwg_units = g.hpwg_units;
         d.rt_base = rt.add(g.n_rt), d.n_rt = g.n_rt;
-        B.max_rle_units = std::max(B.max_rle_units, cdiv(g.n, kBlock));
     }
     B.tot_range = (uint32_t)range.v, B.tot_seg = (uint32_t)seg.v, B.tot_ow = (uint32_t)ow.v;
     B.tot_hch = (uint32_t)hch.v, B.tot_hwg = (uint32_t)hwg.v;
@@ -390,12 +388,18 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
     Bump bp{ws};
     B.d_fd = bp.take<FieldDesc>(sizeof(FieldDesc) * B.nf);
     B.d_dyn = bp.take<FieldDyn>(sizeof(FieldDyn) * B.nf);
-    B.d_seg = bp.take<uint32_t>(4ull * (B.tot_seg + 1));
-    B.d_wcnt = bp.take<uint32_t>(4ull * (B.tot_hch + 1));
-    B.d_rcnt = bp.take<uint32_t>(4ull * (B.tot_rt + 1));
-    const uint32_t big = std::max({B.tot_seg, B.tot_hch, B.tot_rt});
-    B.d_tmp = bp.take<uint32_t>(4ull * scan_tmp_words(big));
-    B.d_result = bp.take<uint64_t>(16);
+    // The outlier, word and run counts lie behind each other and are scanned as
+    // one array (only differences of two offsets of one field are used).  With
+    // VLE the run counts are needed before the word counts exist: an array of
+    // their own.
+    const bool vle = P.codec == EBC_CODEC_RLE_VLE || P.codec == EBC_CODEC_AUTO_VLE;
+    const uint64_t n_scan = (uint64_t)B.tot_seg + B.tot_hch + (vle ? 0 : B.tot_rt);
+    if (n_scan >= 0xFFFFFFFFull) B.overflow = true;
+    B.tot_scan = (uint32_t)n_scan;
+    B.d_seg = bp.take<uint32_t>(4ull * (n_scan + 1));
+    B.d_wcnt = B.d_seg ? B.d_seg + B.tot_seg : nullptr;
+    B.d_rcnt = vle ? bp.take<uint32_t>(4ull * (B.tot_rt + 1)) : B.d_seg ? B.d_wcnt + B.tot_hch : nullptr;
+    B.d_tmp = bp.take<uint32_t>(4ull * std::max(scan_tmp_words(B.tot_scan), scan_tmp_words(B.tot_rt)));
     B.d_est = bp.take<EstDev>(sizeof(EstDev) * B.nf);
     for (int k = 0; k < B.nf; ++k) {
         const int i = B.order[k];
@@ -416,17 +420,24 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
         d.slot = (uint32_t)B.order[k];
         d.q = bp.take<uint16_t>(2 * g.n);
         d.dsc = bp.take<int32_t>(4 * g.n);
-        d.rstart = (uint32_t*)d.dsc;  // used only after the outliers are written
         d.hist = bp.take<uint32_t>(4ull * P.n_bins);
-        d.hpart = bp.take<uint32_t>(4ull * hist_slots(P.n_bins) * d.hrows);
+        // The partial histograms are dead once the codebook is built; the
+        // run-start flags of run-length coding (a bit per code) take their
+        // place where they fit, or get room on fields beyond 2^24 values.
+        // Smaller fields with few bins go without (the write pass then reads
+        // the codes again), so that no workspace grows up to that size.
+        const uint64_t hp = 4ull * hist_slots(P.n_bins) * d.hrows, fl = 2ull * kBlock * g.n_rt;
+        const bool flags = P.codec != EBC_CODEC_HUFFMAN && (fl <= hp || g.n > (1u << 24));
+        d.hpart = bp.take<uint32_t>(flags ? std::max(hp, fl) : hp);
+        d.rflag = flags ? (uint16_t*)d.hpart : nullptr;
         d.rpart = bp.take<uint32_t>(24ull * g.range_units);  // room for 64-bit keys
+        d.rfirst = (uint32_t*)d.rpart;                       // 4 tiles per unit, after the range
         d.code = bp.take<uint64_t>(8ull * P.n_bins);
         d.len = bp.take<uint8_t>(P.n_bins);
         d.cbs = P.n_bins > kMaxBins ? bp.take<uint8_t>(codebook_wide_scratch_bytes(P.n_bins)) : nullptr;
         d.hbits = bp.take<uint32_t>(4ull * g.n_hch);
         // RLE+VLE requested: the run values (at most N, and the encoder may
         // read 30 bytes past the stream) and their histogram
-        const bool vle = P.codec == EBC_CODEC_RLE_VLE || P.codec == EBC_CODEC_AUTO_VLE;
         d.vsym = vle ? bp.take<uint16_t>(2 * g.n + 64) : nullptr;
         d.vhist = vle ? bp.take<uint32_t>(4ull * P.n_bins) : nullptr;
     }
@@ -484,7 +495,9 @@ struct Timer {
 };
 
 // ------------------------------------------------------------------ pipelines
-int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, bool debug_stop = false)
+// res: result records (device), or NULL.  debug_stop: only up to the code
+// histogram and the scanned outlier counts.
+int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, uint64_t* res, bool debug_stop = false)
 {
     const int nf = B.nf;
     HIP_TRY(upload_descs(B.fd.data(), nf, B.d_fd, s));
@@ -496,40 +509,39 @@ int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, bool de
     for (const auto& G : B.groups)
         HIP_TRY(launch_construct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles, G.blocks,
                                  P.n_bins, B.d_seg, s));
-    T.mark("hist_reduce");
-    HIP_TRY(launch_hist_reduce(B.d_fd, nf, P.n_bins, s));
-    T.mark("scan_outliers");
-    HIP_TRY(launch_scan(B.d_seg, B.tot_seg, B.d_tmp, s, B.scan));
-    if (debug_stop) return EBC_OK;
+    // small fields: the codebook adds their few partial histograms itself
+    bool direct = !debug_stop && P.n_bins <= kMaxBins;
+    for (const auto& d : B.fd) direct = direct && d.hrows <= kHistDirect;
+    if (!direct) {
+        T.mark("hist_reduce");
+        HIP_TRY(launch_hist_reduce(B.d_fd, nf, P.n_bins, s));
+    }
+    if (debug_stop) {
+        HIP_TRY(launch_scan(B.d_seg, B.tot_seg, B.d_tmp, s, B.scan));
+        return EBC_OK;
+    }
     T.mark("codebook");
-    HIP_TRY(launch_codebook(B.d_fd, nf, P.n_bins, 0, s));
+    HIP_TRY(launch_codebook(B.d_fd, nf, P.n_bins, 0, direct, s));
     const bool vle = P.codec == EBC_CODEC_RLE_VLE || P.codec == EBC_CODEC_AUTO_VLE;
+    const uint32_t rt = P.codec == EBC_CODEC_HUFFMAN ? 0 : B.tot_rt;  // run-length tiles, if any field may have them
     T.mark("encode_count");
-    HIP_TRY(launch_huff_bits(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_wcnt, 0, s));
-    HIP_TRY(launch_rle_count(B.d_fd, nf, B.tot_rt, B.d_rcnt, s));
-    T.mark("encode_scan");
-    HIP_TRY(launch_scan(B.d_rcnt, B.tot_rt, B.d_tmp, s, B.scan));
+    HIP_TRY(launch_encode_count(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_wcnt, 0, rt, B.d_rcnt, s));
     if (vle) {
+        T.mark("encode_scan");
+        HIP_TRY(launch_scan(B.d_rcnt, B.tot_rt, B.d_tmp, s, B.scan));
         // RLE+VLE fields: the run values become a stream of their own with a
         // codebook of their own, counted like the codes of a Huffman field
         T.mark("rle_vle");
         HIP_TRY(launch_rle_vle_prep(B.d_fd, nf, B.tot_rt, B.d_rcnt, P.n_bins, s));
-        HIP_TRY(launch_codebook(B.d_fd, nf, P.n_bins, 1, s));
-        HIP_TRY(launch_huff_bits(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_wcnt, 1, s));
+        HIP_TRY(launch_codebook(B.d_fd, nf, P.n_bins, 1, false, s));
+        HIP_TRY(launch_encode_count(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_wcnt, 1, 0, nullptr, s));
     }
-    HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
-    T.mark("layout");
-    HIP_TRY(launch_layout(B.d_fd, nf, B.d_seg, B.d_wcnt, B.d_rcnt, s));
-    T.mark("outlier_write");
-    HIP_TRY(launch_outlier_write(B.d_fd, nf, B.tot_ow, B.d_seg, s));
+    T.mark("encode_scan");
+    HIP_TRY(launch_scan(B.d_seg, B.tot_scan, B.d_tmp, s, B.scan));
     T.mark("encode_write");
-    HIP_TRY(launch_huff_write(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_wcnt, s));
-    // run values of RLE fields into the archive, run starts of both run-length
-    // codecs (they overwrite the outlier delta scratch, now written out)
-    HIP_TRY(launch_rle_write(B.d_fd, nf, B.tot_rt, B.d_rcnt, 1 | 4, s));
-    HIP_TRY(launch_rle_len(B.d_fd, nf, B.max_rle_units, s));
-    T.mark("header");
-    HIP_TRY(launch_header(B.d_fd, nf, s));
+    HIP_TRY(launch_huff_write(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_seg, B.d_wcnt, B.d_rcnt, s));
+    T.mark("finish");
+    HIP_TRY(launch_finish(B.d_fd, nf, rt, B.tot_ow, B.d_seg, B.d_wcnt, B.d_rcnt, res, s));
     return EBC_OK;
 }
 
@@ -756,7 +768,6 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
     for (int k = 0; k < B.nf; ++k) B.max_bins = std::max(B.max_bins, din[B.order[k]].H.n_bins);
     B.tab_stride = dectab_bytes(B.max_bins);
     B.d_tabs = bp.take<uint8_t>(B.tab_stride * B.nf);
-    B.d_result = bp.take<uint64_t>(16);
     for (int k = 0; k < B.nf; ++k) {
         const DecompressIn& D = din[B.order[k]];
         const Header& H = D.H;
@@ -1034,7 +1045,7 @@ int ebc_compress(const void* d_field, int rank, const uint64_t dims[3], const eb
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(stats, s);
-    st = enqueue_compress(B, P, s, T);
+    st = enqueue_compress(B, P, s, T, nullptr);
     if (st) return st;
     T.mark("end");
     if (stats) HIP_TRY(launch_estimate(B.d_fd, 1, B.d_est, 0, 0, s));  // after the timed stages
@@ -1070,10 +1081,7 @@ int ebc_compress_async(const void* d_field, int rank, const uint64_t dims[3], co
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(nullptr, s);
-    st = enqueue_compress(B, P, s, T);
-    if (st) return st;
-    HIP_TRY(launch_result(B.d_fd, d_result, s));
-    return EBC_OK;
+    return enqueue_compress(B, P, s, T, d_result);
 }
 
 int ebc_archive_info(const void* h_header, uint64_t header_bytes, int* rank, uint64_t dims[3],
@@ -1229,7 +1237,7 @@ int ebc_batch_compress(int n, const ebc_field* fields, const ebc_params* p, ebc_
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(nullptr, s);
-    st = enqueue_compress(B, P, s, T);
+    st = enqueue_compress(B, P, s, T, nullptr);
     if (st) return st;
     std::vector<FieldDyn> dyn;
     st = read_dyn(B, dyn, s);
@@ -1263,10 +1271,7 @@ int ebc_batch_compress_async(int n, const ebc_field* fields, const ebc_params* p
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(nullptr, s);
-    st = enqueue_compress(B, P, s, T);
-    if (st) return st;
-    HIP_TRY(launch_batch_results(B.d_fd, n, (uint64_t*)d_results, s));
-    return EBC_OK;
+    return enqueue_compress(B, P, s, T, (uint64_t*)d_results);
 }
 
 static int batch_dec_inputs(int n, const ebc_archive_ref* refs, std::vector<DecompressIn>& din)
@@ -1367,7 +1372,7 @@ int ebc_estimate(const void* d_field, int rank, const uint64_t dims[3], const eb
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(nullptr, s);
-    st = enqueue_compress(B, P, s, T, true);  // up to the code histogram
+    st = enqueue_compress(B, P, s, T, nullptr, true);  // up to the code histogram
     if (st) return st;
     HIP_TRY(launch_estimate(B.d_fd, 1, B.d_est, samples, seed, s));
     std::vector<FieldDyn> dyn;
@@ -1412,7 +1417,7 @@ int ebc_debug_construct(const void* d_field, int rank, const uint64_t dims[3], c
     int st = compress_common(fin, p, d_ws, ws_bytes, s, B, P);
     if (st) return st;
     Timer T(nullptr, s);
-    st = enqueue_compress(B, P, s, T, true);
+    st = enqueue_compress(B, P, s, T, nullptr, true);
     if (st) return st;
     std::vector<FieldDyn> dyn;
     st = read_dyn(B, dyn, s);

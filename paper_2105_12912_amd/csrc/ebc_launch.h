@@ -36,7 +36,8 @@ hipError_t launch_hist_reduce(const FieldDesc* F, int nf, uint32_t n_bins, hipSt
 
 // codebook
 size_t codebook_lds_bytes(uint32_t n_bins);
-hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, hipStream_t s);
+// direct: the partial histograms are added up here (no histogram reduce before)
+hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, bool direct, hipStream_t s);
 hipError_t launch_dectab(const FieldDesc* F, int nf, uint8_t* tabs, size_t stride, hipStream_t s);
 size_t codebook_wide_scratch_bytes(uint32_t n_bins);
 
@@ -46,10 +47,12 @@ hipError_t launch_estimate(const FieldDesc* F, int nf, EstDev* est, uint64_t sam
 
 // Huffman
 size_t huff_write_lds_bytes(uint32_t n_bins, uint32_t hc);
-hipError_t launch_huff_bits(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
-                            uint32_t* wcnt, int which, hipStream_t s);
-hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc,
-                             uint32_t n_bins, const uint32_t* woff, hipStream_t s);
+// count pass of the Huffman chunks (which: 0 Huffman fields, 1 RLE+VLE fields)
+// and, with rt_units, of the run-length tiles
+hipError_t launch_encode_count(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
+                               uint32_t* wcnt, int which, uint32_t rt_units, uint32_t* rcnt, hipStream_t s);
+hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
+                             const uint32_t* soff, const uint32_t* woff, const uint32_t* roff, hipStream_t s);
 hipError_t launch_words_check(const FieldDesc* F, int nf, const uint32_t* woff, hipStream_t s);
 hipError_t launch_huff_prep(const FieldDesc* F, int nf, uint32_t units, uint32_t* wcnt, uint32_t* soff,
                             hipStream_t s);
@@ -60,14 +63,9 @@ hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32
 
 // RLE
 hipError_t launch_rle_count(const FieldDesc* F, int nf, uint32_t units, uint32_t* rcnt, hipStream_t s);
-// what: 1 run values into the archive (RLE), 2 run values into the value
-// stream (RLE+VLE), 4 run starts
-hipError_t launch_rle_write(const FieldDesc* F, int nf, uint32_t units, const uint32_t* roff, int what,
-                            hipStream_t s);
-// RLE+VLE: run counts, the run-value stream and its histogram
+// RLE+VLE: the run-value stream, its length and its histogram
 hipError_t launch_rle_vle_prep(const FieldDesc* F, int nf, uint32_t units, const uint32_t* roff,
                                uint32_t n_bins, hipStream_t s);
-hipError_t launch_rle_len(const FieldDesc* F, int nf, uint32_t max_units, hipStream_t s);
 hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint32_t rt_units,
                              uint32_t* starts, uint32_t* tmap, uint32_t* tmp, uint32_t n_starts,
                              uint32_t scan_direct, hipStream_t s);
@@ -76,6 +74,10 @@ hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint
 uint32_t outlier_write_units(uint32_t n_seg);
 hipError_t launch_outlier_write(const FieldDesc* F, int nf, uint32_t units, const uint32_t* soff,
                                 hipStream_t s);
+// headers, result records (res: 16 bytes per field in the caller's order, or
+// NULL), runs of run-length fields (rt_units tiles, if any) and outlier lists
+hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t ow_units, const uint32_t* soff,
+                         const uint32_t* woff, const uint32_t* roff, uint64_t* res, hipStream_t s);
 hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
 
 // reconstruction
@@ -87,12 +89,7 @@ hipError_t launch_dinit(const FieldDesc* F, int nf, hipStream_t s);
 hipError_t launch_fill_const(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
 
 // archive
-hipError_t launch_layout(const FieldDesc* F, int nf, const uint32_t* soff, const uint32_t* woff,
-                         const uint32_t* roff, hipStream_t s);
-hipError_t launch_header(const FieldDesc* F, int nf, hipStream_t s);
-hipError_t launch_result(const FieldDesc* F, uint64_t* res, hipStream_t s);
 hipError_t launch_status(const FieldDesc* F, int32_t* st, hipStream_t s);
-hipError_t launch_batch_results(const FieldDesc* F, int nf, uint64_t* res, hipStream_t s);
 hipError_t launch_batch_status(const FieldDesc* F, int nf, int32_t* st, hipStream_t s);
 hipError_t upload_descs(const FieldDesc* host, int nf, FieldDesc* dev, hipStream_t s);
 

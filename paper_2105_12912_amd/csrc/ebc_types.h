@@ -33,6 +33,10 @@ constexpr uint32_t kPassHc = 4096;          // Huffman chunk symbols an encode p
 constexpr uint32_t kRangeUnit = 16384;      // elements per value-range work unit
 constexpr uint32_t kRleTile = 4096;         // elements per RLE work unit
 constexpr uint32_t kPersistentBlocks = 1024; // grid size of the persistent (grid-stride) kernels
+constexpr uint32_t kEncBlocks = 2048;       // encode passes: run-length tiles stream with a grid that the
+                                            // device holds whole (8 workgroups of 256 per CU; half as
+                                            // many took 75 instead of 63 us on 1.2e8 values)
+constexpr uint32_t kHistDirect = 32;        // partial histogram rows that the codebook adds up itself
 constexpr uint32_t kConstructBlocks = 2048;  // construction grid: 8 workgroups per CU
 constexpr int kLutBits = 12;                // Huffman decode table width (bits looked up at once)
 constexpr int kMaxDecodeLen = 60;          // longest code the decoder accepts (N < 2^32 gives <= 46)
@@ -119,7 +123,8 @@ struct FieldDesc {
     EBC_G uint8_t* len;      // n_bins code lengths
     EBC_G uint8_t* cbs;      // wide bins: codebook scratch (codebook_wide_scratch_bytes)
     EBC_G uint32_t* hbits;   // per Huffman chunk bit counts
-    EBC_G uint32_t* rstart;  // RLE run starts (compress scratch)
+    EBC_G uint16_t* rflag;   // RLE compress: a run-start bit per code (or NULL), in the place of hpart
+    EBC_G uint32_t* rfirst;  // RLE compress: first run start per tile, in the place of rpart
     EBC_G uint16_t* vsym;    // RLE+VLE: run values (compress: source of the Huffman pass;
                              // decompress: its output), n entries at most
     EBC_G uint32_t* vhist;   // RLE+VLE compress: histogram of the run values (n_bins)

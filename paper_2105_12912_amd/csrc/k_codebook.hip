@@ -253,7 +253,7 @@ __device__ __forceinline__ uint32_t leaf_levels(uint32_t m, uint32_t* bnd, PICKE
 template <class LEN>
 __device__ __forceinline__ void canonical_codes(const FieldDesc& fd, EBC_G FieldDyn* dy, int pass, uint32_t m,
                                                 const uint32_t* bnd, uint32_t nlev, uint32_t* wc,
-                                                uint64_t* first, uint64_t* s_bits,
+                                                uint64_t* first, uint64_t* s_bits, int32_t* s_codec,
                                                 const EBC_G uint32_t* __restrict__ hist, LEN len)
 {
     const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
@@ -328,19 +328,25 @@ __device__ __forceinline__ void canonical_codes(const FieldDesc& fd, EBC_G Field
         }
         dy->codec = codec;
         dy->n_out = fd.hist[0];
+        *s_codec = codec;
+    }
+    if (pass == 0 && fd.vhist) {
+        // cleared here for the histogram of the run values
+        __syncthreads();
+        if (*s_codec == ARC_RLE_VLE)
+            for (uint32_t s = threadIdx.x; s < nb; s += kCb) fd.vhist[s] = 0;
     }
 }
 
 // The used symbols in symbol order through put(position, count, symbol); returns
 // their number, and the largest count.
-template <class PUT>
-__device__ __forceinline__ uint32_t compact_used(const EBC_G uint32_t* __restrict__ hist, uint32_t nb,
-                                                 uint32_t* s_w, uint32_t* maxcnt, PUT put)
+template <class HIST, class PUT>
+__device__ __forceinline__ uint32_t compact_used(HIST hist, uint32_t nb, uint32_t* s_w, uint32_t* maxcnt, PUT put)
 {
     uint32_t m = 0, mx = 0;
     for (uint32_t b0 = 0; b0 < nb; b0 += kCb) {
         const uint32_t s = b0 + threadIdx.x;
-        const uint32_t h = s < nb ? hist[s] : 0u;
+        const uint32_t h = s < nb ? hist(s) : 0u;
         const uint64_t g = ballot(h != 0);
         uint32_t tot;
         const uint32_t pos = m + waves_before(__popcll(g), s_w, &tot) + lanes_below(g);
@@ -366,7 +372,7 @@ size_t codebook_lds_bytes(uint32_t n_bins) { return (size_t)15 * ((n_bins + 63) 
 // pass 0: the codebook of the quant-codes and the codec decision; pass 1
 // (RLE+VLE fields only): the codebook of the run values, from their own
 // histogram, which replaces the first in code / len.
-__global__ __launch_bounds__(kCb) void k_codebook(const FieldDesc* __restrict__ F, int pass)
+__global__ __launch_bounds__(kCb) void k_codebook(const FieldDesc* __restrict__ F, int pass, bool direct)
 {
     const FieldDesc& fd = F[blockIdx.x];
     EBC_G FieldDyn* dy = fd.dyn;
@@ -386,9 +392,19 @@ __global__ __launch_bounds__(kCb) void k_codebook(const FieldDesc* __restrict__ 
     __shared__ uint32_t s_lev;
     __shared__ uint64_t first[65];
     __shared__ uint64_t s_bits[kCbWaves];
+    __shared__ int32_t s_codec;
     __shared__ uint32_t wc[kCbWaves * 64];
     uint32_t maxcnt;
-    const uint32_t m = compact_used(hist, nb, s_w, &maxcnt, [&](uint32_t p, uint32_t h, uint32_t s) {
+    auto count = [&](uint32_t s) -> uint32_t {
+        if (!direct) return hist[s];
+        // few partial rows (kHistDirect): added up here instead of in a launch
+        uint32_t h = 0;
+#pragma unroll 8
+        for (uint32_t r = 0; r < fd.hrows; ++r) h += fd.hpart[(uint64_t)r * nb + s];
+        fd.hist[s] = h;
+        return h;
+    };
+    const uint32_t m = compact_used(count, nb, s_w, &maxcnt, [&](uint32_t p, uint32_t h, uint32_t s) {
         lw[p] = h;
         sym[p] = (uint16_t)s;
     });
@@ -414,7 +430,8 @@ __global__ __launch_bounds__(kCb) void k_codebook(const FieldDesc* __restrict__ 
         len_s[sym[i]] = (uint8_t)L;
     }
     __syncthreads();
-    canonical_codes(fd, dy, pass, m, bnd, nlev, wc, first, s_bits, hist, [&](uint32_t s) { return (uint32_t)len_s[s]; });
+    canonical_codes(fd, dy, pass, m, bnd, nlev, wc, first, s_bits, &s_codec, hist,
+                    [&](uint32_t s) { return (uint32_t)len_s[s]; });
 }
 
 // ------------------------------------------------- wide bins (> kMaxBins)
@@ -461,9 +478,11 @@ __global__ __launch_bounds__(kCb) void k_codebook_wide(const FieldDesc* __restri
     __shared__ uint32_t s_lev;
     __shared__ uint64_t first[65];
     __shared__ uint64_t s_bits[kCbWaves];
+    __shared__ int32_t s_codec;
     __shared__ uint32_t wc[kCbWaves * 64];
     uint32_t maxcnt;
-    const uint32_t m = compact_used(hist, nb, s_w, &maxcnt, [&](uint32_t p, uint32_t h, uint32_t s) {
+    auto count = [&](uint32_t s) { return hist[s]; };
+    const uint32_t m = compact_used(count, nb, s_w, &maxcnt, [&](uint32_t p, uint32_t h, uint32_t s) {
         keys[p] = ((uint64_t)h << 16) | s;
         if (p < kWideSort) lw[p] = h, sym[p] = (uint16_t)s;
     });
@@ -514,7 +533,8 @@ __global__ __launch_bounds__(kCb) void k_codebook_wide(const FieldDesc* __restri
         fd.len[in_lds ? (uint32_t)sym[i] : (uint32_t)keys[i] & 0xFFFFu] = (uint8_t)L;
     }
     __syncthreads();
-    canonical_codes(fd, dy, pass, m, bnd, nlev, wc, first, s_bits, hist, [&](uint32_t s) { return (uint32_t)fd.len[s]; });
+    canonical_codes(fd, dy, pass, m, bnd, nlev, wc, first, s_bits, &s_codec, hist,
+                    [&](uint32_t s) { return (uint32_t)fd.len[s]; });
 }
 
 // ------------------------------------------------------- decoder tables
@@ -688,10 +708,10 @@ __global__ __launch_bounds__(kCb) void k_dectab(const FieldDesc* __restrict__ F,
     }
 }
 
-hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, hipStream_t s)
+hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, bool direct, hipStream_t s)
 {
     if (n_bins > kMaxBins) hipLaunchKernelGGL(k_codebook_wide, dim3(nf), dim3(kCb), kWideLds, s, F, pass);
-    else hipLaunchKernelGGL(k_codebook, dim3(nf), dim3(kCb), codebook_lds_bytes(n_bins), s, F, pass);
+    else hipLaunchKernelGGL(k_codebook, dim3(nf), dim3(kCb), codebook_lds_bytes(n_bins), s, F, pass, direct);
     return hipGetLastError();
 }
 

@@ -14,7 +14,7 @@
 // Decode: one lane per sub-chunk; a kLutBits-wide table yields up to three short
 // codewords per lookup, longer codewords use a second table or the canonical
 // limit test.
-#include "ebc_dev.h"
+#include "encode_dev.h"
 #include "ebc_launch.h"
 
 namespace ebc {
@@ -102,6 +102,26 @@ __device__ __forceinline__ EncUnit enc_unit(const FieldDesc* __restrict__ F, int
     return u;
 }
 
+// The first unit from t on, in this workgroup's stride, that the launch codes;
+// the units of a field that it does not code (or past a short value stream)
+// are stepped over at once.  Past the end the unit is dead (ok false, the
+// stream of whatever unit it held or passed last).
+template <uint32_t S>
+__device__ __forceinline__ uint32_t enc_seek(const FieldDesc* __restrict__ F, int nf, uint32_t t, uint32_t units,
+                                             int which, EncUnit& u)
+{
+    u.ok = false;
+    while (t < units) {
+        u = enc_unit<S>(F, nf, t, which);
+        const FieldDesc& fd = F[u.f];
+        if (u.ok && (t - fd.hwg_base) * huff_cpw(64 * S) < u.nch) return t;
+        u.ok = false;
+        const uint32_t end = fd.hwg_base + fd.hwg_units;
+        t += ((end - t + gridDim.x - 1) / gridDim.x) * gridDim.x;
+    }
+    return t;
+}
+
 // For S >= 8 the loads are unconditional (a lane with nothing to load reads
 // the start of the stream instead), so every pipeline stage issues the same
 // number of loads and the compiler's wait counts never have to assume a stage
@@ -131,26 +151,21 @@ template <uint32_t S, class Proc>
 __device__ __forceinline__ void enc_pipeline(const FieldDesc* __restrict__ F, int nf, uint32_t units,
                                              int which, Proc& proc)
 {
-    uint32_t t = blockIdx.x;
-    if (t >= units) return;
     SymRaw<S> A, B;
-    EncUnit ua = enc_unit<S>(F, nf, t, which), ub;
+    EncUnit ua = {};
+    uint32_t t = enc_seek<S>(F, nf, blockIdx.x, units, which, ua);
+    if (t >= units) return;
+    EncUnit ub = ua;  // a dead unit still names a stream that can be read
     enc_issue<S>(F, ua, A);
     for (;;) {
         // the next stage's loads are always issued (a dead unit past the end)
-        uint32_t tn = t + gridDim.x;
-        ub = enc_unit<S>(F, nf, tn < units ? tn : t, which);
-        if (tn >= units) ub.ok = false;
+        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, ub);
         enc_issue<S>(F, ub, B);
         proc(ua, A);
-        t = tn;
         if (t >= units) break;
-        tn = t + gridDim.x;
-        ua = enc_unit<S>(F, nf, tn < units ? tn : t, which);
-        if (tn >= units) ua.ok = false;
+        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, ua);
         enc_issue<S>(F, ua, A);
         proc(ub, B);
-        t = tn;
         if (t >= units) break;
     }
 }
@@ -200,12 +215,18 @@ struct BitsProc {
     }
 };
 
+// Bits of the Huffman fields' chunks; with rt_units (workgroups of kBlock
+// threads), run starts of the run-length fields' tiles as well, which saves a
+// launch that most fields have no use for.
 template <uint32_t S, bool W>
 __global__ __launch_bounds__(kBlock) void k_huff_bits(const FieldDesc* __restrict__ F, int nf,
                                                       uint32_t* __restrict__ wcnt, uint32_t units,
-                                                      int which)
+                                                      int which, uint32_t rt_units,
+                                                      uint32_t* __restrict__ rcnt)
 {
     __shared__ uint8_t len_s[W ? 1 : kMaxBins];
+    __shared__ RleShared sh;
+    if (rt_units) rle_count_tiles(F, nf, rcnt, rt_units, sh);
     BitsProc<S, W> proc{F, wcnt, len_s, -1};
     enc_pipeline<S>(F, nf, units, which, proc);
 }
@@ -253,9 +274,12 @@ __device__ __forceinline__ void put_left(uint64_t& acc, uint32_t& nacc, uint32_t
 template <uint32_t S, bool W>
 struct WriteProc {
     const FieldDesc* F;
-    const uint32_t* woff;
+    const uint32_t *soff, *woff, *roff;
     uint64_t* lds64;
     int cur;
+    bool fits;                  // field cur's archive fits into its buffer
+    EBC_G uint32_t* words;      // its sections
+    EBC_G uint16_t* sbits;
     __device__ __forceinline__ uint64_t entry(const FieldDesc& fd, const uint64_t* code_s, uint32_t sym) const
     {
         return W ? write_entry(fd.code[sym]) : code_s[sym];
@@ -275,13 +299,20 @@ struct WriteProc {
         // out need no barrier; only a new field's code table (shared by the
         // workgroup, whose waves all work on one field) does.
         uint32_t* wbuf = (uint32_t*)(lds64 + (W ? 0 : nb)) + (threadIdx.x / kWave) * 2 * hc;
-        if (!W && u.f != cur) {
-            __syncthreads();
-            for (uint32_t s = threadIdx.x; s < nb; s += kWave * huff_cpw(64 * S))
-                code_s[s] = write_entry(fd.code[s]);
-            __syncthreads();
+        if (u.f != cur) {
+            const Layout y = layout_of(fd, dy->codec, soff, woff, roff);
+            fits = y.total <= fd.arc_cap;
+            words = (EBC_G uint32_t*)(fd.arc + y.off_words);
+            sbits = (EBC_G uint16_t*)(fd.arc + y.off_sbits);
+            if (!W) {
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < nb; s += kWave * huff_cpw(64 * S))
+                    code_s[s] = write_entry(fd.code[s]);
+                __syncthreads();
+            }
             cur = u.f;
         }
+        if (!fits) return;
         const bool live = u.c < u.nch;
         const uint32_t cbits = live ? kconst(fd.hbits)[u.c] : 0u;
         const uint32_t nw = (cbits + 31) / 32;
@@ -345,10 +376,9 @@ struct WriteProc {
             if (nacc) atomicOr(&wbuf[w], (uint32_t)(acc >> 32));
         }
         if (live) {
-            EBC_G uint8_t* arc = fd.arc;
             const auto* wk = (const __attribute__((address_space(4))) uint32_t*)woff;
             const uint32_t wo = wk[fd.hch_base + u.c] - wk[fd.hch_base];
-            EBC_G uint32_t* dst = (EBC_G uint32_t*)(arc + dy->off_words) + wo;
+            EBC_G uint32_t* dst = words + wo;
             for (uint32_t i = lane_id(); i < nw; i += kWave) dst[i] = wbuf[i];
             // sub-chunk bit counts (u16): one per kSubMax symbols of the
             // chunk, or one for the whole chunk when it is shorter
@@ -356,18 +386,19 @@ struct WriteProc {
             const uint32_t hs = fd.hs;
             const uint64_t sub = (uint64_t)u.c * (hc / hs) + lane_id() / kLps;
             if (lane_id() % kLps == 0 && lo < u.cnt && sub < u.nsub)
-                ((EBC_G uint16_t*)(arc + dy->off_sbits))[sub] = (uint16_t)sb;
+                sbits[sub] = (uint16_t)sb;
         }
     }
 };
 
 template <uint32_t S, bool W>
 __global__ __launch_bounds__(kBlock) void k_huff_write(const FieldDesc* __restrict__ F, int nf,
+                                                       const uint32_t* __restrict__ soff,
                                                        const uint32_t* __restrict__ woff,
-                                                       uint32_t units)
+                                                       const uint32_t* __restrict__ roff, uint32_t units)
 {
     extern __shared__ uint64_t lds64[];
-    WriteProc<S, W> proc{F, woff, lds64, -1};
+    WriteProc<S, W> proc{F, soff, woff, roff, lds64, -1, false, nullptr, nullptr};
     enc_pipeline<S>(F, nf, units, 2, proc);
 }
 
@@ -435,7 +466,9 @@ __global__ __launch_bounds__(kWave) void k_huff_bits_long(const FieldDesc* __res
 
 template <bool W>
 __global__ __launch_bounds__(kWave) void k_huff_write_long(const FieldDesc* __restrict__ F, int nf,
+                                                           const uint32_t* __restrict__ soff,
                                                            const uint32_t* __restrict__ woff,
+                                                           const uint32_t* __restrict__ roff,
                                                            uint32_t units)
 {
     extern __shared__ uint64_t lds64[];
@@ -454,9 +487,11 @@ __global__ __launch_bounds__(kWave) void k_huff_write_long(const FieldDesc* __re
         }
         auto entry = [&](uint32_t sym) { return W ? write_entry(fd.code[sym]) : code_s[sym]; };
         if (u.c >= u.nch) continue;
+        const Layout y = layout_of(fd, dy->codec, soff, woff, roff);
+        if (y.total > fd.arc_cap) continue;
         const uint32_t wo = woff[fd.hch_base + u.c] - woff[fd.hch_base];
-        EBC_G uint32_t* dst = (EBC_G uint32_t*)(fd.arc + dy->off_words) + wo;
-        EBC_G uint16_t* sbits = (EBC_G uint16_t*)(fd.arc + dy->off_sbits);
+        EBC_G uint32_t* dst = (EBC_G uint32_t*)(fd.arc + y.off_words) + wo;
+        EBC_G uint16_t* sbits = (EBC_G uint16_t*)(fd.arc + y.off_sbits);
         uint64_t done = 0;      // bits of the chunk already packed
         uint32_t carry = 0;     // the partial word at bit (done & ~31)
         uint32_t words_out = 0; // complete words stored
@@ -912,12 +947,21 @@ hipError_t launch_words_check(const FieldDesc* F, int nf, const uint32_t* woff, 
 // persistent grid: enough workgroups to fill the device several times over
 static uint32_t persistent_grid(uint32_t units) { return units < kPersistentBlocks ? units : kPersistentBlocks; }
 
-hipError_t launch_huff_bits(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
-                            uint32_t* wcnt, int which, hipStream_t s)
+// Workgroups of kBlock threads (chunks of at most 1024 symbols) take the
+// run-length tiles along; with longer chunks these get a launch of their own.
+static bool takes_runs(uint32_t hc) { return kWave * huff_cpw(hc) == (uint32_t)kBlock; }
+
+hipError_t launch_encode_count(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
+                               uint32_t* wcnt, int which, uint32_t rt_units, uint32_t* rcnt, hipStream_t s)
 {
+    if (rt_units && (!takes_runs(hc) || !units)) {
+        const hipError_t e = launch_rle_count(F, nf, rt_units, rcnt, s);
+        if (e != hipSuccess) return e;
+        rt_units = 0;
+    }
     if (!units) return hipSuccess;
     const bool wide = n_bins > kMaxBins;
-    const dim3 g(persistent_grid(units));
+    const dim3 g(max(persistent_grid(units), min(rt_units, kEncBlocks)));
     if (hc > kPassHc) {
         if (wide) hipLaunchKernelGGL(k_huff_bits_long<true>, g, dim3(kWave), 0, s, F, nf, wcnt, units, which);
         else hipLaunchKernelGGL(k_huff_bits_long<false>, g, dim3(kWave), 0, s, F, nf, wcnt, units, which);
@@ -925,30 +969,30 @@ hipError_t launch_huff_bits(const FieldDesc* F, int nf, uint32_t units, uint32_t
     }
     const dim3 b(kWave * huff_cpw(hc));
     if (wide) {
-        EBC_HC_DISPATCH(k_huff_bits, true, g, b, 0, s, F, nf, wcnt, units, which)
+        EBC_HC_DISPATCH(k_huff_bits, true, g, b, 0, s, F, nf, wcnt, units, which, rt_units, rcnt)
     } else {
-        EBC_HC_DISPATCH(k_huff_bits, false, g, b, 0, s, F, nf, wcnt, units, which)
+        EBC_HC_DISPATCH(k_huff_bits, false, g, b, 0, s, F, nf, wcnt, units, which, rt_units, rcnt)
     }
     return hipGetLastError();
 }
 
-hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc,
-                             uint32_t n_bins, const uint32_t* woff, hipStream_t s)
+hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
+                             const uint32_t* soff, const uint32_t* woff, const uint32_t* roff, hipStream_t s)
 {
     if (!units) return hipSuccess;
     const bool wide = n_bins > kMaxBins;
     const dim3 g(persistent_grid(units));
     const size_t sh = huff_write_lds_bytes(n_bins, hc);
     if (hc > kPassHc) {
-        if (wide) hipLaunchKernelGGL(k_huff_write_long<true>, g, dim3(kWave), sh, s, F, nf, woff, units);
-        else hipLaunchKernelGGL(k_huff_write_long<false>, g, dim3(kWave), sh, s, F, nf, woff, units);
+        if (wide) hipLaunchKernelGGL(k_huff_write_long<true>, g, dim3(kWave), sh, s, F, nf, soff, woff, roff, units);
+        else hipLaunchKernelGGL(k_huff_write_long<false>, g, dim3(kWave), sh, s, F, nf, soff, woff, roff, units);
         return hipGetLastError();
     }
     const dim3 b(kWave * huff_cpw(hc));
     if (wide) {
-        EBC_HC_DISPATCH(k_huff_write, true, g, b, sh, s, F, nf, woff, units)
+        EBC_HC_DISPATCH(k_huff_write, true, g, b, sh, s, F, nf, soff, woff, roff, units)
     } else {
-        EBC_HC_DISPATCH(k_huff_write, false, g, b, sh, s, F, nf, woff, units)
+        EBC_HC_DISPATCH(k_huff_write, false, g, b, sh, s, F, nf, soff, woff, roff, units)
     }
     return hipGetLastError();
 }

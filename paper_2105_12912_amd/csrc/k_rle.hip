@@ -3,157 +3,32 @@
 // Sec. III-B: a run of equal symbols is stored as a (value, count) tuple; the
 // run lengths are metadata.  Runs are maximal and taken over the whole code
 // array in row-major order.  Encoding marks run starts (a code differing from
-// its predecessor), counts them per tile, scans the counts, and compacts
-// (value, start) pairs in order; lengths are differences of successive
-// starts.  Decoding scans the stored lengths into starts and expands each
-// output tile from the runs that overlap it.
-#include "ebc_dev.h"
+// its predecessor), counts them per tile, scans the counts, and writes
+// (value, length) pairs in order (encode_dev.h).  Decoding scans the stored
+// lengths into starts and expands each output tile from the runs that overlap
+// it.
+#include "encode_dev.h"
 #include "ebc_launch.h"
 
 namespace ebc {
 
-constexpr int kRleItems = kRleTile / kBlock;  // 16 codes per thread
-
-// load 16 codes owned by this thread and the flags "starts a run"
-__device__ __forceinline__ uint32_t run_flags(const FieldDesc& fd, uint64_t lo, uint16_t c[kRleItems])
-{
-    __shared__ uint16_t s_last[kBlock];
-    const uint64_t i0 = lo + (uint64_t)threadIdx.x * kRleItems;
-    const uint64_t n = fd.n;
-    const EBC_G uint16_t* __restrict__ q = fd.q;
-    if (i0 + kRleItems <= n) {
-        const uint4 a = *(const EBC_G uint4*)(q + i0);
-        const uint4 b = *(const EBC_G uint4*)(q + i0 + 8);
-        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) c[2 * k] = w[k] & 0xFFFF, c[2 * k + 1] = w[k] >> 16;
-    } else {
-#pragma unroll
-        for (int k = 0; k < kRleItems; ++k) c[k] = i0 + k < n ? q[i0 + k] : 0;
-    }
-    s_last[threadIdx.x] = c[kRleItems - 1];
-    __syncthreads();
-    uint32_t prev;
-    bool have_prev;
-    if (threadIdx.x > 0) {
-        prev = s_last[threadIdx.x - 1];
-        have_prev = true;
-    } else {
-        have_prev = lo > 0;
-        prev = have_prev ? q[lo - 1] : 0u;
-    }
-    uint32_t flags = 0;
-#pragma unroll
-    for (int k = 0; k < kRleItems; ++k) {
-        if (i0 + k < n && (!have_prev || c[k] != prev)) flags |= 1u << k;
-        prev = c[k];
-        have_prev = true;
-    }
-    __syncthreads();
-    return flags;
-}
-
-__device__ __forceinline__ uint32_t block_excl_scan_rle(uint32_t v, uint32_t* total)
-{
-    __shared__ uint32_t s_w[kWavesPerBlock];
-    const int w = threadIdx.x / kWave;
-    const uint32_t inc = wave_incl_scan_u32(v);
-    if (lane_id() == kWave - 1) s_w[w] = inc;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) {
-        off += k < w ? s_w[k] : 0u;
-        tot += s_w[k];
-    }
-    __syncthreads();
-    *total = tot;
-    return off + inc - v;
-}
-
-// Both encode passes are persistent (grid stride over the tiles).
-// Grid-stride step past field fd's RLE tiles (those of a field that is not
-// run-length coded): the first tile index of this workgroup's stride at or
-// beyond the field's end, so such a field costs one iteration per workgroup.
-__device__ __forceinline__ uint32_t skip_field(const FieldDesc& fd, uint32_t t)
-{
-    const uint32_t end = fd.rt_base + fd.n_rt;
-    return t + ((end - t + gridDim.x - 1) / gridDim.x) * gridDim.x;
-}
-
 __global__ __launch_bounds__(kBlock) void k_rle_count(const FieldDesc* __restrict__ F, int nf,
                                                       uint32_t* __restrict__ rcnt, uint32_t units)
 {
-    for (uint32_t t = blockIdx.x; t < units;) {
-        const int f = find_field<&FieldDesc::rt_base>(F, nf, t);
-        const FieldDesc& fd = F[f];
-        const auto* dy = kconst(fd.dyn);
-        if (dy->status != ST_OK || !rle_codec(dy->codec)) {
-            t = skip_field(fd, t);
-            continue;
-        }
-        uint16_t c[kRleItems];
-        const uint32_t flags = run_flags(fd, (uint64_t)(t - fd.rt_base) * kRleTile, c);
-        uint32_t tot;
-        block_excl_scan_rle(__popc(flags), &tot);
-        if (threadIdx.x == 0) rcnt[t] = tot;
-        t += gridDim.x;
-    }
+    __shared__ RleShared sh;
+    rle_count_tiles(F, nf, rcnt, units, sh);
 }
 
-// what: kRleValArc writes the run values into the archive (RLE codec),
-// kRleValSym into the run-value stream of the Huffman pass (RLE+VLE codec),
-// kRleStart the run starts (both codecs; they overwrite the outlier delta
-// scratch, so only after the outlier list is written).
-constexpr int kRleValArc = 1, kRleValSym = 2, kRleStart = 4;
-
+// RLE+VLE: the run values before their codebook exists
 __global__ __launch_bounds__(kBlock) void k_rle_write(const FieldDesc* __restrict__ F, int nf,
+                                                      const uint32_t* __restrict__ soff,
+                                                      const uint32_t* __restrict__ woff,
                                                       const uint32_t* __restrict__ roff, uint32_t units,
                                                       int what)
 {
-    for (uint32_t t = blockIdx.x; t < units; t += gridDim.x) {
-        const int f = find_field<&FieldDesc::rt_base>(F, nf, t);
-        const FieldDesc& fd = F[f];
-        const auto* dy = kconst(fd.dyn);
-        const int32_t codec = dy->codec;
-        const bool val_arc = (what & kRleValArc) && codec == ARC_RLE;
-        const bool val_sym = (what & kRleValSym) && codec == ARC_RLE_VLE;
-        const bool starts = (what & kRleStart) && rle_codec(codec);
-        if (dy->status != ST_OK || !(val_arc || val_sym || starts)) {
-            t = skip_field(fd, t) - gridDim.x;  // the loop step adds it back
-            continue;
-        }
-        const uint64_t lo = (uint64_t)(t - fd.rt_base) * kRleTile;
-        // the tile's output offset is loaded before its codes, so its latency
-        // overlaps theirs
-        const uint32_t base = roff[t] - roff[fd.rt_base];
-        uint16_t c[kRleItems];
-        const uint32_t flags = run_flags(fd, lo, c);
-        uint32_t tot;
-        uint32_t pos = block_excl_scan_rle(__popc(flags), &tot) + base;
-        EBC_G uint16_t* val = val_arc ? (EBC_G uint16_t*)(fd.arc + kHdr) : fd.vsym;
-        const uint64_t i0 = lo + (uint64_t)threadIdx.x * kRleItems;
-#pragma unroll
-        for (int k = 0; k < kRleItems; ++k) {
-            if (flags & (1u << k)) {
-                if (val_arc || val_sym) val[pos] = c[k];
-                if (starts) fd.rstart[pos] = (uint32_t)(i0 + k);
-                ++pos;
-            }
-        }
-    }
-}
-
-// RLE+VLE compress: the run count of each field (from the scanned tile
-// counts) and its run-value histogram cleared; one workgroup per field.
-__global__ __launch_bounds__(kBlock) void k_rle_total(const FieldDesc* __restrict__ F,
-                                                      const uint32_t* __restrict__ roff)
-{
-    const FieldDesc& fd = F[blockIdx.x];
-    EBC_G FieldDyn* dy = fd.dyn;
-    if (dy->status != ST_OK || dy->codec != ARC_RLE_VLE) return;
-    for (uint32_t b = threadIdx.x; b < fd.n_bins; b += kBlock) fd.vhist[b] = 0;
-    if (threadIdx.x == 0) dy->n_runs = roff[fd.rt_base + fd.n_rt] - roff[fd.rt_base];
+    rle_write_tiles(F, nf, soff, woff, roff, units, what,
+                    blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
+                    gridDim.x * kWavesPerBlock);
 }
 
 // RLE+VLE compress: histogram of the run values, kRleTile values per
@@ -195,21 +70,6 @@ __global__ __launch_bounds__(kBlock) void k_rle_vhist(const FieldDesc* __restric
         for (uint32_t b = threadIdx.x; b < ns; b += kBlock)
             if (sh[b]) atomicAdd(&fd.vhist[wide && b ? wlo + b - 1 : b], sh[b]);
         __syncthreads();
-    }
-}
-
-// lengths = differences of successive starts; grid-stride over the runs
-__global__ __launch_bounds__(kBlock) void k_rle_len(const FieldDesc* __restrict__ F)
-{
-    const FieldDesc& fd = F[blockIdx.y];
-    const auto* dy = kconst(fd.dyn);
-    if (dy->status != ST_OK || !rle_codec(dy->codec)) return;
-    const uint64_t R = dy->n_runs;
-    EBC_G uint32_t* len = (EBC_G uint32_t*)(fd.arc + dy->off_rlen);
-    for (uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x; k < R;
-         k += (uint64_t)gridDim.x * kBlock) {
-        const uint64_t end = k + 1 < R ? fd.rstart[k + 1] : fd.n;
-        len[k] = (uint32_t)(end - fd.rstart[k]);
     }
 }
 
@@ -356,46 +216,23 @@ __global__ __launch_bounds__(kBlock) void k_rle_expand(const FieldDesc* __restri
     }
 }
 
-// The two encode passes stream the codes with a grid the device holds whole
-// (8 workgroups of 256 per CU): with half that many workgroups in flight the
-// count and write stages on a 1.2e8-value field took 75 and 101 us instead
-// of 63 and 81.
-constexpr uint32_t kRleBlocks = 2048;
-
 hipError_t launch_rle_count(const FieldDesc* F, int nf, uint32_t units, uint32_t* rcnt, hipStream_t s)
 {
     if (!units) return hipSuccess;
-    const uint32_t g = units < kRleBlocks ? units : kRleBlocks;
-    hipLaunchKernelGGL(k_rle_count, dim3(g), dim3(kBlock), 0, s, F, nf, rcnt, units);
-    return hipGetLastError();
-}
-
-hipError_t launch_rle_write(const FieldDesc* F, int nf, uint32_t units, const uint32_t* roff, int what,
-                            hipStream_t s)
-{
-    if (!units) return hipSuccess;
-    const uint32_t g = units < kRleBlocks ? units : kRleBlocks;
-    hipLaunchKernelGGL(k_rle_write, dim3(g), dim3(kBlock), 0, s, F, nf, roff, units, what);
+    hipLaunchKernelGGL(k_rle_count, dim3(min(units, kEncBlocks)), dim3(kBlock), 0, s, F, nf, rcnt, units);
     return hipGetLastError();
 }
 
 hipError_t launch_rle_vle_prep(const FieldDesc* F, int nf, uint32_t units, const uint32_t* roff,
                                uint32_t n_bins, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_rle_total, dim3(nf), dim3(kBlock), 0, s, F, roff);
+    if (!units) return hipSuccess;
+    hipLaunchKernelGGL(k_rle_write, dim3(min(units, kEncBlocks)), dim3(kBlock), 0, s, F, nf, roff, roff, roff,
+                       units, kRleValSym);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !units) return e;
-    e = launch_rle_write(F, nf, units, roff, kRleValSym, s);
     if (e != hipSuccess) return e;
     const uint32_t g = units < kPersistentBlocks ? units : kPersistentBlocks;
     hipLaunchKernelGGL(k_rle_vhist, dim3(g), dim3(kBlock), (size_t)hist_slots(n_bins) * 4, s, F, nf, units);
-    return hipGetLastError();
-}
-
-hipError_t launch_rle_len(const FieldDesc* F, int nf, uint32_t max_units, hipStream_t s)
-{
-    const uint32_t g = max(1u, min(max_units, 2048u));
-    hipLaunchKernelGGL(k_rle_len, dim3(g, nf), dim3(kBlock), 0, s, F);
     return hipGetLastError();
 }
 

@@ -165,7 +165,8 @@ hipError_t launch_scan(uint32_t* a, uint32_t n, uint32_t* tmp, hipStream_t s, ui
         return hipGetLastError();
     }
     const uint32_t nb = (n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, s, a, n, tmp);
+    // a single tile needs no sums
+    if (nb > 1) hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, s, a, n, tmp);
     if (nb <= direct_max) {
         hipLaunchKernelGGL(k_scan_down<false>, dim3(nb), dim3(kBlock), 0, s, a, n, tmp, nb);
     } else {
