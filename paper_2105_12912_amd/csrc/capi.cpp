@@ -165,7 +165,7 @@ struct Geo {
     uint32_t wx, xs, nxb, nyb, nzb, n_wave_tiles, wg_tiles;
     uint32_t grid;  // persistent construction grid (workgroups)
     uint32_t scan;  // scan schedule: direct down-sweep up to this many tiles (0: default)
-    uint32_t n_seg, range_units, ow_units, n_hch, hwg_units, n_rt;
+    uint32_t n_seg, range_units, ow_units, ow_segs, n_hch, hwg_units, n_rt;
     uint32_t hs, n_sub, hpwg_units;
 };
 
@@ -197,7 +197,8 @@ Geo make_geo(int rank, const uint64_t dims[3], uint32_t hc)
         g.n_seg = (uint32_t)(g.nz * g.ny * g.nxb);
     }
     g.range_units = cdiv(g.n, kRangeUnit);
-    g.ow_units = outlier_write_units(g.n_seg);
+    g.ow_segs = outlier_write_segs(g.n_seg);
+    g.ow_units = cdiv(g.n_seg, g.ow_segs);
     g.n_hch = cdiv(g.n, hc);
     g.hwg_units = cdiv(g.n_hch, huff_cpw(hc));
     g.hs = std::min(hc, kSubMax);
@@ -322,7 +323,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         G.count++;
         d.range_base = range.add(g.range_units), d.range_units = g.range_units;
         d.seg_base = seg.add(g.n_seg), d.n_seg = g.n_seg;
-        d.ow_base = ow.add(g.ow_units), d.ow_units = g.ow_units;
+        d.ow_base = ow.add(g.ow_units), d.ow_units = g.ow_units, d.ow_segs = g.ow_segs;
         d.hch_base = hch.add(g.n_hch), d.n_hch = g.n_hch;
         d.hwg_base = hwg.add(g.hwg_units), d.hwg_units = g.hwg_units;
         d.hs = g.hs;
@@ -500,7 +501,7 @@ struct Timer {
 int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, uint64_t* res, bool debug_stop = false)
 {
     const int nf = B.nf;
-    HIP_TRY(upload_descs(B.fd.data(), nf, B.d_fd, s));
+    HIP_TRY(upload_descs(B.fd.data(), nf, B.d_fd, false, s));
     T.mark("range");
     HIP_TRY(launch_range(B.d_fd, nf, B.tot_range, P.dtype == EBC_F64, s));
     T.mark("params");
@@ -718,10 +719,11 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         const uint64_t hm = stream(B.order[k]);
         d.hn = huff ? hm : 0;
         d.hs = g.hs;
-        d.n_hch = huff ? cdiv(hm, H.hc) : 0, d.hch_base = hch.add(d.n_hch);
+        // word offsets: an entry of its own behind each field's chunks
+        d.n_hch = huff ? cdiv(hm, H.hc) : 0, d.hch_base = hch.add(d.n_hch + 1);
         d.n_sub = huff ? cdiv(hm, g.hs) : 0, d.sub_base = sub.add(d.n_sub);
         d.hdwg_units = cdiv(cdiv(d.n_sub, kWave), B.dec_groups), d.hdwg_base = hdwg.add(d.hdwg_units);
-        d.hpwg_units = cdiv(d.n_hch, kBlock), d.hpwg_base = hpwg.add(d.hpwg_units);
+        d.hpwg_units = cdiv(d.n_hch, 1024), d.hpwg_base = hpwg.add(d.hpwg_units);
         d.n_rt = rle ? g.n_rt : 0, d.rt_base = rt.add(d.n_rt);
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
         d.rl_units = cdiv(d.n_runs_hdr, kBlock), d.rl_base = rl.add(d.rl_units);
@@ -840,18 +842,17 @@ int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
     return EBC_OK;
 }
 
-int enqueue_decompress(Batch& B, hipStream_t s, Timer& T)
+// status: where the fields' statuses go (device, the caller's order), or NULL
+int enqueue_decompress(Batch& B, hipStream_t s, Timer& T, int32_t* status)
 {
     const int nf = B.nf;
-    HIP_TRY(upload_descs(B.fd.data(), nf, B.d_fd, s));
-    HIP_TRY(launch_dinit(B.d_fd, nf, s));
+    HIP_TRY(upload_descs(B.fd.data(), nf, B.d_fd, true, s));
     T.mark("decode_prep");
-    if (B.tot_hch) {
-        HIP_TRY(launch_huff_prep(B.d_fd, nf, B.tot_hpwg, B.d_wcnt, B.d_soff, s));
-        HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
-        HIP_TRY(launch_words_check(B.d_fd, nf, B.d_wcnt, s));
-        T.mark("dectab");
-        HIP_TRY(launch_dectab(B.d_fd, nf, B.d_tabs, B.tab_stride, s));
+    if (B.tot_hdwg) {
+        bool direct = true;
+        for (const auto& d : B.fd) direct = direct && d.n_hch <= kPrepDirect;
+        HIP_TRY(launch_dec_prep(B.d_fd, nf, B.tot_hpwg, direct, B.d_tabs, B.tab_stride, B.d_wcnt, B.d_soff, s));
+        if (!direct) HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
         T.mark("huffman_decode");
         HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.dec_lanes, B.d_wcnt, B.d_soff, B.d_tabs, B.tab_stride, s));
     }
@@ -862,8 +863,8 @@ int enqueue_decompress(Batch& B, hipStream_t s, Timer& T)
     const int st = enqueue_reconstruct(B, s, T);
     if (st) return st;
     T.mark("check");
-    HIP_TRY(launch_recon_check(B.d_fd, nf, s));
     HIP_TRY(launch_fill_const(B.d_fd, nf, B.tot_range, s));
+    HIP_TRY(launch_recon_check(B.d_fd, nf, status, s));
     return EBC_OK;
 }
 
@@ -1124,7 +1125,7 @@ int ebc_decompress_workspace_size(const void* h_header, uint64_t header_bytes, u
 
 static int decompress_impl(const Header& H, const void* d_archive, uint64_t size, void* d_out,
                            uint64_t out_elems, void* d_ws, uint64_t ws_bytes, hipStream_t s,
-                           Batch& B, Timer& T)
+                           Batch& B, Timer& T, int32_t* status)
 {
     if (!d_archive || !d_out || !d_ws) return fail(EBC_ERR_ARG, "NULL argument");
     int st = header_supported(H);
@@ -1141,7 +1142,7 @@ static int decompress_impl(const Header& H, const void* d_archive, uint64_t size
         return fail(EBC_ERR_WS_TOO_SMALL, "workspace %llu < required %llu",
                     (unsigned long long)ws_bytes, (unsigned long long)sizing.ws_bytes);
     if (int e_ = plan_decompress(B, din, (uint8_t*)d_ws)) return e_;
-    return enqueue_decompress(B, s, T);
+    return enqueue_decompress(B, s, T, status);
 }
 
 int ebc_decompress(const void* d_archive, uint64_t size, void* d_out, uint64_t out_elems,
@@ -1159,7 +1160,7 @@ int ebc_decompress(const void* d_archive, uint64_t size, void* d_out, uint64_t o
     if (st) return st;
     Batch B;
     Timer T(stats, s);
-    st = decompress_impl(H, d_archive, size, d_out, out_elems, d_ws, ws_bytes, s, B, T);
+    st = decompress_impl(H, d_archive, size, d_out, out_elems, d_ws, ws_bytes, s, B, T, nullptr);
     if (st) return st;
     T.mark("end");
     std::vector<FieldDyn> dyn;
@@ -1191,10 +1192,7 @@ int ebc_decompress_async(const void* h_header, const void* d_archive, uint64_t s
     if (st) return st;
     Batch B;
     Timer T(nullptr, s);
-    st = decompress_impl(H, d_archive, size, d_out, out_elems, d_ws, ws_bytes, s, B, T);
-    if (st) return st;
-    HIP_TRY(launch_status(B.d_fd, d_status, s));
-    return EBC_OK;
+    return decompress_impl(H, d_archive, size, d_out, out_elems, d_ws, ws_bytes, s, B, T, d_status);
 }
 
 // ------------------------------------------------------------------ batch
@@ -1305,7 +1303,7 @@ int ebc_batch_decompress_workspace_size(int n, const ebc_archive_ref* refs, uint
 }
 
 static int batch_dec_prepare(int n, const ebc_archive_ref* refs, void* d_ws, uint64_t ws_bytes,
-                             hipStream_t s, Batch& B)
+                             hipStream_t s, Batch& B, int32_t* status)
 {
     if (!d_ws) return fail(EBC_ERR_ARG, "workspace is NULL");
     std::vector<DecompressIn> din;
@@ -1321,7 +1319,7 @@ static int batch_dec_prepare(int n, const ebc_archive_ref* refs, void* d_ws, uin
     if (ws_bytes < sizing.ws_bytes) return fail(EBC_ERR_WS_TOO_SMALL, "workspace too small");
     if (int e_ = plan_decompress(B, din, (uint8_t*)d_ws)) return e_;
     Timer T(nullptr, s);
-    return enqueue_decompress(B, s, T);
+    return enqueue_decompress(B, s, T, status);
 }
 
 int ebc_batch_decompress(int n, const ebc_archive_ref* refs, int32_t* statuses, void* d_ws,
@@ -1331,7 +1329,7 @@ int ebc_batch_decompress(int n, const ebc_archive_ref* refs, int32_t* statuses, 
     if (!statuses) return fail(EBC_ERR_ARG, "NULL argument");
     hipStream_t s = (hipStream_t)stream;
     Batch B;
-    int st = batch_dec_prepare(n, refs, d_ws, ws_bytes, s, B);
+    int st = batch_dec_prepare(n, refs, d_ws, ws_bytes, s, B, nullptr);
     if (st) return st;
     std::vector<FieldDyn> dyn;
     st = read_dyn(B, dyn, s);
@@ -1351,10 +1349,7 @@ int ebc_batch_decompress_async(int n, const ebc_archive_ref* refs, int32_t* d_st
     if (!d_statuses) return fail(EBC_ERR_ARG, "NULL argument");
     hipStream_t s = (hipStream_t)stream;
     Batch B;
-    int st = batch_dec_prepare(n, refs, d_ws, ws_bytes, s, B);
-    if (st) return st;
-    HIP_TRY(launch_batch_status(B.d_fd, n, d_statuses, s));
-    return EBC_OK;
+    return batch_dec_prepare(n, refs, d_ws, ws_bytes, s, B, d_statuses);
 }
 
 // ------------------------------------------------------------------ estimates
@@ -1478,12 +1473,11 @@ int ebc_debug_reconstruct(const uint16_t* d_q, const uint32_t* d_oidx, const int
     FieldDesc& d = B.fd[0];
     HIP_TRY(hipMemcpyAsync(d.q, d_q, 2 * H.n, hipMemcpyDeviceToDevice, s));
     d.n_hch = 0, d.hdwg_units = 0;  // no entropy decoding
-    HIP_TRY(upload_descs(B.fd.data(), 1, B.d_fd, s));
-    HIP_TRY(launch_dinit(B.d_fd, 1, s));
+    HIP_TRY(upload_descs(B.fd.data(), 1, B.d_fd, true, s));
     Timer T(nullptr, s);
     st = enqueue_reconstruct(B, s, T);
     if (st) return st;
-    HIP_TRY(launch_recon_check(B.d_fd, 1, s));
+    HIP_TRY(launch_recon_check(B.d_fd, 1, nullptr, s));
     std::vector<FieldDyn> dyn;
     st = read_dyn(B, dyn, s);
     if (st) return st;

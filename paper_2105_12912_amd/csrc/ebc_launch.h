@@ -38,7 +38,9 @@ hipError_t launch_hist_reduce(const FieldDesc* F, int nf, uint32_t n_bins, hipSt
 size_t codebook_lds_bytes(uint32_t n_bins);
 // direct: the partial histograms are added up here (no histogram reduce before)
 hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, bool direct, hipStream_t s);
-hipError_t launch_dectab(const FieldDesc* F, int nf, uint8_t* tabs, size_t stride, hipStream_t s);
+// decompression prologue; direct: no field has more than kPrepDirect chunks
+hipError_t launch_dec_prep(const FieldDesc* F, int nf, uint32_t units, bool direct, uint8_t* tabs, size_t stride,
+                           uint32_t* wcnt, uint32_t* soff, hipStream_t s);
 size_t codebook_wide_scratch_bytes(uint32_t n_bins);
 
 // compressibility estimates (histogram bounds; madogram over `samples` pairs)
@@ -53,9 +55,6 @@ hipError_t launch_encode_count(const FieldDesc* F, int nf, uint32_t units, uint3
                                uint32_t* wcnt, int which, uint32_t rt_units, uint32_t* rcnt, hipStream_t s);
 hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
                              const uint32_t* soff, const uint32_t* woff, const uint32_t* roff, hipStream_t s);
-hipError_t launch_words_check(const FieldDesc* F, int nf, const uint32_t* woff, hipStream_t s);
-hipError_t launch_huff_prep(const FieldDesc* F, int nf, uint32_t units, uint32_t* wcnt, uint32_t* soff,
-                            hipStream_t s);
 void huff_decode_split(uint64_t n_grp, uint32_t* lanes, uint32_t* groups);
 hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t lanes,
                               const uint32_t* woff, const uint32_t* soff, const uint8_t* tabs,
@@ -71,7 +70,7 @@ hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint
                              uint32_t scan_direct, hipStream_t s);
 
 // outliers
-uint32_t outlier_write_units(uint32_t n_seg);
+uint32_t outlier_write_segs(uint32_t n_seg);
 hipError_t launch_outlier_write(const FieldDesc* F, int nf, uint32_t units, const uint32_t* soff,
                                 hipStream_t s);
 // headers, result records (res: 16 bytes per field in the caller's order, or
@@ -84,13 +83,12 @@ hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, hi
 hipError_t launch_reconstruct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,
                               uint32_t blocks, hipStream_t s);
 hipError_t launch_recon_fix(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
-hipError_t launch_recon_check(const FieldDesc* F, int nf, hipStream_t s);
-hipError_t launch_dinit(const FieldDesc* F, int nf, hipStream_t s);
+// st: statuses in the caller's order (device), or NULL
+hipError_t launch_recon_check(const FieldDesc* F, int nf, int32_t* st, hipStream_t s);
 hipError_t launch_fill_const(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
 
 // archive
-hipError_t launch_status(const FieldDesc* F, int32_t* st, hipStream_t s);
-hipError_t launch_batch_status(const FieldDesc* F, int nf, int32_t* st, hipStream_t s);
-hipError_t upload_descs(const FieldDesc* host, int nf, FieldDesc* dev, hipStream_t s);
+// init: a decompression's device scalars as well
+hipError_t upload_descs(const FieldDesc* host, int nf, FieldDesc* dev, bool init, hipStream_t s);
 
 }  // namespace ebc

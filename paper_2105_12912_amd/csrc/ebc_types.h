@@ -36,6 +36,9 @@ constexpr uint32_t kPersistentBlocks = 1024; // grid size of the persistent (gri
 constexpr uint32_t kEncBlocks = 2048;       // encode passes: run-length tiles stream with a grid that the
                                             // device holds whole (8 workgroups of 256 per CU; half as
                                             // many took 75 instead of 63 us on 1.2e8 values)
+constexpr uint32_t kPrepDirect = 4096;      // decompress: chunks of a field that one workgroup's scan takes
+                                            // (four per thread; with 16384 and a batch's longest field of
+                                            // 12k chunks it took 46 us, the counts and two scans 20)
 constexpr uint32_t kHistDirect = 32;        // partial histogram rows that the codebook adds up itself
 constexpr uint32_t kConstructBlocks = 2048;  // construction grid: 8 workgroups per CU
 constexpr int kLutBits = 12;                // Huffman decode table width (bits looked up at once)
@@ -138,13 +141,13 @@ struct FieldDesc {
     uint32_t range_units, range_base;  // value range / fill: kRangeUnit elements per WG
     uint32_t wg_tiles, wg_base;        // construct / reconstruct WG tiles (rank group relative)
     uint32_t n_seg, seg_base;          // outlier segments: count-array entries
-    uint32_t ow_units, ow_base;        // outlier write: 64 segments per WG
+    uint32_t ow_units, ow_base, ow_segs; // outlier write: ow_segs segments per WG
     uint32_t n_hch, hch_base;          // Huffman chunks: word-count array entries
     uint32_t hs;                       // Huffman sub-chunk symbols: min(hc, 256)
     uint32_t n_sub, sub_base;          // Huffman sub-chunks: in-chunk start offsets
     uint32_t hwg_units, hwg_base;      // Huffman encode: huff_cpw(hc) chunks per WG
     uint32_t hdwg_units, hdwg_base;    // Huffman decode: Batch::dec_groups * 64 sub-chunks per WG
-    uint32_t hpwg_units, hpwg_base;    // Huffman decode prologue: kBlock chunks per WG
+    uint32_t hpwg_units, hpwg_base;    // Huffman decode prologue: 1024 chunks per WG
     uint32_t n_rt, rt_base;            // RLE tiles of kRleTile elements (count array / WG)
     uint32_t n_runs_hdr, rle_base;     // decompress: runs in the archive (start array entries)
     uint32_t sc_units, sc_base;        // decompress outlier scatter: 256 outliers per WG

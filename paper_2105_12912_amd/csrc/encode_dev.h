@@ -23,37 +23,21 @@ __device__ __forceinline__ uint32_t kcount(const uint32_t* p, uint64_t i)
 __device__ __forceinline__ Layout layout_of(const FieldDesc& fd, int32_t codec, const uint32_t* soff,
                                             const uint32_t* woff, const uint32_t* roff)
 {
-    Layout y = {};
-    if (codec == ARC_CONST) {
-        y.total = kHdr;
-        return y;
-    }
-    y.n_out = kcount(soff, (uint64_t)fd.seg_base + fd.n_seg) - kcount(soff, fd.seg_base);
-    uint64_t off_o;
-    if (codec == ARC_HUFFMAN) {
-        y.n_words = kcount(woff, (uint64_t)fd.hch_base + fd.n_hch) - kcount(woff, fd.hch_base);
-        y.off_sbits = align16(kHdr + fd.n_bins);
-        y.off_words = align16(y.off_sbits + 2ull * fd.n_sub);
-        off_o = align16(y.off_words + 4ull * y.n_words);
-    } else {
-        const uint64_t R = kcount(roff, (uint64_t)fd.rt_base + fd.n_rt) - kcount(roff, fd.rt_base);
-        y.n_runs = R;
-        if (codec == ARC_RLE_VLE) {
-            // the Huffman stream of the R run values, then the run lengths
-            const uint64_t nch = (R + fd.hc - 1) / fd.hc, nsub = (R + fd.hs - 1) / fd.hs;
-            y.n_words = kcount(woff, fd.hch_base + nch) - kcount(woff, fd.hch_base);
-            y.off_sbits = align16(kHdr + fd.n_bins);
-            y.off_words = align16(y.off_sbits + 2ull * nsub);
-            y.off_rlen = align16(y.off_words + 4ull * y.n_words);
-        } else {
-            y.off_rlen = align16(kHdr + 2ull * R);
-        }
-        off_o = align16(y.off_rlen + 4ull * R);
-    }
-    y.off_oidx = off_o;
-    y.off_oval = align16(off_o + 4ull * y.n_out);
-    y.total = align16(y.off_oval + 4ull * y.n_out);
-    return y;
+    if (codec == ARC_CONST) return Layout{0, 0, 0, 0, 0, 0, 0, 0, kHdr};
+    const bool huff = huff_codec(codec), rle = rle_codec(codec);
+    const uint64_t no = kcount(soff, (uint64_t)fd.seg_base + fd.n_seg) - kcount(soff, fd.seg_base);
+    uint32_t R = 0, nw = 0;
+    if (rle) R = kcount(roff, (uint64_t)fd.rt_base + fd.n_rt) - kcount(roff, fd.rt_base);
+    // the Huffman stream: the N codes, or the R run values
+    const uint32_t nch = rle ? (uint32_t)(((uint64_t)R + fd.hc - 1) / fd.hc) : fd.n_hch;
+    const uint32_t nsub = rle ? (uint32_t)(((uint64_t)R + fd.hs - 1) / fd.hs) : fd.n_sub;
+    if (huff) nw = kcount(woff, (uint64_t)fd.hch_base + nch) - kcount(woff, fd.hch_base);
+    const uint64_t sbits = huff ? align16(kHdr + fd.n_bins) : 0, words = huff ? align16(sbits + 2ull * nsub) : 0;
+    // run values (RLE) or the stream's words, then run lengths, then outliers
+    const uint64_t first = huff ? align16(words + 4ull * nw) : align16(kHdr + 2ull * R);
+    const uint64_t rlen = rle ? first : 0, oidx = rle ? align16(first + 4ull * R) : first;
+    const uint64_t oval = align16(oidx + 4ull * no);
+    return Layout{no, nw, R, sbits, words, rlen, oidx, oval, align16(oval + 4ull * no)};
 }
 
 // --------------------------------------------------------- run-length passes

@@ -1,5 +1,5 @@
 // k_archive.hip -- the archive format (its sections are laid out in encode_dev.h,
-// the header written in k_outlier.hip), statuses, descriptor upload.
+// the header written in k_outlier.hip) and the descriptor upload.
 //
 // Archive format v2 (little-endian, 128-byte header, every section starts on
 // a 16-byte boundary, padding is zero):
@@ -18,45 +18,43 @@
 
 namespace ebc {
 
-__global__ void k_status(const FieldDesc* __restrict__ F, int32_t* __restrict__ st)
+// Upload up to kDescPerLaunch descriptors passed by value, a word per thread
+// (a descriptor per thread took 5 us for eight).  For a decompression (init) the
+// fields' device scalars start from the header values and their code-0 counters
+// from zero.
+__global__ __launch_bounds__(kBlock) void k_put_desc(DescBlob blob, FieldDesc* __restrict__ dst, int init)
 {
-    *st = F[0].dyn->status;
+    // the arguments as memory: indexing the parameter itself by thread would
+    // copy it to scratch first
+    const auto* src = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr() +
+                      offsetof(DescBlob, d) / 4;
+    const uint32_t words = (uint32_t)blob.count * (sizeof(FieldDesc) / 4);
+    uint32_t* out = (uint32_t*)(dst + blob.first);
+    for (uint32_t i = threadIdx.x; i < words; i += kBlock) out[i] = src[i];
+    if (!init) return;
+    const auto* fds = (const __attribute__((address_space(4))) FieldDesc*)src;
+    for (int k = threadIdx.x / kWave; k < blob.count; k += kWavesPerBlock) {
+        const auto& fd = fds[__builtin_amdgcn_readfirstlane(k)];
+        if (fd.codec_hdr != ARC_CONST) fd.zslot[lane_id() * kZeroStride] = 0;
+        if (lane_id() != 0) continue;
+        FieldDyn d = {};
+        d.status = ST_OK;
+        d.codec = fd.codec_hdr;
+        d.ebx2 = fd.ebx2_hdr;
+        d.n_out = fd.n_out_hdr;
+        *fd.dyn = d;
+    }
 }
+static_assert(sizeof(FieldDesc) % 8 == 0 && offsetof(DescBlob, d) % 8 == 0, "copied as words");
 
-__global__ void k_batch_status(const FieldDesc* __restrict__ F, int nf, int32_t* __restrict__ st)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nf) return;
-    st[F[k].slot] = F[k].dyn->status;
-}
-
-// Upload up to kDescPerLaunch descriptors passed by value.
-__global__ void k_put_desc(DescBlob blob, FieldDesc* __restrict__ dst)
-{
-    const int k = threadIdx.x;
-    if (k < blob.count) dst[blob.first + k] = blob.d[k];
-}
-
-hipError_t launch_status(const FieldDesc* F, int32_t* st, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_status, dim3(1), dim3(1), 0, s, F, st);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_status(const FieldDesc* F, int nf, int32_t* st, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_batch_status, dim3((nf + 63) / 64), dim3(64), 0, s, F, nf, st);
-    return hipGetLastError();
-}
-
-hipError_t upload_descs(const FieldDesc* host, int nf, FieldDesc* dev, hipStream_t s)
+hipError_t upload_descs(const FieldDesc* host, int nf, FieldDesc* dev, bool init, hipStream_t s)
 {
     for (int first = 0; first < nf; first += kDescPerLaunch) {
         DescBlob b;
         b.first = first;
         b.count = min(kDescPerLaunch, nf - first);
         for (int k = 0; k < b.count; ++k) b.d[k] = host[first + k];
-        hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(kDescPerLaunch), 0, s, b, dev);
+        hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(kBlock), 0, s, b, dev, init ? 1 : 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -545,13 +545,10 @@ __global__ __launch_bounds__(kCb) void k_codebook_wide(const FieldDesc* __restri
 // above a window is the length of the codeword it starts with.  A search over
 // the lengths for every entry and a scan for the long prefixes took 18 us for
 // 1024 bins (36 us for 16384).
-__global__ __launch_bounds__(kCb) void k_dectab(const FieldDesc* __restrict__ F,
-                                                   uint8_t* __restrict__ tabs, size_t stride)
+__device__ __forceinline__ void build_dectab(const FieldDesc& fd, DecTab* T)
 {
-    const FieldDesc& fd = F[blockIdx.x];
     EBC_G FieldDyn* dy = fd.dyn;
     if (dy->status != ST_OK || !huff_codec(dy->codec)) return;
-    DecTab* T = (DecTab*)(tabs + (size_t)blockIdx.x * stride);
     const uint32_t nb = fd.n_bins;
     const bool narrow = nb <= kMaxBins;  // the permutation is kept in LDS too
     __shared__ uint32_t wc[kCbWaves * 64];
@@ -708,6 +705,80 @@ __global__ __launch_bounds__(kCb) void k_dectab(const FieldDesc* __restrict__ F,
     }
 }
 
+// Chunk c of a field: the start bits of its sub-chunks inside it (the running
+// sums of the stored sub-chunk bit counts); returns its word count.
+__device__ __forceinline__ uint32_t chunk_words(const FieldDesc& fd, uint32_t c, uint32_t* __restrict__ soff)
+{
+    const EBC_G uint16_t* __restrict__ sb = (const EBC_G uint16_t*)(fd.arc + fd.off_sbits);
+    const uint32_t k = fd.hc / fd.hs;  // sub-chunks per chunk
+    const uint32_t s0 = c * k, s1 = min(s0 + k, fd.n_sub);
+    uint32_t run = 0;
+    uint32_t s = s0;
+    for (; s + 4 <= s1; s += 4) {
+        uint32_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = sb[s + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            soff[fd.sub_base + s + u] = run;
+            run += x[u];
+        }
+    }
+    for (; s < s1; ++s) {
+        soff[fd.sub_base + s] = run;
+        run += sb[s];
+    }
+    return (run + 31) / 32;
+}
+
+// Huffman decompression prologue: the decoder tables of every field (workgroups
+// below nf), and the offsets of its sub-chunks.  DIRECT (no field has more than
+// kPrepDirect chunks): one workgroup per field scans the word counts as well,
+// and no scan launches follow.  Otherwise a thread per chunk stores its word
+// count for the scan.  (Tables, counts, two scan launches and a check of their
+// sum were five launches, 23 us on 256x256.)
+template <bool DIRECT>
+__global__ __launch_bounds__(kCb) void k_dec_prep(const FieldDesc* __restrict__ F, int nf,
+                                                  uint8_t* __restrict__ tabs, size_t stride,
+                                                  uint32_t* __restrict__ wcnt, uint32_t* __restrict__ soff)
+{
+    uint32_t t = blockIdx.x;
+    if (t < (uint32_t)nf) {
+        build_dectab(F[t], (DecTab*)(tabs + (size_t)t * stride));
+        return;
+    }
+    t -= (uint32_t)nf;
+    if (DIRECT) {
+        __shared__ uint32_t s_w[kCbWaves];
+        const FieldDesc& fd = F[t];
+        if (!huff_codec(fd.codec_hdr)) return;
+        constexpr uint32_t kPer = kPrepDirect / kCb;
+        const uint32_t c0 = threadIdx.x * kPer;
+        uint32_t words[kPer], sum = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) {
+            words[k] = c0 + k < fd.n_hch ? chunk_words(fd, c0 + k, soff) : 0u;
+            sum += words[k];
+        }
+        const uint32_t inc = wave_incl_scan_u32(sum);
+        uint32_t tot;
+        uint32_t off = waves_before((uint32_t)__builtin_amdgcn_readlane((int)inc, 63), s_w, &tot) + inc - sum;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) {
+            if (c0 + k < fd.n_hch) wcnt[fd.hch_base + c0 + k] = off;
+            off += words[k];
+        }
+        if (threadIdx.x == 0) wcnt[fd.hch_base + fd.n_hch] = tot;
+    } else {
+        const int f = find_field<&FieldDesc::hpwg_base>(F, nf, t);
+        const FieldDesc& fd = F[f];
+        const uint32_t c = (t - fd.hpwg_base) * kCb + threadIdx.x;
+        if (!huff_codec(fd.codec_hdr)) return;
+        if (c == 0) wcnt[fd.hch_base + fd.n_hch] = 0;
+        if (c < fd.n_hch) wcnt[fd.hch_base + c] = chunk_words(fd, c, soff);
+    }
+}
+
 hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass, bool direct, hipStream_t s)
 {
     if (n_bins > kMaxBins) hipLaunchKernelGGL(k_codebook_wide, dim3(nf), dim3(kCb), kWideLds, s, F, pass);
@@ -715,9 +786,13 @@ hipError_t launch_codebook(const FieldDesc* F, int nf, uint32_t n_bins, int pass
     return hipGetLastError();
 }
 
-hipError_t launch_dectab(const FieldDesc* F, int nf, uint8_t* tabs, size_t stride, hipStream_t s)
+hipError_t launch_dec_prep(const FieldDesc* F, int nf, uint32_t units, bool direct, uint8_t* tabs, size_t stride,
+                           uint32_t* wcnt, uint32_t* soff, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dectab, dim3(nf), dim3(kCb), 0, s, F, tabs, stride);
+    if (direct)
+        hipLaunchKernelGGL(k_dec_prep<true>, dim3(2 * nf), dim3(kCb), 0, s, F, nf, tabs, stride, wcnt, soff);
+    else
+        hipLaunchKernelGGL(k_dec_prep<false>, dim3(nf + units), dim3(kCb), 0, s, F, nf, tabs, stride, wcnt, soff);
     return hipGetLastError();
 }
 

@@ -676,6 +676,12 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     const FieldDesc& fd = F[f];
     EBC_G FieldDyn* dy = fd.dyn;
     if (dy->status != ST_OK || !huff_codec(dy->codec)) return;
+    // the chunks' words must add up to the header's count
+    const uint32_t tot = woff[fd.hch_base + fd.n_hch] - woff[fd.hch_base];
+    if ((uint64_t)tot != fd.n_words_hdr) {
+        if (threadIdx.x == 0) atomicMin(&dy->status, (int32_t)ST_ERR_ARCHIVE);
+        return;
+    }
     const DecTab* __restrict__ T = (const DecTab*)(tabs + (size_t)f * tab_stride);
     const uint32_t l2k = T->l2k, l2n = T->l2n;
     const uint32_t l2sub = (1u << (kLutBits + l2k)) - l2n;  // first long prefix << l2k
@@ -736,8 +742,8 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
         const uint32_t w0 = (uint32_t)(b0 >> 5);
         const uint32_t skip = (uint32_t)(b0 & 31);
         const uint32_t nwl = live ? (skip + nbits + 31) / 32 : 0u;  // words the lane may read
-        // the chunk words were checked against the archive's word count, and a
-        // sub-chunk ends inside its chunk by construction of the offsets
+        // the chunks' words add up to the archive's word count, and a sub-chunk
+        // ends inside its chunk by construction of the offsets
         const EBC_G uint32_t* __restrict__ words = stream + w0;
 
         // Stream position: pm = (bit position) - 1, counted from the first bit
@@ -892,29 +898,6 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     }
 }
 
-// Huffman decompression prologue, one thread per chunk: the in-chunk start
-// bit of each of its sub-chunks (the running sum of the stored sub-chunk bit
-// counts) and the chunk's word count (scanned next into word offsets).
-__global__ __launch_bounds__(kBlock) void k_huff_prep(const FieldDesc* __restrict__ F, int nf,
-                                                      uint32_t* __restrict__ wcnt,
-                                                      uint32_t* __restrict__ soff)
-{
-    const uint32_t t = blockIdx.x;
-    const int f = find_field<&FieldDesc::hpwg_base>(F, nf, t);
-    const FieldDesc& fd = F[f];
-    const uint32_t c = (t - fd.hpwg_base) * kBlock + threadIdx.x;
-    if (!huff_codec(fd.dyn->codec) || c >= fd.n_hch) return;
-    const uint32_t per = fd.hc / fd.hs;
-    const uint32_t s0 = c * per, s1 = min(s0 + per, fd.n_sub);
-    const EBC_G uint16_t* sb = (const EBC_G uint16_t*)(fd.arc + fd.off_sbits);
-    uint32_t run = 0;
-    for (uint32_t k = s0; k < s1; ++k) {
-        soff[fd.sub_base + k] = run;
-        run += sb[k];
-    }
-    wcnt[fd.hch_base + c] = (run + 31) / 32;
-}
-
 #define EBC_HC_DISPATCH(KERNEL, W, ...)                                                     \
     switch (hc) {                                                                           \
     case 64: hipLaunchKernelGGL((KERNEL<1, W>), __VA_ARGS__); break;                        \
@@ -926,23 +909,6 @@ __global__ __launch_bounds__(kBlock) void k_huff_prep(const FieldDesc* __restric
     case 4096: hipLaunchKernelGGL((KERNEL<64, W>), __VA_ARGS__); break;                     \
     default: return hipErrorInvalidValue;                                                   \
     }
-
-// decompression: the scanned word counts must add up to the header's count
-__global__ void k_words_check(const FieldDesc* __restrict__ F, int nf, const uint32_t* __restrict__ woff)
-{
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const FieldDesc& fd = F[f];
-    if (!huff_codec(fd.codec_hdr)) return;
-    const uint32_t tot = woff[fd.hch_base + fd.n_hch] - woff[fd.hch_base];
-    if ((uint64_t)tot != fd.n_words_hdr) atomicMin(&fd.dyn->status, (int32_t)ST_ERR_ARCHIVE);
-}
-
-hipError_t launch_words_check(const FieldDesc* F, int nf, const uint32_t* woff, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_words_check, dim3((nf + 63) / 64), dim3(64), 0, s, F, nf, woff);
-    return hipGetLastError();
-}
 
 // persistent grid: enough workgroups to fill the device several times over
 static uint32_t persistent_grid(uint32_t units) { return units < kPersistentBlocks ? units : kPersistentBlocks; }
@@ -994,14 +960,6 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
     } else {
         EBC_HC_DISPATCH(k_huff_write, false, g, b, sh, s, F, nf, soff, woff, roff, units)
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_huff_prep(const FieldDesc* F, int nf, uint32_t units, uint32_t* wcnt, uint32_t* soff,
-                            hipStream_t s)
-{
-    if (!units) return hipSuccess;
-    hipLaunchKernelGGL(k_huff_prep, dim3(units), dim3(kBlock), 0, s, F, nf, wcnt, soff);
     return hipGetLastError();
 }
 

@@ -14,10 +14,14 @@
 
 namespace ebc {
 
-constexpr uint32_t kSegPerBlock = kWave;  // segments per workgroup
-constexpr uint32_t kSegLane = 8;          // elements of a segment per lane
+constexpr uint32_t kSegLane = 8;  // elements of a segment per lane
 
-uint32_t outlier_write_units(uint32_t n_seg) { return (n_seg + kSegPerBlock - 1) / kSegPerBlock; }
+// Segments per workgroup.  Most segments of a large field hold no outlier and a
+// workgroup's time is that of looking at them: 256, one per thread (18 us with
+// 64 against 10 us on the 1M segments of 512^3).  Smaller fields have too few
+// workgroups for that if many segments hold outliers (62 us against 37 us on
+// the 2e5 of a rough 100x500x500 field): 64.
+uint32_t outlier_write_segs(uint32_t n_seg) { return n_seg > (1u << 19) ? kBlock : kWave; }
 
 // element range [a, b) of segment s
 __device__ __forceinline__ void seg_range(const FieldDesc& fd, uint32_t s, uint64_t& a, uint64_t& b)
@@ -38,51 +42,64 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 
-// A workgroup looks at kSegPerBlock segments (xs elements each, a power of two
+// A workgroup looks at its segments (xs elements each, a power of two
 // from 32 to 256) and lists those that hold outliers; a field without many
 // ends there.  Listed segments are then compacted 256 * 8 / xs at a time, xs / 8
-// lanes to a segment and eight elements to a lane: codes and deltas come in one
-// round trip of 16-byte loads (any alignment) for two such groups, and a scan of
-// the lanes' counts gives every outlier its place.  With a thread per segment,
+// lanes to a segment and eight elements to a lane, two such groups in flight:
+// codes by 16-byte loads (any alignment) and the deltas along with them, or if
+// outliers are rare only those of the lanes that turn out to hold one, and a scan
+// of the lanes' counts gives every outlier its place.  With a thread per segment,
 // each walking up to 256 elements, the kernel took 77 us on a 100x500x500 field
 // most of whose segments hold outliers (15 us on 256x256).
 // offsets(): the list's two sections, asked for only when there is something
 // to write.
 struct OutlierLds {
-    uint32_t seg[kSegPerBlock], pos[kSegPerBlock], n;
+    uint32_t seg[kBlock], pos[kBlock], n[kWavesPerBlock];
+};
+struct OutlierOut {
+    EBC_G uint32_t* oidx;
+    EBC_G int32_t* oval;
+    bool ok;
 };
 template <class OFFSETS>
 __device__ __forceinline__ void outlier_unit(const FieldDesc& fd, uint32_t t, const uint32_t* __restrict__ soff,
                                              OutlierLds& sm, OFFSETS offsets)
 {
-    const uint32_t l = lane_id();
-    if (threadIdx.x < (uint32_t)kWave) {
-        const uint32_t sg = (t - fd.ow_base) * kSegPerBlock + l;
+    const uint32_t l = lane_id(), w = threadIdx.x / kWave;
+    {
+        const uint32_t sg = (t - fd.ow_base) * fd.ow_segs + threadIdx.x;
         const uint32_t* off = soff + fd.seg_base;
         uint32_t o0 = 0, o1 = 0;
-        if (sg < fd.n_seg) o0 = off[sg], o1 = off[sg + 1];
+        if (threadIdx.x < fd.ow_segs && sg < fd.n_seg) o0 = off[sg], o1 = off[sg + 1];
         const uint64_t m = ballot(o0 != o1);
+        if (l == 0) sm.n[w] = __popcll(m);
+        __syncthreads();
+        uint32_t k = __popcll(m & ((1ull << l) - 1));
+#pragma unroll
+        for (uint32_t v = 0; v < (uint32_t)kWavesPerBlock - 1; ++v) k += v < w ? sm.n[v] : 0u;
         if (o0 != o1) {
-            const uint32_t k = __popcll(m & ((1ull << l) - 1));
             sm.seg[k] = sg;
-            sm.pos[k] = o0 - off[0];
+            sm.pos[k] = o0 - kcount(off, 0);
         }
-        if (l == 0) sm.n = __popcll(m);
     }
     __syncthreads();
-    const uint32_t n = sm.n;
+    const uint32_t n = sm.n[0] + sm.n[1] + sm.n[2] + sm.n[3];
     if (n == 0) return;
-    EBC_G uint32_t* oidx;
-    EBC_G int32_t* oval;
-    if (!offsets(oidx, oval)) return;
+    const OutlierOut to = offsets();
+    if (!to.ok) return;
+    EBC_G uint32_t* const oidx = to.oidx;
+    EBC_G int32_t* const oval = to.oval;
     const EBC_G uint16_t* __restrict__ q = fd.q;
     const EBC_G int32_t* __restrict__ dsc = fd.dsc;
     const uint32_t g = fd.xs / kSegLane;  // lanes per segment: 4 .. 32
+    // outliers in more than one of 16 elements: nearly every lane needs its deltas
+    const bool dense = 16 * (uint64_t)(kcount(soff, (uint64_t)fd.seg_base + fd.n_seg) - kcount(soff, fd.seg_base)) > fd.n;
     const uint32_t sub = threadIdx.x / g, gl = threadIdx.x % g, per = kBlock / g;
     for (uint32_t k0 = 0; k0 < n; k0 += 2 * per) {
         u32x4 c[2], d0[2], d1[2];
         uint64_t i[2];
         uint32_t p[2];
+        bool full[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const uint32_t k = k0 + h * per + sub;
@@ -95,36 +112,46 @@ __device__ __forceinline__ void outlier_unit(const FieldDesc& fd, uint32_t t, co
             i[h] = a + gl * kSegLane;
             c[h] = u32x4{0x00010001u, 0x00010001u, 0x00010001u, 0x00010001u};
             d0[h] = d1[h] = u32x4{0u, 0u, 0u, 0u};
-            if (i[h] + kSegLane <= b) {
+            full[h] = i[h] + kSegLane <= b;
+            if (full[h]) {
                 c[h] = *(const EBC_G u32x4_a2*)(q + i[h]);
-                d0[h] = *(const EBC_G u32x4_a4*)(dsc + i[h]);
-                d1[h] = *(const EBC_G u32x4_a4*)(dsc + i[h] + 4);
+                if (dense) {
+                    d0[h] = *(const EBC_G u32x4_a4*)(dsc + i[h]);
+                    d1[h] = *(const EBC_G u32x4_a4*)(dsc + i[h] + 4);
+                }
             } else if (i[h] < b) {  // the row's end
 #pragma unroll
                 for (uint32_t e = 0; e < kSegLane - 1; ++e) {
                     if (i[h] + e < b) {
                         const uint32_t sh = 16 * (e & 1);
                         c[h][e / 2] = (c[h][e / 2] & ~(0xFFFFu << sh)) | ((uint32_t)q[i[h] + e] << sh);
-                        if (e < 4) d0[h][e & 3] = (uint32_t)dsc[i[h] + e];
-                        else d1[h][e & 3] = (uint32_t)dsc[i[h] + e];
                     }
                 }
             }
         }
+        uint32_t zm[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            uint32_t zm = 0;
+            zm[h] = 0;
 #pragma unroll
             for (uint32_t e = 0; e < kSegLane; ++e)
-                zm |= (((c[h][e / 2] >> (16 * (e & 1))) & 0xFFFFu) == 0 ? 1u : 0u) << e;
+                zm[h] |= (((c[h][e / 2] >> (16 * (e & 1))) & 0xFFFFu) == 0 ? 1u : 0u) << e;
+            // (the workspace goes on past the field's last delta)
+            if (!dense || !full[h]) {
+                if (zm[h] & 0x0Fu) d0[h] = *(const EBC_G u32x4_a4*)(dsc + i[h]);
+                if (zm[h] & 0xF0u) d1[h] = *(const EBC_G u32x4_a4*)(dsc + i[h] + 4);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
             // rank of the lane's outliers inside its segment
-            const uint32_t cnt = __popc(zm), excl = wave_incl_scan_u32(cnt) - cnt;
+            const uint32_t cnt = __popc(zm[h]), excl = wave_incl_scan_u32(cnt) - cnt;
             const uint32_t first = (uint32_t)__shfl((int)excl, (int)(l - l % g));
-            if (zm) {
+            if (zm[h]) {
                 uint32_t pos = p[h] + excl - first;
 #pragma unroll
                 for (uint32_t e = 0; e < kSegLane; ++e) {
-                    if ((zm >> e) & 1u) {
+                    if ((zm[h] >> e) & 1u) {
                         oidx[pos] = (uint32_t)(i[h] + e);
                         oval[pos] = (int32_t)(e < 4 ? d0[h][e & 3] : d1[h][e & 3]);
                         ++pos;
@@ -146,10 +173,8 @@ __global__ __launch_bounds__(kBlock) void k_outlier_write(const FieldDesc* __res
     const auto* dy = kconst(fd.dyn);
     if (dy->status != ST_OK || dy->codec == ARC_CONST || dy->n_out == 0) return;
     __shared__ OutlierLds sm;
-    outlier_unit(fd, t, soff, sm, [&](EBC_G uint32_t*& oidx, EBC_G int32_t*& oval) {
-        oidx = (EBC_G uint32_t*)(fd.arc + dy->off_oidx);
-        oval = (EBC_G int32_t*)(fd.arc + dy->off_oval);
-        return true;
+    outlier_unit(fd, t, soff, sm, [&] {
+        return OutlierOut{(EBC_G uint32_t*)(fd.arc + dy->off_oidx), (EBC_G int32_t*)(fd.arc + dy->off_oval), true};
     });
 }
 
@@ -199,6 +224,7 @@ __device__ __forceinline__ void write_header(const FieldDesc& fd, const uint32_t
                ((uint32_t)fd.dtype << 24);
         h[3] = fd.n_bins;
         const uint64_t dims[3] = {fd.nx, fd.ny, fd.nz};
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
             h[4 + 2 * k] = (uint32_t)dims[k];
             h[5 + 2 * k] = (uint32_t)(dims[k] >> 32);
@@ -208,6 +234,7 @@ __device__ __forceinline__ void write_header(const FieldDesc& fd, const uint32_t
         h[12] = fd.rank == 3 ? 8u : 1u;
         h[13] = fd.hc;
         const double dd[3] = {fd.eb, dy->eb_abs, dy->ebx2};
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
             const uint64_t b = (uint64_t)__double_as_longlong(dd[k]);
             h[14 + 2 * k] = (uint32_t)b;
@@ -219,6 +246,7 @@ __device__ __forceinline__ void write_header(const FieldDesc& fd, const uint32_t
         h[21] = (uint32_t)(cb >> 32);
         const uint64_t na = codec == ARC_HUFFMAN ? (uint64_t)fd.n_hch : y.n_runs;  // RLE, RLE+VLE: runs
         const uint64_t v[4] = {y.n_out, codec == ARC_CONST ? 0ull : na, y.n_words, y.total};
+#pragma unroll
         for (int k = 0; k < 4; ++k) {
             h[22 + 2 * k] = (uint32_t)v[k];
             h[23 + 2 * k] = (uint32_t)(v[k] >> 32);
@@ -282,11 +310,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(const FieldDesc* __restrict__
     const auto* dy = kconst(fd.dyn);
     const int32_t codec = dy->codec;
     if (dy->status != ST_OK || codec == ARC_CONST) return;
-    outlier_unit(fd, t, soff, sm, [&](EBC_G uint32_t*& oidx, EBC_G int32_t*& oval) {
+    outlier_unit(fd, t, soff, sm, [&] {
         const Layout y = layout_of(fd, codec, soff, woff, roff);
-        oidx = (EBC_G uint32_t*)(fd.arc + y.off_oidx);
-        oval = (EBC_G int32_t*)(fd.arc + y.off_oval);
-        return y.total <= fd.arc_cap;
+        return OutlierOut{(EBC_G uint32_t*)(fd.arc + y.off_oidx), (EBC_G int32_t*)(fd.arc + y.off_oval),
+                          y.total <= fd.arc_cap};
     });
 }
 

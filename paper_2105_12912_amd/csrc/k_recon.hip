@@ -595,31 +595,21 @@ __global__ __launch_bounds__(kBlock) void k_recon3_fix(const FieldDesc* __restri
         atomicAdd(&fd.zslot[((t * kWavesPerBlock + w) % kZeroSlots) * kZeroStride], zs);
 }
 
-// decompression epilogue: the code-0 count must equal the outlier count (one
-// wave per field)
+// decompression epilogue, one wave per field: the code-0 count must equal the
+// outlier count; the field's status into the caller's slot (st may be NULL)
 static_assert(kZeroSlots == kWave, "one lane per counter");
-__global__ __launch_bounds__(kWave) void k_recon_check(const FieldDesc* __restrict__ F)
+__global__ __launch_bounds__(kWave) void k_recon_check(const FieldDesc* __restrict__ F, int32_t* __restrict__ st)
 {
     const FieldDesc& fd = F[blockIdx.x];
     EBC_G FieldDyn* dy = fd.dyn;
-    if (dy->status != ST_OK || fd.codec_hdr == ARC_CONST) return;
-    const uint64_t z = wave_sum_u64(fd.zslot[lane_id() * kZeroStride]);
-    if (lane_id() == 0 && z != fd.n_out_hdr) dy->status = ST_ERR_ARCHIVE;
-}
-
-// decompression prologue: per-field device scalars from the header values, and
-// the code-0 counters cleared (one wave per field)
-__global__ __launch_bounds__(kWave) void k_dinit(const FieldDesc* __restrict__ F)
-{
-    const FieldDesc& fd = F[blockIdx.x];
-    if (fd.codec_hdr != ARC_CONST) fd.zslot[lane_id() * kZeroStride] = 0;
+    int32_t status = dy->status;
+    if (status == ST_OK && fd.codec_hdr != ARC_CONST) {
+        const uint64_t z = wave_sum_u64(fd.zslot[lane_id() * kZeroStride]);
+        if (z != fd.n_out_hdr) status = ST_ERR_ARCHIVE;
+    }
     if (lane_id() != 0) return;
-    FieldDyn d = {};
-    d.status = ST_OK;
-    d.codec = fd.codec_hdr;
-    d.ebx2 = fd.ebx2_hdr;
-    d.n_out = fd.n_out_hdr;
-    *fd.dyn = d;
+    dy->status = status;
+    if (st) st[fd.slot] = status;
 }
 
 // constant field (range zero): every element is the stored value
@@ -672,15 +662,9 @@ hipError_t launch_recon_fix(const FieldDesc* F, int nf, uint32_t units, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_recon_check(const FieldDesc* F, int nf, hipStream_t s)
+hipError_t launch_recon_check(const FieldDesc* F, int nf, int32_t* st, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_recon_check, dim3(nf), dim3(kWave), 0, s, F);
-    return hipGetLastError();
-}
-
-hipError_t launch_dinit(const FieldDesc* F, int nf, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_dinit, dim3(nf), dim3(kWave), 0, s, F);
+    hipLaunchKernelGGL(k_recon_check, dim3(nf), dim3(kWave), 0, s, F, st);
     return hipGetLastError();
 }
 

@@ -90,40 +90,42 @@ __global__ __launch_bounds__(kBlock) void k_rle_prep(const FieldDesc* __restrict
     starts[fd.rle_base + k] = L;
 }
 
-// After the scan: the runs must cover the field exactly.  With every length
-// in [1, n], the relative starts (mod 2^32) increase strictly exactly when no
-// prefix sum wrapped, and then the last one is the true total, which must
-// equal n.  One thread per run (the run-length prep grid).
-__global__ __launch_bounds__(kBlock) void k_rle_check(const FieldDesc* __restrict__ F, int nf,
-                                                      const uint32_t* __restrict__ starts)
-{
-    const uint32_t t = blockIdx.x;
-    const int f = find_field<&FieldDesc::rl_base>(F, nf, t);
-    const FieldDesc& fd = F[f];
-    const uint32_t k = (t - fd.rl_base) * kBlock + threadIdx.x;
-    if (!rle_codec(fd.codec_hdr) || k >= fd.n_runs_hdr) return;
-    const uint32_t* S = starts + fd.rle_base;
-    const uint32_t s0 = S[0];
-    const uint32_t a = S[k] - s0, b = S[k + 1] - s0;
-    bool bad = b <= a;
-    if (k + 1 == fd.n_runs_hdr && (uint64_t)b != fd.n) bad = true;
-    if (bad) atomicMin(&fd.dyn->status, ST_ERR_ARCHIVE);
-}
-
-// After the check: for every output tile, the run that holds its first
-// element (the largest r with start[r] <= tile start) and the number of runs
-// it overlaps, one thread per tile, so that every tile's searches are in
+// After the scan, two things in one launch.
+//
+// Check, one thread per run (workgroups below rl_units): the runs must cover
+// the field exactly.  With every length in [1, n], the relative starts (mod
+// 2^32) increase strictly exactly when no prefix sum wrapped, and then the last
+// one is the true total, which must equal n.
+//
+// Tile map, one thread per output tile (the other workgroups): the run that
+// holds the tile's first element (the largest r with start[r] <= tile start)
+// and the number of runs it overlaps, so that every tile's searches are in
 // flight at once rather than one thread per workgroup searching while the
-// others wait.  tmap[2t] = first run, tmap[2t + 1] = run count.
-__global__ __launch_bounds__(kBlock) void k_rle_tilemap(const FieldDesc* __restrict__ F, int nf,
-                                                        uint32_t units, const uint32_t* __restrict__ starts,
-                                                        uint32_t* __restrict__ tmap)
+// others wait.  The searches stay inside the run array whatever it holds.
+// tmap[2t] = first run, tmap[2t + 1] = run count.
+__global__ __launch_bounds__(kBlock) void k_rle_map(const FieldDesc* __restrict__ F, int nf, uint32_t rl_units,
+                                                    uint32_t rt_units, const uint32_t* __restrict__ starts,
+                                                    uint32_t* __restrict__ tmap)
 {
-    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= units) return;
+    if (blockIdx.x < rl_units) {
+        const uint32_t t = blockIdx.x;
+        const int f = find_field<&FieldDesc::rl_base>(F, nf, t);
+        const FieldDesc& fd = F[f];
+        const uint32_t k = (t - fd.rl_base) * kBlock + threadIdx.x;
+        if (!rle_codec(fd.codec_hdr) || k >= fd.n_runs_hdr) return;
+        const uint32_t* S = starts + fd.rle_base;
+        const uint32_t s0 = S[0];
+        const uint32_t a = S[k] - s0, b = S[k + 1] - s0;
+        bool bad = b <= a;
+        if (k + 1 == fd.n_runs_hdr && (uint64_t)b != fd.n) bad = true;
+        if (bad) atomicMin(&fd.dyn->status, ST_ERR_ARCHIVE);
+        return;
+    }
+    const uint32_t t = (blockIdx.x - rl_units) * kBlock + threadIdx.x;
+    if (t >= rt_units) return;
     const int f = find_field<&FieldDesc::rt_base>(F, nf, t);
     const FieldDesc& fd = F[f];
-    if (fd.dyn->status != ST_OK || !rle_codec(fd.codec_hdr)) return;
+    if (!rle_codec(fd.codec_hdr)) return;
     const uint32_t* S = starts + fd.rle_base;
     const uint32_t s0 = S[0];
     const uint64_t lo = (uint64_t)(t - fd.rt_base) * kRleTile;
@@ -244,12 +246,9 @@ hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint
     hipLaunchKernelGGL(k_rle_prep, dim3(rl_units), dim3(kBlock), 0, s, F, nf, starts);
     hipError_t e = launch_scan(starts, n_starts, tmp, s, scan_direct);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rle_check, dim3(rl_units), dim3(kBlock), 0, s, F, nf, starts);
-    if (rt_units) {
-        hipLaunchKernelGGL(k_rle_tilemap, dim3((rt_units + kBlock - 1) / kBlock), dim3(kBlock), 0, s, F, nf,
-                           rt_units, starts, tmap);
-        hipLaunchKernelGGL(k_rle_expand, dim3(rt_units), dim3(kBlock), 0, s, F, nf, starts, tmap);
-    }
+    hipLaunchKernelGGL(k_rle_map, dim3(rl_units + (rt_units + kBlock - 1) / kBlock), dim3(kBlock), 0, s, F, nf,
+                       rl_units, rt_units, starts, tmap);
+    if (rt_units) hipLaunchKernelGGL(k_rle_expand, dim3(rt_units), dim3(kBlock), 0, s, F, nf, starts, tmap);
     return hipGetLastError();
 }
 
