@@ -6,13 +6,10 @@
 // chunk, and the N-D sum splits into one-axis passes (x, then y, then z;
 // Algorithm 1, decompression half).  Output = d * (2 eb) rounded once to fp32.
 //
-// Mapping (same tiles and lane layout as construction): a lane owns four
-// consecutive x.  The x pass is a within-lane prefix plus the totals of the
-// quads to its left in the chunk row (one DPP row shift in 3D, two lane
-// shuffles in 2D, a full-wave scan for the 256-long 1D chunk).  The y pass is
-// a scan across the lanes of a chunk column with DPP row shifts (8 lanes in
-// 3D, the 16 lanes of a DPP row in 2D); the z pass is a running sum in
-// registers as the wave walks the chunk's planes.  Integer sums wrap modulo
+// Mapping: a lane owns four consecutive x.  The x pass is a within-lane prefix
+// plus the totals of the quads to its left in the chunk row (DPP row shifts in
+// 2D and 3D, a full-wave scan for the 256-long 1D chunk); the y and z passes are
+// running sums in registers as the wave walks the chunk's rows and planes.  Integer sums wrap modulo
 // 2^32 exactly as the CPU recurrence truncated to int32 does.
 #include "ebc_dev.h"
 #include "ebc_launch.h"
@@ -117,47 +114,22 @@ template <class OT> __device__ __forceinline__ EBC_G OT* field_out(const FieldDe
 template <> __device__ __forceinline__ EBC_G float* field_out<float>(const FieldDesc& fd) { return fd.outf; }
 template <> __device__ __forceinline__ EBC_G double* field_out<double>(const FieldDesc& fd) { return fd.outd; }
 
-// This lane's quads of one workgroup tile: four 256-long chunks' quads (1D),
-// four chunks along x (2D) or the eight z-planes of the chunk column (3D).
-template <int RANK>
+// 1D: this lane's quads of one workgroup tile, one in each of the wave's four
+// 256-long chunks.
 struct RTile {
-    static constexpr int NQ = RANK == 3 ? 8 : 4;
+    static constexpr int NQ = 4;
     u32x2 raw[NQ];
 };
 
 // lane geometry of a tile: first element of quad k and its valid count
-template <int RANK>
 __device__ __forceinline__ void rquad(const FieldDesc& fd, uint32_t tl, int k, uint64_t& i0, int& nv)
 {
     const int l = lane_id();
     const uint32_t w = threadIdx.x / kWave;
-    if (RANK == 1) {
-        const uint32_t wt = tl * kWavesPerBlock + w;
-        i0 = (uint64_t)wt * 1024 + k * 256 + 4 * l;
-        nv = (wt >= fd.n_wave_tiles || i0 >= fd.n) ? 0 : (int)min<uint64_t>(4, fd.n - i0);
-        if (nv == 0) i0 = 0;
-        return;
-    }
-    const uint32_t wx = fd.wx, wy = kWavesPerBlock / wx;
-    const uint32_t wxi = w % wx, wyi = w / wx;
-    const uint32_t nxb = fd.nxb, nyb = fd.nyb;
-    const uint32_t xb = tl % nxb, yb = (tl / nxb) % nyb, zb = tl / (nxb * nyb);
-    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    uint32_t x0, yy, z;
-    if (RANK == 3) {
-        const uint32_t y = l & 7, xq = l >> 3;
-        x0 = xb * fd.xs + wxi * 32 + 4 * xq;
-        yy = yb * 8 * wy + wyi * 8 + y;
-        z = zb * 8 + k;
-    } else {
-        const uint32_t y = l & 15, xq = l >> 4;
-        x0 = xb * fd.xs + wxi * 64 + 16 * k + 4 * xq;
-        yy = yb * 16 * wy + wyi * 16 + y;
-        z = 0;
-    }
-    const bool ok = x0 < nx && yy < ny && z < nz;
-    nv = ok ? (int)min<uint32_t>(4, nx - x0) : 0;
-    i0 = ok ? ((uint64_t)z * ny + yy) * nx + x0 : 0;
+    const uint32_t wt = tl * kWavesPerBlock + w;
+    i0 = (uint64_t)wt * 1024 + k * 256 + 4 * l;
+    nv = (wt >= fd.n_wave_tiles || i0 >= fd.n) ? 0 : (int)min<uint64_t>(4, fd.n - i0);
+    if (nv == 0) i0 = 0;
 }
 
 // With 16-byte rows (VEC) every quad is loaded with one unconditional vector
@@ -165,33 +137,31 @@ __device__ __forceinline__ void rquad(const FieldDesc& fd, uint32_t tl, int k, u
 // 1D field may read up to 6 bytes past the codes, into the outlier scratch
 // that follows them), so the number of memory operations per tile is fixed
 // and the compiler never has to wait for stores before a load's use.
-template <int RANK, bool VEC>
-__device__ __forceinline__ void rtile_load(const FieldDesc& fd, uint32_t tl, RTile<RANK>& T)
+template <bool VEC>
+__device__ __forceinline__ void rtile_load(const FieldDesc& fd, uint32_t tl, RTile& T)
 {
 #pragma unroll
-    for (int k = 0; k < RTile<RANK>::NQ; ++k) {
+    for (int k = 0; k < RTile::NQ; ++k) {
         uint64_t i0;
         int nv;
-        rquad<RANK>(fd, tl, k, i0, nv);
+        rquad(fd, tl, k, i0, nv);
         if (VEC) T.raw[k] = ld_nt_u2(fd.q + (nv > 0 ? i0 : 0));
         else T.raw[k] = load_packed<false>(fd.q, i0, nv);
     }
 }
 
-template <int RANK, bool VEC, class OT>
-__device__ __forceinline__ void rtile_process(const FieldDesc& fd, uint32_t tl, const RTile<RANK>& T,
+template <bool VEC, class OT>
+__device__ __forceinline__ void rtile_process(const FieldDesc& fd, uint32_t tl, const RTile& T,
                                               double ebx2, uint32_t& zeros)
 {
-    const int l = lane_id();
     const int32_t r = (int32_t)(fd.n_bins / 2);
     const EBC_G int32_t* __restrict__ dsc = fd.dsc;
     EBC_G OT* __restrict__ out = field_out<OT>(fd);
-    uint32_t zprev[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int k = 0; k < RTile<RANK>::NQ; ++k) {
+    for (int k = 0; k < RTile::NQ; ++k) {
         uint64_t i0;
         int nv;
-        rquad<RANK>(fd, tl, k, i0, nv);
+        rquad(fd, tl, k, i0, nv);
         uint32_t c[4], s[4];
         unpack4(T.raw[k], c);
         if (VEC) {
@@ -201,49 +171,10 @@ __device__ __forceinline__ void rtile_process(const FieldDesc& fd, uint32_t tl, 
         }
         fuse4(c, nv, r, dsc, i0, s, zeros);
         s[1] += s[0], s[2] += s[1], s[3] += s[2];  // x pass within the quad
-        if (RANK == 1) {
-            // exclusive prefix of the lane totals over the 256-long chunk
-            const uint32_t excl = wave_incl_scan_u32(s[3]) - s[3];
+        // exclusive prefix of the lane totals over the 256-long chunk
+        const uint32_t excl = wave_incl_scan_u32(s[3]) - s[3];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] += excl;
-        } else if (RANK == 3) {
-            const uint32_t y = l & 7, xq = l >> 3;
-            uint32_t left = dpp_shr_u<8>(s[3]);  // the quad to the left in the chunk
-            if ((xq & 1) == 0) left = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                s[j] += left;
-                // y pass: inclusive scan over the 8 lanes of the chunk column
-                uint32_t a = dpp_shr_u<1>(s[j]);
-                s[j] += y >= 1 ? a : 0u;
-                a = dpp_shr_u<2>(s[j]);
-                s[j] += y >= 2 ? a : 0u;
-                a = dpp_shr_u<4>(s[j]);
-                s[j] += y >= 4 ? a : 0u;
-                // z pass: running sum over the planes of the chunk
-                s[j] += zprev[j];
-                zprev[j] = s[j];
-            }
-        } else {
-            const uint32_t xq = l >> 4;
-            // x pass over the 4 quads of the chunk row
-            const uint32_t tot = s[3];
-            uint32_t inc = tot;
-            uint32_t a = (uint32_t)__shfl_up((int)inc, 16);
-            inc += xq >= 1 ? a : 0u;
-            a = (uint32_t)__shfl_up((int)inc, 32);
-            inc += xq >= 2 ? a : 0u;
-            const uint32_t left = inc - tot;
-            // y pass: the 16 rows of a chunk are the 16 lanes of a DPP row
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                s[j] += left;
-                s[j] += dpp_shr_u<1>(s[j]);
-                s[j] += dpp_shr_u<2>(s[j]);
-                s[j] += dpp_shr_u<4>(s[j]);
-                s[j] += dpp_shr_u<8>(s[j]);
-            }
-        }
+        for (int j = 0; j < 4; ++j) s[j] += excl;
         OT v[4];
         dequant4(s, ebx2, v);
         if constexpr (VEC && sizeof(OT) == 4) {
@@ -274,27 +205,27 @@ __device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t& zeros
     }
 }
 
-// Grid-stride over the workgroup tiles of one (rank, layout) group, with the
+// 1D: grid-stride over the workgroup tiles of one layout group, with the
 // next tile's codes in flight while the current tile is reconstructed (two
 // static buffers).  Launched with one workgroup per tile, which measured
 // faster than a resident-size grid; the stride loop serves tuned grids.
-template <int RANK, bool VEC, class OT>
+template <bool VEC, class OT>
 __global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restrict__ F, int nf,
                                                         uint32_t n_tiles)
 {
     __shared__ uint32_t s_z[kWavesPerBlock];
     uint32_t t = blockIdx.x;
     if (t >= n_tiles) return;
-    RTile<RANK> A, B;
+    RTile A, B;
     int fa = find_field<&FieldDesc::wg_base>(F, nf, t), fb;
-    rtile_load<RANK, VEC>(F[fa], t - F[fa].wg_base, A);
+    rtile_load<VEC>(F[fa], t - F[fa].wg_base, A);
     int cur = -1;
     uint32_t zeros = 0;
     for (;;) {
         uint32_t tn = t + gridDim.x;
         const uint32_t tb = tn < n_tiles ? tn : t;
         fb = find_field<&FieldDesc::wg_base>(F, nf, tb);
-        if (tn < n_tiles) rtile_load<RANK, VEC>(F[fb], tb - F[fb].wg_base, B);
+        if (tn < n_tiles) rtile_load<VEC>(F[fb], tb - F[fb].wg_base, B);
         {
             const FieldDesc& fd = F[fa];
             const auto* dy = kconst(fd.dyn);
@@ -303,14 +234,14 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restr
                 cur = fa;
             }
             if (dy->status == ST_OK && dy->codec != ARC_CONST)
-                rtile_process<RANK, VEC, OT>(fd, t - fd.wg_base, A, dy->ebx2, zeros);
+                rtile_process<VEC, OT>(fd, t - fd.wg_base, A, dy->ebx2, zeros);
         }
         t = tn;
         if (t >= n_tiles) break;
         tn = t + gridDim.x;
         const uint32_t ta = tn < n_tiles ? tn : t;
         fa = find_field<&FieldDesc::wg_base>(F, nf, ta);
-        if (tn < n_tiles) rtile_load<RANK, VEC>(F[fa], ta - F[fa].wg_base, A);
+        if (tn < n_tiles) rtile_load<VEC>(F[fa], ta - F[fa].wg_base, A);
         {
             const FieldDesc& fd = F[fb];
             const auto* dy = kconst(fd.dyn);
@@ -319,7 +250,7 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restr
                 cur = fb;
             }
             if (dy->status == ST_OK && dy->codec != ARC_CONST)
-                rtile_process<RANK, VEC, OT>(fd, t - fd.wg_base, B, dy->ebx2, zeros);
+                rtile_process<VEC, OT>(fd, t - fd.wg_base, B, dy->ebx2, zeros);
         }
         t = tn;
         if (t >= n_tiles) break;
@@ -335,6 +266,109 @@ __device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b)
                                                                   __builtin_bit_cast(u16x2, b)));
 }
 __device__ __forceinline__ bool has_zero_half(uint32_t w) { return (w & 0xFFFFu) == 0 || (w >> 16) == 0; }
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+// 2D: a wave owns a tile of xs = 64 wx elements along x by 16 * 4 / wx rows; a
+// lane is a quad along x and walks the 16 rows of its chunk row, so a row of the
+// tile is one contiguous load and store, the y pass a running sum in registers
+// and the x pass a prefix over the four lanes of a 16-wide chunk.  All rows are
+// loaded at once (the kernel is bound by that round trip on fields of a few
+// million values, by traffic on larger ones).  Deltas are loaded for eight rows at
+// a time, only if some lane holds an outlier there.  With the 16 rows across the
+// lanes of a DPP row a load touched 16 rows by 32 bytes, and every outlier waited
+// for its own delta: 32 us on 1800x3600, against the 8 us that its bytes take.
+template <bool VEC, class OT>
+__global__ __launch_bounds__(kWave) void k_reconstruct2(const FieldDesc* __restrict__ F, int nf)
+{
+    const uint32_t t = blockIdx.x;
+    const int f = find_field<&FieldDesc::wg_base>(F, nf, t);
+    const FieldDesc& fd = F[f];
+    const auto* dy = kconst(fd.dyn);
+    if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
+    const uint32_t tl = t - fd.wg_base, nxb = fd.nxb;
+    const uint32_t l = lane_id(), lx = fd.xs / 4;  // lanes along x: 16, 32 or 64
+    const uint32_t nx = fd.nx, ny = fd.ny;
+    const uint32_t x0 = (tl % nxb) * fd.xs + 4 * (l & (lx - 1));
+    const uint32_t y0 = (tl / nxb * (kWave / lx) + l / lx) * 16;
+    const uint32_t nv = x0 < nx && y0 < ny ? min<uint32_t>(4, nx - x0) : 0u;
+    const uint32_t rows = nv ? min<uint32_t>(16, ny - y0) : 0u;
+    const uint64_t i0 = nv ? (uint64_t)y0 * nx + x0 : 0;
+    const EBC_G uint16_t* __restrict__ q = fd.q + i0;
+    const EBC_G int32_t* __restrict__ dsc = fd.dsc + i0;
+    EBC_G OT* __restrict__ out = field_out<OT>(fd) + i0;
+    const uint32_t r = fd.n_bins / 2;
+    const double ebx2 = dy->ebx2;
+    u32x2 raw[16];
+#pragma unroll
+    for (uint32_t y = 0; y < 16; ++y) {
+        raw[y] = u32x2{0x00010001u, 0x00010001u};  // absent codes read as 1
+        if (y < rows) {
+            if (nv == 4) {
+                if (VEC) raw[y] = ld_nt_u2(q + (uint64_t)y * nx);
+                else raw[y] = *(const EBC_G u32x2_a2*)(q + (uint64_t)y * nx);
+            } else {
+                uint32_t c[3] = {1u, 1u, 1u};
+#pragma unroll
+                for (uint32_t k = 0; k < 3; ++k)
+                    if (k < nv) c[k] = q[(uint64_t)y * nx + k];
+                raw[y] = u32x2{c[0] | (c[1] << 16), c[2] | 0x00010000u};
+            }
+        }
+    }
+    const uint32_t m1 = (l & 3) >= 1 ? ~0u : 0u, m2 = (l & 3) >= 2 ? ~0u : 0u;
+    uint32_t yprev[4] = {0, 0, 0, 0};
+    uint32_t zeros = 0;
+#pragma unroll
+    for (uint32_t h = 0; h < 16; h += 8) {
+        uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+        for (uint32_t y = h; y < h + 8; ++y) low = min_halves(low, min_halves(raw[y].x, raw[y].y));
+        const bool any = __any(has_zero_half(low));
+        u32x4 d[8];
+        if (any) {
+#pragma unroll
+            for (uint32_t y = h; y < h + 8; ++y) {
+                d[y - h] = u32x4{0u, 0u, 0u, 0u};
+                // (the workspace goes on past the field's last delta)
+                if (has_zero_half(min_halves(raw[y].x, raw[y].y)))
+                    d[y - h] = *(const EBC_G u32x4_a4*)(dsc + (uint64_t)y * nx);
+            }
+        }
+#pragma unroll
+        for (uint32_t y = h; y < h + 8; ++y) {
+            uint32_t c[4], s[4];
+            unpack4(raw[y], c);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s[k] = c[k] - r;
+            if (any) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    s[k] = c[k] == 0 ? d[y - h][k] : s[k];
+                    zeros += c[k] == 0;
+                }
+            }
+            s[1] += s[0], s[2] += s[1], s[3] += s[2];  // x pass within the quad
+            uint32_t inc = s[3];
+            inc += dpp_shr_u<1>(inc) & m1;
+            inc += dpp_shr_u<2>(inc) & m2;
+            const uint32_t left = inc - s[3];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                s[k] += left + yprev[k];  // y pass
+                yprev[k] = s[k];
+            }
+            OT v[4];
+            dequant4(s, ebx2, v);
+            if (y < rows) store_quad<VEC>(out, (uint64_t)y * nx, (int)nv, v);
+        }
+    }
+    const uint32_t zs = wave_sum_u32(zeros);
+    if (l == 0 && zs) atomicAdd(&fd.zslot[(t % kZeroSlots) * kZeroStride], zs);
+}
 
 // Chunk rows of one wave of the 3D reconstruction (see k_reconstruct3).
 // FULL: the wave's 256 x 8 x 8 block lies inside the field and its rows are
@@ -464,10 +498,6 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __rest
         if (met && fd.n_out_hdr == 0) atomicAdd(&fd.zslot[0], 1u);
     }
 }
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 
 // eight consecutive elements of a chunk row
 __device__ __forceinline__ void store_row8(EBC_G float* o, const uint32_t s[8], double ebx2)
@@ -634,11 +664,12 @@ static void reconstruct_launch(const FieldDesc* F, int nf, int rank, bool vec, u
 {
     const dim3 g(blocks), b(kBlock);
     if (rank == 1) {
-        if (vec) hipLaunchKernelGGL((k_reconstruct<1, true, OT>), g, b, 0, s, F, nf, wg_tiles);
-        else hipLaunchKernelGGL((k_reconstruct<1, false, OT>), g, b, 0, s, F, nf, wg_tiles);
+        if (vec) hipLaunchKernelGGL((k_reconstruct<true, OT>), g, b, 0, s, F, nf, wg_tiles);
+        else hipLaunchKernelGGL((k_reconstruct<false, OT>), g, b, 0, s, F, nf, wg_tiles);
     } else if (rank == 2) {
-        if (vec) hipLaunchKernelGGL((k_reconstruct<2, true, OT>), g, b, 0, s, F, nf, wg_tiles);
-        else hipLaunchKernelGGL((k_reconstruct<2, false, OT>), g, b, 0, s, F, nf, wg_tiles);
+        const dim3 g2(wg_tiles), b2(kWave);  // one wave per tile
+        if (vec) hipLaunchKernelGGL((k_reconstruct2<true, OT>), g2, b2, 0, s, F, nf);
+        else hipLaunchKernelGGL((k_reconstruct2<false, OT>), g2, b2, 0, s, F, nf);
     } else {
         const dim3 g3(wg_tiles);  // one workgroup per tile
         if (vec) hipLaunchKernelGGL((k_reconstruct3<true, OT>), g3, b, 0, s, F, nf);
