@@ -257,6 +257,27 @@ __device__ __forceinline__ uint64_t write_entry(uint64_t packed)
     return ((uint64_t)((uint32_t)packed << (32 - L)) << 32) | L;
 }
 
+// The entry of lanes with at most 16 symbols: the codeword right-aligned in the
+// high word (a longer one than 32 bits as its length only), its length below.
+__device__ __forceinline__ uint64_t join_entry(uint64_t packed)
+{
+    const uint32_t L = (uint32_t)(packed >> 56);
+    return ((uint64_t)(L <= 32 ? (uint32_t)packed : 0u) << 32) | L;
+}
+
+// OR a piece of L <= 64 bits, right-aligned in v, into the word buffer at bit b
+__device__ __forceinline__ void or_bits(uint32_t* wbuf, uint32_t b, uint64_t v, uint32_t L)
+{
+    const uint64_t x = v << ((64 - L) & 63);  // left-aligned (an empty piece is 0)
+    const uint32_t hi = (uint32_t)(x >> 32), lo = (uint32_t)x, s = b & 31;
+    uint32_t* w = wbuf + (b >> 5);
+    atomicOr(w, hi >> s);
+    if (s + L > 32) {
+        atomicOr(w + 1, __builtin_amdgcn_alignbit(hi, lo, s));
+        if (s + L > 64) atomicOr(w + 2, __builtin_amdgcn_alignbit(lo, 0u, s));
+    }
+}
+
 // append a codeword of L <= 32 bits given left-aligned in cw
 __device__ __forceinline__ void put_left(uint64_t& acc, uint32_t& nacc, uint32_t& w, uint32_t* wbuf,
                                          uint32_t cw, uint32_t L)
@@ -280,13 +301,44 @@ struct WriteProc {
     bool fits;                  // field cur's archive fits into its buffer
     EBC_G uint32_t* words;      // its sections
     EBC_G uint16_t* sbits;
+    // Lanes of up to 16 symbols keep their table entries in registers and join
+    // them by shifts before they touch the word buffer; wider lanes look them up
+    // twice and append them one by one.
+    static constexpr bool kKeep = S <= 16;
+    __device__ __forceinline__ static uint64_t make_entry(uint64_t packed)
+    {
+        return kKeep ? join_entry(packed) : write_entry(packed);
+    }
     __device__ __forceinline__ uint64_t entry(const FieldDesc& fd, const uint64_t* code_s, uint32_t sym) const
     {
-        return W ? write_entry(fd.code[sym]) : code_s[sym];
+        return W ? make_entry(fd.code[sym]) : code_s[sym];
     }
-    // up to 16 symbols per lane keep their table entries in registers between
-    // the bit count and the packing; wider lanes look them up twice
-    static constexpr bool kKeep = S <= 16;
+    // The lane's symbols as pieces of neighbours: pairs of at most 32 bits, fours
+    // and eights of at most 64.  A wave whose pieces all fit ORs one (S <= 8) or
+    // two pieces of eight per lane into its buffer, or fours where eights are too
+    // long: 7 vector instructions per symbol instead of 24 for appending the
+    // codewords one by one behind a branch (512^3: 109 to 100 us; 64M walk 41 to 31).
+    // False: a pair or a four is too long (or a codeword is).
+    __device__ __forceinline__ static bool join(const uint64_t (&e)[kKeep ? S : 1], uint64_t (&p4)[(S + 3) / 4],
+                                                uint32_t (&l4)[(S + 3) / 4], uint32_t& bits)
+    {
+        bool ok = true;
+        bits = 0;
+#pragma unroll
+        for (uint32_t g = 0; g < (S + 3) / 4; ++g) {
+            uint32_t c[4] = {0, 0, 0, 0}, L[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                if (4 * g + k < S) c[k] = (uint32_t)(e[4 * g + k] >> 32), L[k] = (uint32_t)e[4 * g + k];
+            const uint32_t la = L[0] + L[1], lb = L[2] + L[3];
+            ok = ok && max(la, lb) <= 32;
+            const uint32_t a = (c[0] << (L[1] & 31)) | c[1], b = (c[2] << (L[3] & 31)) | c[3];
+            p4[g] = ((uint64_t)a << (lb & 63)) | b;
+            l4[g] = la + lb;
+            bits += l4[g];
+        }
+        return ok;
+    }
     __device__ __forceinline__ void operator()(const EncUnit& u, const SymRaw<S>& r)
     {
         if (!u.ok) return;
@@ -307,7 +359,7 @@ struct WriteProc {
             if (!W) {
                 __syncthreads();
                 for (uint32_t s = threadIdx.x; s < nb; s += kWave * huff_cpw(64 * S))
-                    code_s[s] = write_entry(fd.code[s]);
+                    code_s[s] = make_entry(fd.code[s]);
                 __syncthreads();
             }
             cur = u.f;
@@ -320,16 +372,14 @@ struct WriteProc {
         // symbols past the stream's end take the empty entry
         const uint32_t m = live && lo < u.cnt ? (uint32_t)min<uint64_t>(S, u.cnt - lo) : 0u;
         uint64_t e[kKeep ? S : 1];
-        uint32_t mybits = 0, lmax = 0;
+        uint32_t mybits = 0;
         if (__all(m == S)) {
             // every lane holds S symbols (all chunks but a field's last)
 #pragma unroll
             for (uint32_t k = 0; k < S; ++k) {
                 const uint64_t v = entry(fd, code_s, r.at(k));
                 if (kKeep) e[kKeep ? k : 0] = v;
-                const uint32_t L = (uint32_t)v & 0xFFu;
-                mybits += L;
-                lmax = max(lmax, L);
+                else mybits += (uint32_t)v & 0xFFu;
             }
         } else {
 #pragma unroll
@@ -337,11 +387,14 @@ struct WriteProc {
                 const uint64_t v0 = entry(fd, code_s, k < m ? r.at(k) : 0u);
                 const uint64_t v = k < m ? v0 : 0ull;
                 if (kKeep) e[kKeep ? k : 0] = v;
-                const uint32_t L = (uint32_t)v & 0xFFu;
-                mybits += L;
-                lmax = max(lmax, L);
+                else mybits += (uint32_t)v & 0xFFu;
             }
         }
+        constexpr uint32_t kFours = (S + 3) / 4;
+        uint64_t p4[kFours];
+        uint32_t l4[kFours];
+        bool joined = false;
+        if constexpr (kKeep) joined = __all(join(e, p4, l4, mybits));
         for (uint32_t i = lane_id(); i < nw; i += kWave) wbuf[i] = 0;
         uint32_t sb = 0;
         if (live) {
@@ -351,29 +404,46 @@ struct WriteProc {
             // lanes of S symbols each): the scan at its last lane minus b0
             constexpr uint32_t kLps = kSubMax / S < 64 ? kSubMax / S : 64u;
             sb = (uint32_t)__shfl((int)incl, (int)min<uint32_t>(lane_id() + kLps - 1, 63)) - b0;
-            uint32_t w = b0 >> 5, nacc = b0 & 31;
-            uint64_t acc = 0;
-            if (!__any(lmax > 32)) {
+            if (joined) {
+                uint32_t b = b0;
+                uint32_t longest = 0;
+#pragma unroll
+                for (uint32_t g = 0; g + 1 < kFours; g += 2) longest = max(longest, l4[g] + l4[g + 1]);
+                if (kFours > 1 && __all(longest <= 64)) {
+#pragma unroll
+                    for (uint32_t g = 0; g < kFours; g += 2) {
+                        const uint32_t g1 = g + 1 < kFours ? g + 1 : g;
+                        const uint32_t L = l4[g] + l4[g1];
+                        // (a second four of 64 bits leaves none for the first)
+                        const uint64_t v = (l4[g1] < 64 ? p4[g] << (l4[g1] & 63) : 0ull) | p4[g1];
+                        or_bits(wbuf, b, v, L);
+                        b += L;
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t g = 0; g < kFours; ++g) {
+                        or_bits(wbuf, b, p4[g], l4[g]);
+                        b += l4[g];
+                    }
+                }
+            } else {
+                uint32_t w = b0 >> 5, nacc = b0 & 31;
+                uint64_t acc = 0;
 #pragma unroll
                 for (uint32_t k = 0; k < S; ++k) {
                     const uint64_t v = kKeep ? e[kKeep ? k : 0] : (k < m ? entry(fd, code_s, r.at(k)) : 0ull);
-                    put_left(acc, nacc, w, wbuf, (uint32_t)(v >> 32), (uint32_t)v & 0xFFu);
-                }
-            } else {  // a codeword longer than 32 bits somewhere in the chunk
-#pragma unroll
-                for (uint32_t k = 0; k < S; ++k) {
-                    const uint64_t v = k < m ? entry(fd, code_s, r.at(k)) : 0ull;
                     const uint32_t L = (uint32_t)v & 0xFFu;
                     if (L <= 32) {
-                        put_left(acc, nacc, w, wbuf, (uint32_t)(v >> 32), L);
+                        const uint32_t c = (uint32_t)(v >> 32);
+                        put_left(acc, nacc, w, wbuf, kKeep ? (L ? c << (32 - L) : 0u) : c, L);
                     } else {
                         const uint64_t cw = fd.code[r.at(k)] & ((1ull << 56) - 1);
                         put_bits(acc, nacc, w, wbuf, cw >> 32, L - 32);
                         put_bits(acc, nacc, w, wbuf, cw & 0xFFFFFFFFull, 32);
                     }
                 }
+                if (nacc) atomicOr(&wbuf[w], (uint32_t)(acc >> 32));
             }
-            if (nacc) atomicOr(&wbuf[w], (uint32_t)(acc >> 32));
         }
         if (live) {
             const auto* wk = (const __attribute__((address_space(4))) uint32_t*)woff;
