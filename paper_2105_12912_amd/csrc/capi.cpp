@@ -246,7 +246,8 @@ struct Batch {
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
-    uint32_t dec_lanes = 0, dec_groups = 0;  // decompress: lanes and 64-sub-chunk groups per decode workgroup
+    // decompress: sub-chunks per wave of a decode workgroup, its lanes, its groups of sub-chunks
+    uint32_t dec_per_wave = 0, dec_lanes = 0, dec_groups = 0;
     EstDev* d_est = nullptr;
     uint64_t ws_bytes = 0;
 };
@@ -705,10 +706,10 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         sub{0, ov}, hpwg{0, ov};
     // symbols of a Huffman stream: the N codes, or the run values of RLE+VLE
     auto stream = [&](int i) { return din[i].H.codec == EBC_ARC_RLE_VLE ? din[i].H.n_a : geo[i].n; };
-    uint64_t all_grp = 0;
+    uint64_t all_sub = 0;
     for (int i = 0; i < B.nf; ++i)
-        if (huff_codec(din[i].H.codec)) all_grp += cdiv(stream(i), (uint64_t)geo[i].hs * kWave);
-    huff_decode_split(all_grp, &B.dec_lanes, &B.dec_groups);
+        if (huff_codec(din[i].H.codec)) all_sub += (uint64_t)kWave * cdiv(stream(i), (uint64_t)geo[i].hs * kWave);
+    huff_decode_split(all_sub, &B.dec_per_wave, &B.dec_lanes, &B.dec_groups);
     for (int k = 0; k < B.nf; ++k) {
         const DecompressIn& D = din[B.order[k]];
         const Header& H = D.H;
@@ -722,7 +723,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         // word offsets: an entry of its own behind each field's chunks
         d.n_hch = huff ? cdiv(hm, H.hc) : 0, d.hch_base = hch.add(d.n_hch + 1);
         d.n_sub = huff ? cdiv(hm, g.hs) : 0, d.sub_base = sub.add(d.n_sub);
-        d.hdwg_units = cdiv(cdiv(d.n_sub, kWave), B.dec_groups), d.hdwg_base = hdwg.add(d.hdwg_units);
+        d.hdwg_units = cdiv(cdiv(d.n_sub, B.dec_per_wave), B.dec_groups), d.hdwg_base = hdwg.add(d.hdwg_units);
         d.hpwg_units = cdiv(d.n_hch, 1024), d.hpwg_base = hpwg.add(d.hpwg_units);
         d.n_rt = rle ? g.n_rt : 0, d.rt_base = rt.add(d.n_rt);
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
@@ -854,7 +855,8 @@ int enqueue_decompress(Batch& B, hipStream_t s, Timer& T, int32_t* status)
         HIP_TRY(launch_dec_prep(B.d_fd, nf, B.tot_hpwg, direct, B.d_tabs, B.tab_stride, B.d_wcnt, B.d_soff, s));
         if (!direct) HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
         T.mark("huffman_decode");
-        HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.dec_lanes, B.d_wcnt, B.d_soff, B.d_tabs, B.tab_stride, s));
+        HIP_TRY(launch_huff_decode(B.d_fd, nf, B.tot_hdwg, B.dec_per_wave, B.dec_lanes, B.d_wcnt, B.d_soff, B.d_tabs,
+                                   B.tab_stride, s));
     }
     if (B.tot_runs) {
         T.mark("rle_decode");

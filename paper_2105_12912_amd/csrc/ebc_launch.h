@@ -55,8 +55,8 @@ hipError_t launch_encode_count(const FieldDesc* F, int nf, uint32_t units, uint3
                                uint32_t* wcnt, int which, uint32_t rt_units, uint32_t* rcnt, hipStream_t s);
 hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_t hc, uint32_t n_bins,
                              const uint32_t* soff, const uint32_t* woff, const uint32_t* roff, hipStream_t s);
-void huff_decode_split(uint64_t n_grp, uint32_t* lanes, uint32_t* groups);
-hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t lanes,
+void huff_decode_split(uint64_t n_sub, uint32_t* per_wave, uint32_t* lanes, uint32_t* groups);
+hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t per_wave, uint32_t lanes,
                               const uint32_t* woff, const uint32_t* soff, const uint8_t* tabs,
                               size_t tab_stride, hipStream_t s);
 

@@ -704,7 +704,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #endif
 
 // One lane per sub-chunk (hs = min(hc, 256) symbols, its bit count and its
-// start from the archive's sub-chunk counts), blockDim.x lanes per workgroup.
+// start from the archive's sub-chunk counts), blockDim.x lanes per workgroup,
+// of which each wave's first per_wave ones work.
 // The decoded stream is the field's quant-codes, or its run values (RLE+VLE).
 //
 // The loop runs groups of kSteps table steps.  A group starts with the 64-bit
@@ -723,20 +724,21 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Codewords longer than 32 bits leave for an exact path that reads windows
 // straight from the stream.  Flushed blocks are stored non-temporally: they
 // are not read before the kernel ends, and kept in the L2 they push out the
-// stream's lines, each of which a lane comes back to eight times (209 us
-// against 185 us on the 512^3 field).
+// stream's lines, each of which a lane comes back to eight times (195 us
+// against 173 us on the 512^3 field).
 //
 // With the former step (bit buffer topped up from an LDS ring, exact clipping
 // and both table levels in every step: about 60 vector instructions) a wave
 // needed 900 cycles per step by itself and the kernel 257-290 us on a 512^3
-// field at 3.8 bits per symbol, 82 us on 256x256; now 185 and 59 us.  What
+// field at 3.8 bits per symbol, 82 us on 256x256; now 172 and 50 us.  What
 // bounds it now is latency: a wave waits half of its time (table reads that
 // depend on each other, stream blocks), and the LDS rows allow 16 waves per CU.
 // Three, four or five steps per group make no difference on the large field.
 __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restrict__ F, int nf,
                                                       const uint32_t* __restrict__ woff,
                                                       const uint32_t* __restrict__ soff,
-                                                      const uint8_t* __restrict__ tabs, size_t tab_stride)
+                                                      const uint8_t* __restrict__ tabs, size_t tab_stride,
+                                                      uint32_t per_wave)
 {
     extern __shared__ uint64_t lds64[];
     DecLds& sm = *(DecLds*)lds64;
@@ -788,19 +790,19 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
         return u32x4{EBC_LDS(const u32_lds, a), EBC_LDS(const u32_lds, a + 4), EBC_LDS(const u32_lds, a + 8),
                      EBC_LDS(const u32_lds, a + 12)};
     };
-    // The field's groups of 64 sub-chunks go to its workgroups in turn (so that
+    // The field's groups of per_wave sub-chunks go to its workgroups in turn (so that
     // each has a mix of dense and sparse parts), and a workgroup's waves take
     // its groups as they finish: waves differ by a factor of three in steps.
-    const uint32_t n_grp = (fd.n_sub + kWave - 1) / kWave;
+    const uint32_t n_grp = (fd.n_sub + per_wave - 1) / per_wave;
     for (;;) {
         uint32_t gi = 0;
         if (lane == 0) gi = atomicAdd(&sm.next, 1u);
         gi = __builtin_amdgcn_readfirstlane(gi);
         const uint32_t g = gi * fd.hdwg_units + (t - fd.hdwg_base);
         if (gi >= n_grp || g >= n_grp) break;
-        const uint32_t sub0 = g * kWave;
+        const uint32_t sub0 = g * per_wave;
         const uint32_t sub = sub0 + lane;
-        const bool live = sub < fd.n_sub;
+        const bool live = lane < per_wave && sub < fd.n_sub;
         const uint32_t c = live ? sub / per : 0;
         const uint32_t nbits = live ? ((const EBC_G uint16_t*)(arc + fd.off_sbits))[sub] : 0u;
         // start bit of the sub-chunk inside the field's word stream
@@ -1033,28 +1035,33 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
     return hipGetLastError();
 }
 
-// Decode workgroups of a call whose streams make n_grp groups of 64
-// sub-chunks: lanes per workgroup, and groups that a workgroup takes.  The
-// tables take 42 KB of LDS per workgroup and a lane 116 bytes, so a CU holds
-// one workgroup of 1024 lanes (16 waves), two of 256 or three of 64.  A call
-// that leaves CUs idle with wide workgroups is split finer; a large one gets
-// one workgroup per CU, so that the tables are loaded once and the waves even
-// out.
-void huff_decode_split(uint64_t n_grp, uint32_t* lanes, uint32_t* groups)
+// Decode workgroups of a call whose streams make n_sub sub-chunks: sub-chunks per
+// wave, lanes per workgroup, and waves' worth of work that a workgroup takes.  The
+// tables take 42 KB of LDS per workgroup and a lane 116 bytes, so a CU holds one
+// workgroup of 1024 lanes (16 waves) or two of 256.  A large call gets one
+// workgroup per CU, so that the tables are loaded once and the waves even out.  A
+// call of up to two workgroups of 256 lanes per CU is split over all of them, with
+// half of each wave's lanes idle: four waves load the tables, and a wave waits for
+// the slowest of 32 lanes only (one wave of 64 per workgroup: 256x256 55 us, here
+// 50; 1800x3600 44 and 40; 1501x2999 with 16384 bins 87 and 81).  16 sub-chunks per
+// wave gain nothing more on those, 8 lose once the workgroups do not fit at once
+// (1800x3600: 58 us).
+void huff_decode_split(uint64_t n_sub, uint32_t* per_wave, uint32_t* lanes, uint32_t* groups)
 {
     constexpr uint32_t kCus = 256;
-    if (n_grp <= 3 * kCus) *lanes = 64, *groups = 1;
-    else if (n_grp <= 2 * kCus * 4) *lanes = 256, *groups = 4;
+    *per_wave = n_sub <= 32 * 4 * 2 * kCus ? 32 : 64;
+    const uint64_t n_grp = (n_sub + *per_wave - 1) / *per_wave;
+    if (n_grp <= 2 * kCus * 4) *lanes = 256, *groups = 4;
     else *lanes = 1024, *groups = n_grp <= kCus * 16 ? 16 : (uint32_t)((n_grp + kCus - 1) / kCus);
 }
 
-hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t lanes,
+hipError_t launch_huff_decode(const FieldDesc* F, int nf, uint32_t units, uint32_t per_wave, uint32_t lanes,
                               const uint32_t* woff, const uint32_t* soff, const uint8_t* tabs,
                               size_t tab_stride, hipStream_t s)
 {
     if (!units) return hipSuccess;
     hipLaunchKernelGGL(k_huff_decode, dim3(units), dim3(lanes), huff_decode_lds_bytes(lanes), s, F, nf, woff,
-                       soff, tabs, tab_stride);
+                       soff, tabs, tab_stride, per_wave);
     return hipGetLastError();
 }
 

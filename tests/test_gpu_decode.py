@@ -58,3 +58,10 @@ def test_workgroup_sizes(E, groups, kind):
 
 def test_many_bins(E):
     check(E, walk(300_003, "flat", 3), 1024, n_bins=65536)
+
+
+@pytest.mark.parametrize("kind", ["flat", "long"])
+@pytest.mark.parametrize("subs", [31, 32, 33, 127, 129, 65_536, 65_537])
+def test_half_waves(E, subs, kind):
+    # up to 65536 sub-chunks, 32 to a wave and 128 to a workgroup; sub-chunks of 64
+    check(E, walk(subs * 64 - 5, kind, subs), 64)
