@@ -246,6 +246,7 @@ struct Batch {
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
+    bool rle_1d = false, rle_nd = false;  // decompress: run-length coded fields of rank 1, of rank 2 or 3
     // decompress: sub-chunks per wave of a decode workgroup, its lanes, its groups of sub-chunks
     uint32_t dec_per_wave = 0, dec_lanes = 0, dec_groups = 0;
     EstDev* d_est = nullptr;
@@ -726,6 +727,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.hdwg_units = cdiv(cdiv(d.n_sub, B.dec_per_wave), B.dec_groups), d.hdwg_base = hdwg.add(d.hdwg_units);
         d.hpwg_units = cdiv(d.n_hch, 1024), d.hpwg_base = hpwg.add(d.hpwg_units);
         d.n_rt = rle ? g.n_rt : 0, d.rt_base = rt.add(d.n_rt);
+        if (rle) (H.rank == 1 ? B.rle_1d : B.rle_nd) = true;
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
         d.rl_units = cdiv(d.n_runs_hdr, kBlock), d.rl_base = rl.add(d.rl_units);
         d.sc_units = cst ? 0 : cdiv(H.n_out, kBlock), d.sc_base = sc.add(d.sc_units);
@@ -750,7 +752,8 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         for (int k = G.first; k < G.first + G.count; ++k) {
             FieldDesc& d = B.fd[k];
             const Geo& g = geo[B.order[k]];
-            uint32_t wt = d.codec_hdr == EBC_ARC_CONST ? 0 : g.wg_tiles;
+            // (1D run-length coded fields are reconstructed by their RLE tiles)
+            uint32_t wt = d.codec_hdr == EBC_ARC_CONST || (G.rank == 1 && rle_codec(d.codec_hdr)) ? 0 : g.wg_tiles;
             if (G.rank == 3 && wt) {
                 uint32_t t3[3];
                 recon3_tiles(g, t3);
@@ -801,7 +804,8 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.off_sbits = H.off_sbits, d.off_words = H.off_words, d.off_val = H.off_val;
         d.off_rlen = H.off_rlen, d.off_oidx = H.off_oidx, d.off_oval = H.off_oval;
         const bool cst = H.codec == EBC_ARC_CONST;
-        d.q = bp.take<uint16_t>(cst ? 0 : 2 * g.n);
+        const bool codes = !cst && !(g.rank == 1 && rle_codec(H.codec));  // kept in memory
+        d.q = bp.take<uint16_t>(codes ? 2 * g.n : 0);
         d.dsc = bp.take<int32_t>(cst ? 0 : 4 * g.n);
         // RLE+VLE: the decoded run values feed the run expansion
         d.vsym = bp.take<uint16_t>(H.codec == EBC_ARC_RLE_VLE ? 2 * H.n_a : 0);
@@ -824,7 +828,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
 // deltas itself.
 int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
 {
-    bool has3 = false, has12 = false;
+    bool has3 = false, has12 = B.rle_1d;
     for (const auto& G : B.groups) (G.rank == 3 ? has3 : has12) |= G.wg_tiles > 0;
     if (has3) T.mark("reconstruct");
     for (const auto& G : B.groups)
@@ -832,12 +836,13 @@ int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
             HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles,
                                        G.blocks, s));
     if (B.tot_sc) T.mark("outlier_scatter");
-    HIP_TRY(launch_outlier_scatter(B.d_fd, B.nf, B.tot_sc, s));
+    HIP_TRY(launch_outlier_scatter(B.d_fd, B.nf, B.tot_sc, B.d_starts, B.d_tmap, s));
     if (has12) T.mark(has3 ? "reconstruct_12" : "reconstruct");
     for (const auto& G : B.groups)
         if (G.rank != 3)
             HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles,
                                        G.blocks, s));
+    if (B.rle_1d) HIP_TRY(launch_rle_reconstruct(B.d_fd, B.nf, B.tot_rt, B.d_starts, B.d_tmap, s));
     if (B.tot_fx) T.mark("outlier_fix");
     HIP_TRY(launch_recon_fix(B.d_fd, B.nf, B.tot_fx, s));
     return EBC_OK;
@@ -860,7 +865,8 @@ int enqueue_decompress(Batch& B, hipStream_t s, Timer& T, int32_t* status)
     }
     if (B.tot_runs) {
         T.mark("rle_decode");
-        HIP_TRY(launch_rle_decode(B.d_fd, nf, B.tot_rl, B.tot_rt, B.d_starts, B.d_tmap, B.d_tmp, B.tot_runs, B.scan, s));
+        HIP_TRY(launch_rle_decode(B.d_fd, nf, B.tot_rl, B.tot_rt, B.d_starts, B.d_tmap, B.d_tmp, B.tot_runs, B.scan,
+                                  B.rle_nd, s));
     }
     const int st = enqueue_reconstruct(B, s, T);
     if (st) return st;

@@ -67,7 +67,9 @@ hipError_t launch_rle_vle_prep(const FieldDesc* F, int nf, uint32_t units, const
                                uint32_t n_bins, hipStream_t s);
 hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint32_t rt_units,
                              uint32_t* starts, uint32_t* tmap, uint32_t* tmp, uint32_t n_starts,
-                             uint32_t scan_direct, hipStream_t s);
+                             uint32_t scan_direct, bool expand, hipStream_t s);
+hipError_t launch_rle_reconstruct(const FieldDesc* F, int nf, uint32_t rt_units, const uint32_t* starts,
+                                  const uint32_t* tmap, hipStream_t s);
 
 // outliers
 uint32_t outlier_write_segs(uint32_t n_seg);
@@ -77,7 +79,8 @@ hipError_t launch_outlier_write(const FieldDesc* F, int nf, uint32_t units, cons
 // NULL), runs of run-length fields (rt_units tiles, if any) and outlier lists
 hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t ow_units, const uint32_t* soff,
                          const uint32_t* woff, const uint32_t* roff, uint64_t* res, hipStream_t s);
-hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
+hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, const uint32_t* starts,
+                                  const uint32_t* tmap, hipStream_t s);
 
 // reconstruction
 hipError_t launch_reconstruct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,

@@ -10,6 +10,7 @@
 // a group of lanes.  Decompression scatters the list into a
 // dense delta scratch and validates it against the codes.
 #include "encode_dev.h"
+#include "rle_dev.h"
 #include "ebc_launch.h"
 
 namespace ebc {
@@ -319,7 +320,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(const FieldDesc* __restrict__
 
 // ------------------------------------------------------------- decoding
 // one thread per listed outlier: index in range, strictly ascending, code 0
-__global__ __launch_bounds__(kBlock) void k_outlier_scatter(const FieldDesc* __restrict__ F, int nf)
+// (the code of a 1D run-length coded field is looked up among its tile's runs)
+__global__ __launch_bounds__(kBlock) void k_outlier_scatter(const FieldDesc* __restrict__ F, int nf,
+                                                            const uint32_t* __restrict__ starts,
+                                                            const uint32_t* __restrict__ tmap)
 {
     const uint32_t t = blockIdx.x;
     const int f = find_field<&FieldDesc::sc_base>(F, nf, t);
@@ -332,7 +336,10 @@ __global__ __launch_bounds__(kBlock) void k_outlier_scatter(const FieldDesc* __r
     const EBC_G int32_t* oval = (const EBC_G int32_t*)(fd.arc + fd.off_oval);
     const uint32_t i = oidx[k];
     bool bad = i >= fd.n || (k > 0 && oidx[k - 1] >= i);
-    if (!bad) bad = fd.q[i] != 0;
+    if (!bad) {
+        if (fd.rank == 1 && rle_codec(fd.codec_hdr)) bad = run_value(fd, i, starts, tmap) != 0;
+        else bad = fd.q[i] != 0;
+    }
     if (bad) {
         atomicMin(&dy->status, ST_ERR_ARCHIVE);
         return;
@@ -358,10 +365,11 @@ hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t
     return hipGetLastError();
 }
 
-hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, hipStream_t s)
+hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, const uint32_t* starts,
+                                  const uint32_t* tmap, hipStream_t s)
 {
     if (!units) return hipSuccess;
-    hipLaunchKernelGGL(k_outlier_scatter, dim3(units), dim3(kBlock), 0, s, F, nf);
+    hipLaunchKernelGGL(k_outlier_scatter, dim3(units), dim3(kBlock), 0, s, F, nf, starts, tmap);
     return hipGetLastError();
 }
 

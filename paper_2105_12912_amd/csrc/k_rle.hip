@@ -8,6 +8,7 @@
 // lengths into starts and expands each output tile from the runs that overlap
 // it.
 #include "encode_dev.h"
+#include "rle_dev.h"
 #include "ebc_launch.h"
 
 namespace ebc {
@@ -102,7 +103,8 @@ __global__ __launch_bounds__(kBlock) void k_rle_prep(const FieldDesc* __restrict
 // and the number of runs it overlaps, so that every tile's searches are in
 // flight at once rather than one thread per workgroup searching while the
 // others wait.  The searches stay inside the run array whatever it holds.
-// tmap[2t] = first run, tmap[2t + 1] = run count.
+// tmap[2t] = first run, or the run's value if it is the only one; tmap[2t + 1] =
+// run count.
 __global__ __launch_bounds__(kBlock) void k_rle_map(const FieldDesc* __restrict__ F, int nf, uint32_t rl_units,
                                                     uint32_t rt_units, const uint32_t* __restrict__ starts,
                                                     uint32_t* __restrict__ tmap)
@@ -142,79 +144,37 @@ __global__ __launch_bounds__(kBlock) void k_rle_map(const FieldDesc* __restrict_
         if ((uint64_t)(S[m] - s0) <= hi - 1) c = m;
         else d = m - 1;
     }
-    tmap[2 * t] = a;
+    tmap[2 * t] = c == a ? fd.rval[a] : a;
     tmap[2 * t + 1] = c - a + 1;
 }
 
-// runs of one tile staged in LDS by the expansion (a tile with more runs
-// searches them in HBM)
-constexpr uint32_t kRleStage = 1024;
-
-// The kRleItems codes from element i0 on: the run holding i0 by binary search
-// over the tile's nr run starts (relative to the field), then a forward walk.
-template <class START, class VAL>
-__device__ __forceinline__ void expand_codes(uint64_t i0, uint32_t nr, uint16_t c[kRleItems], START start,
-                                             VAL value)
-{
-    uint32_t a = 0, b = nr - 1;
-    while (a < b) {
-        const uint32_t m = (a + b + 1) >> 1;
-        if ((uint64_t)start(m) <= i0) a = m;
-        else b = m - 1;
-    }
-#pragma unroll
-    for (int k = 0; k < kRleItems; ++k) {
-        const uint64_t i = i0 + k;
-        while (a + 1 < nr && (uint64_t)start(a + 1) <= i) ++a;
-        c[k] = value(a);
-    }
-}
-
+// Expansion of 2D and 3D fields into the code array (1D fields are reconstructed
+// from their runs, see k_rle_reconstruct).
 __global__ __launch_bounds__(kBlock) void k_rle_expand(const FieldDesc* __restrict__ F, int nf,
                                                        const uint32_t* __restrict__ starts,
                                                        const uint32_t* __restrict__ tmap)
 {
-    __shared__ uint32_t s_start[kRleStage];
-    __shared__ uint16_t s_val[kRleStage];
+    __shared__ RleStage sm;
     const uint32_t t = blockIdx.x;
     const int f = find_field<&FieldDesc::rt_base>(F, nf, t);
     const FieldDesc& fd = F[f];
-    EBC_G FieldDyn* dy = fd.dyn;
-    if (dy->status != ST_OK || !rle_codec(fd.codec_hdr)) return;
-    const uint32_t* S = starts + fd.rle_base;
-    const uint32_t s0 = S[0];
-    const uint64_t lo = (uint64_t)(t - fd.rt_base) * kRleTile;
-    const uint64_t hi = min(lo + (uint64_t)kRleTile, fd.n);
-    const uint32_t rlo = tmap[2 * t], nr = tmap[2 * t + 1];  // nr <= kRleTile: runs are non-empty
-    const EBC_G uint16_t* val = fd.rval;
-    const bool staged = nr <= kRleStage;  // uniform over the workgroup
-    if (staged) {
-        for (uint32_t i = threadIdx.x; i < nr; i += kBlock) {
-            s_start[i] = S[rlo + i] - s0;
-            s_val[i] = val[rlo + i];
-        }
-    }
-    __syncthreads();
-    const uint64_t i0 = lo + (uint64_t)threadIdx.x * kRleItems;
-    if (i0 >= hi) return;
+    if (fd.dyn->status != ST_OK || !rle_codec(fd.codec_hdr) || fd.rank == 1) return;
     uint16_t c[kRleItems];
-    if (staged)
-        expand_codes(i0, nr, c, [&](uint32_t k) { return s_start[k]; }, [&](uint32_t k) { return s_val[k]; });
-    else
-        expand_codes(i0, nr, c, [&](uint32_t k) { return S[rlo + k] - s0; },
-                     [&](uint32_t k) { return (uint16_t)val[rlo + k]; });
+    const uint64_t i0 = (uint64_t)(t - fd.rt_base) * kRleTile + (uint64_t)threadIdx.x * kRleItems;
+    const uint32_t rlo = tmap[2 * t], nr = tmap[2 * t + 1];
+    if (nr == 1) {  // rlo is the value
+#pragma unroll
+        for (int k = 0; k < kRleItems; ++k) c[k] = (uint16_t)rlo;
+    } else {
+        expand_tile(fd, t, rlo, nr, starts, sm, c);
+    }
     EBC_G uint16_t* __restrict__ q = fd.q;
-    if (i0 + kRleItems <= hi) {
-        uint4 x, y;
-        x.x = c[0] | ((uint32_t)c[1] << 16), x.y = c[2] | ((uint32_t)c[3] << 16);
-        x.z = c[4] | ((uint32_t)c[5] << 16), x.w = c[6] | ((uint32_t)c[7] << 16);
-        y.x = c[8] | ((uint32_t)c[9] << 16), y.y = c[10] | ((uint32_t)c[11] << 16);
-        y.z = c[12] | ((uint32_t)c[13] << 16), y.w = c[14] | ((uint32_t)c[15] << 16);
-        *(EBC_G uint4*)(q + i0) = x;
-        *(EBC_G uint4*)(q + i0 + 8) = y;
+    if (i0 + kRleItems <= fd.n) {
+        *(EBC_G uint4*)(q + i0) = pack8(c);
+        *(EBC_G uint4*)(q + i0 + 8) = pack8(c + 8);
     } else {
         for (int k = 0; k < kRleItems; ++k)
-            if (i0 + k < hi) q[i0 + k] = c[k];
+            if (i0 + k < fd.n) q[i0 + k] = c[k];
     }
 }
 
@@ -240,7 +200,7 @@ hipError_t launch_rle_vle_prep(const FieldDesc* F, int nf, uint32_t units, const
 
 hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint32_t rt_units,
                              uint32_t* starts, uint32_t* tmap, uint32_t* tmp, uint32_t n_starts,
-                             uint32_t scan_direct, hipStream_t s)
+                             uint32_t scan_direct, bool expand, hipStream_t s)
 {
     if (!rl_units) return hipSuccess;
     hipLaunchKernelGGL(k_rle_prep, dim3(rl_units), dim3(kBlock), 0, s, F, nf, starts);
@@ -248,7 +208,8 @@ hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_rle_map, dim3(rl_units + (rt_units + kBlock - 1) / kBlock), dim3(kBlock), 0, s, F, nf,
                        rl_units, rt_units, starts, tmap);
-    if (rt_units) hipLaunchKernelGGL(k_rle_expand, dim3(rt_units), dim3(kBlock), 0, s, F, nf, starts, tmap);
+    if (rt_units && expand)
+        hipLaunchKernelGGL(k_rle_expand, dim3(rt_units), dim3(kBlock), 0, s, F, nf, starts, tmap);
     return hipGetLastError();
 }
 
