@@ -438,7 +438,6 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
         d.code = bp.take<uint64_t>(8ull * P.n_bins);
         d.len = bp.take<uint8_t>(P.n_bins);
         d.cbs = P.n_bins > kMaxBins ? bp.take<uint8_t>(codebook_wide_scratch_bytes(P.n_bins)) : nullptr;
-        d.hbits = bp.take<uint32_t>(4ull * g.n_hch);
         // RLE+VLE requested: the run values (at most N, and the encoder may
         // read 30 bytes past the stream) and their histogram
         d.vsym = vle ? bp.take<uint16_t>(2 * g.n + 64) : nullptr;

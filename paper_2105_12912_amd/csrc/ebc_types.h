@@ -125,7 +125,6 @@ struct FieldDesc {
     EBC_G uint64_t* code;    // n_bins packed codewords: (len << 56) | code
     EBC_G uint8_t* len;      // n_bins code lengths
     EBC_G uint8_t* cbs;      // wide bins: codebook scratch (codebook_wide_scratch_bytes)
-    EBC_G uint32_t* hbits;   // per Huffman chunk bit counts
     EBC_G uint16_t* rflag;   // RLE compress: a run-start bit per code (or NULL), in the place of hpart
     EBC_G uint32_t* rfirst;  // RLE compress: first run start per tile, in the place of rpart
     EBC_G uint16_t* vsym;    // RLE+VLE: run values (compress: source of the Huffman pass;

@@ -20,13 +20,17 @@
 namespace ebc {
 
 
+// words of a wave's buffer in the write pass: 32 bits per symbol of a chunk (a
+// chunk of more is packed in place, in memory: that takes a field of some 1e8
+// elements, most of one code); the passes of chunks longer than kPassHc keep room
+// for 64
+__host__ __device__ constexpr uint32_t huff_buf_words(uint32_t hc) { return hc <= kPassHc ? hc + 2 : 2 * kPassHc; }
+
 size_t huff_write_lds_bytes(uint32_t n_bins, uint32_t hc)
 {
-    // code table (none for wide bins, whose table stays in HBM), then per
-    // wave a word buffer of 2 * hc words (one pass of kPassHc symbols for
-    // longer chunks)
-    const uint32_t span = hc <= kPassHc ? hc : kPassHc;
-    return (size_t)(n_bins > kMaxBins ? 0 : n_bins) * 8 + (size_t)huff_cpw(hc) * 2 * span * 4;
+    // code table (none for wide bins, whose table stays in HBM), then the word
+    // buffers
+    return (size_t)(n_bins > kMaxBins ? 0 : n_bins) * 8 + (size_t)huff_cpw(hc) * huff_buf_words(hc) * 4;
 }
 
 // The writer's table entry for symbol s (see write_entry), for wide bins
@@ -69,38 +73,48 @@ __device__ __forceinline__ void load_raw(const EBC_G uint16_t* __restrict__ q, u
     }
 }
 
-// One encode work unit: huff_cpw(hc) chunks, one per wavefront.  The coded
-// stream is a field's quant-codes (Huffman codec) or its run values (RLE+VLE
-// codec, as many as the run count found on the device); `which` selects the
-// codecs a launch covers: 0 Huffman, 1 RLE+VLE, 2 both.
-struct EncUnit {
+// The coded stream of a field: its quant-codes (Huffman codec) or its run values
+// (RLE+VLE codec, as many as the run count found on the device); `which` selects
+// the codecs a launch covers: 0 Huffman, 1 RLE+VLE, 2 both.  A workgroup keeps
+// it while it stays in the field's work units [lo, hi): looked up for every
+// unit, the chain of scalar loads through descriptor and device scalars was
+// most of a unit's time.
+struct EncField {
     int f;
-    uint32_t c;                      // this wave's chunk
+    uint32_t lo, hi;
     bool ok;                         // field is being Huffman-coded by this launch
     const EBC_G uint16_t* src;       // symbols of the stream
     uint64_t cnt;                    // symbols in the stream
     uint32_t nch, nsub;              // its chunks and sub-chunks
+    uint32_t hch;                    // its first entry among the word counts
 };
 
-template <uint32_t S>
-__device__ __forceinline__ EncUnit enc_unit(const FieldDesc* __restrict__ F, int nf, uint32_t t, int which)
+__device__ __forceinline__ EncField enc_field(const FieldDesc* __restrict__ F, int nf, uint32_t t, int which)
 {
-    EncUnit u;
-    u.f = find_field<&FieldDesc::hwg_base>(F, nf, t);
-    const FieldDesc& fd = F[u.f];
+    EncField e;
+    e.f = find_field<&FieldDesc::hwg_base>(F, nf, t);
+    const FieldDesc& fd = F[e.f];
     const auto* dk = kconst(fd.dyn);
     const int32_t codec = dk->codec;
-    u.ok = dk->status == ST_OK &&
+    e.lo = fd.hwg_base, e.hi = fd.hwg_base + fd.hwg_units;
+    e.ok = dk->status == ST_OK &&
            (which == 0 ? codec == ARC_HUFFMAN : which == 1 ? codec == ARC_RLE_VLE : huff_codec(codec));
     const bool vle = codec == ARC_RLE_VLE;
-    u.src = vle ? fd.vsym : fd.q;
-    u.cnt = vle ? dk->n_runs : fd.n;
-    u.nch = vle ? (uint32_t)((u.cnt + fd.hc - 1) / fd.hc) : fd.n_hch;
-    u.nsub = vle ? (uint32_t)((u.cnt + fd.hs - 1) / fd.hs) : fd.n_sub;
-    // blockDim = 64 * cpw; the chunk index is wave-uniform (scalar)
-    u.c = (t - fd.hwg_base) * huff_cpw(64 * S) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    return u;
+    e.src = vle ? fd.vsym : fd.q;
+    e.cnt = vle ? dk->n_runs : fd.n;
+    e.nch = vle ? (uint32_t)((e.cnt + fd.hc - 1) / fd.hc) : fd.n_hch;
+    e.nsub = vle ? (uint32_t)((e.cnt + fd.hs - 1) / fd.hs) : fd.n_sub;
+    e.hch = fd.hch_base;
+    return e;
 }
+
+// One encode work unit: huff_cpw(hc) chunks, one per wavefront.
+struct EncUnit {
+    EncField e;
+    uint32_t c;   // this wave's chunk
+    uint32_t wo;  // its scanned word offset (write pass)
+    bool ok;
+};
 
 // The first unit from t on, in this workgroup's stride, that the launch codes;
 // the units of a field that it does not code (or past a short value stream)
@@ -108,16 +122,20 @@ __device__ __forceinline__ EncUnit enc_unit(const FieldDesc* __restrict__ F, int
 // stream of whatever unit it held or passed last).
 template <uint32_t S>
 __device__ __forceinline__ uint32_t enc_seek(const FieldDesc* __restrict__ F, int nf, uint32_t t, uint32_t units,
-                                             int which, EncUnit& u)
+                                             int which, const uint32_t* __restrict__ woff, EncUnit& u)
 {
+    constexpr uint32_t kCpw = huff_cpw(64 * S);
     u.ok = false;
     while (t < units) {
-        u = enc_unit<S>(F, nf, t, which);
-        const FieldDesc& fd = F[u.f];
-        if (u.ok && (t - fd.hwg_base) * huff_cpw(64 * S) < u.nch) return t;
-        u.ok = false;
-        const uint32_t end = fd.hwg_base + fd.hwg_units;
-        t += ((end - t + gridDim.x - 1) / gridDim.x) * gridDim.x;
+        if (t < u.e.lo || t >= u.e.hi) u.e = enc_field(F, nf, t, which);
+        if (u.e.ok && (t - u.e.lo) * kCpw < u.e.nch) {
+            // blockDim = 64 * cpw; the chunk index is wave-uniform (scalar)
+            u.c = (t - u.e.lo) * kCpw + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+            if (woff) u.wo = kcount(woff, (uint64_t)u.e.hch + min(u.c, u.e.nch - 1));
+            u.ok = true;
+            return t;
+        }
+        t += ((u.e.hi - t + gridDim.x - 1) / gridDim.x) * gridDim.x;
     }
     return t;
 }
@@ -129,42 +147,42 @@ __device__ __forceinline__ uint32_t enc_seek(const FieldDesc* __restrict__ F, in
 // tail chunk's last lane may read up to 30 bytes past the stream, which the
 // workspace always follows with other scratch.
 template <uint32_t S>
-__device__ __forceinline__ void enc_issue(const FieldDesc* __restrict__ F, const EncUnit& u, SymRaw<S>& r)
+__device__ __forceinline__ void enc_issue(const EncUnit& u, SymRaw<S>& r)
 {
-    const FieldDesc& fd = F[u.f];
-    const uint64_t lo = (uint64_t)u.c * fd.hc + (uint64_t)lane_id() * S;
-    const bool live = u.ok && u.c < u.nch && lo < u.cnt;
+    const uint64_t lo = (uint64_t)u.c * (64 * S) + (uint64_t)lane_id() * S;
+    const bool live = u.ok && u.c < u.e.nch && lo < u.e.cnt;
     if (S >= 8) {
-        const EBC_G uint16_t* p = u.src + (live ? lo : 0);
+        const EBC_G uint16_t* p = u.e.src + (live ? lo : 0);
 #pragma unroll
         for (uint32_t k = 0; k < SymRaw<S>::NV; ++k) r.v[k] = *(const EBC_G uint4*)(p + 8 * k);
     } else if (live) {
-        load_raw<S>(u.src, lo, u.cnt, r);
+        load_raw<S>(u.e.src, lo, u.e.cnt, r);
     }
 }
 
 // Grid-stride walk over the work units with the next unit's symbols in
 // flight while the current one is processed (two static buffers, so no
 // register copy ever waits on a load).  proc(unit, symbols) must treat the
-// workgroup uniformly (it may synchronise).
+// workgroup uniformly (it may synchronise).  woff: scanned word offsets, or NULL.
 template <uint32_t S, class Proc>
 __device__ __forceinline__ void enc_pipeline(const FieldDesc* __restrict__ F, int nf, uint32_t units,
-                                             int which, Proc& proc)
+                                             int which, const uint32_t* __restrict__ woff, Proc& proc)
 {
     SymRaw<S> A, B;
-    EncUnit ua = {};
-    uint32_t t = enc_seek<S>(F, nf, blockIdx.x, units, which, ua);
+    EncUnit ua;
+    ua.e.lo = ua.e.hi = 0, ua.wo = 0;
+    uint32_t t = enc_seek<S>(F, nf, blockIdx.x, units, which, woff, ua);
     if (t >= units) return;
     EncUnit ub = ua;  // a dead unit still names a stream that can be read
-    enc_issue<S>(F, ua, A);
+    enc_issue<S>(ua, A);
     for (;;) {
         // the next stage's loads are always issued (a dead unit past the end)
-        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, ub);
-        enc_issue<S>(F, ub, B);
+        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, woff, ub);
+        enc_issue<S>(ub, B);
         proc(ua, A);
         if (t >= units) break;
-        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, ua);
-        enc_issue<S>(F, ua, A);
+        t = enc_seek<S>(F, nf, t + gridDim.x, units, which, woff, ua);
+        enc_issue<S>(ua, A);
         proc(ub, B);
         if (t >= units) break;
     }
@@ -180,38 +198,39 @@ struct BitsProc {
     uint32_t* wcnt;
     uint8_t* len_s;
     int cur;
+    const EBC_G uint8_t* len;
     __device__ __forceinline__ void operator()(const EncUnit& u, const SymRaw<S>& r)
     {
         if (!u.ok) return;
-        const FieldDesc& fd = F[u.f];
-        if (!W && u.f != cur) {
-            __syncthreads();
-            for (uint32_t s = threadIdx.x; s < fd.n_bins; s += kWave * huff_cpw(64 * S)) len_s[s] = fd.len[s];
-            __syncthreads();
-            cur = u.f;
+        if (u.e.f != cur) {
+            const FieldDesc& fd = F[u.e.f];
+            len = fd.len;
+            if (!W) {
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < fd.n_bins; s += kWave * huff_cpw(64 * S)) len_s[s] = len[s];
+                __syncthreads();
+            }
+            cur = u.e.f;
         }
-        if (u.c >= u.nch) return;
-        const uint64_t lo = (uint64_t)u.c * fd.hc + (uint64_t)lane_id() * S;
+        if (u.c >= u.e.nch) return;
+        const uint64_t lo = (uint64_t)u.c * (64 * S) + (uint64_t)lane_id() * S;
         // symbols past the stream's end count zero bits; every lookup is
         // issued before any is used
-        const uint32_t m = lo < u.cnt ? (uint32_t)min<uint64_t>(S, u.cnt - lo) : 0u;
+        const uint32_t m = lo < u.e.cnt ? (uint32_t)min<uint64_t>(S, u.e.cnt - lo) : 0u;
         uint32_t bits = 0;
         if (__all(m == S)) {
             // every lane holds S symbols (all chunks but a field's last)
 #pragma unroll
-            for (uint32_t k = 0; k < S; ++k) bits += W ? fd.len[r.at(k)] : len_s[r.at(k)];
+            for (uint32_t k = 0; k < S; ++k) bits += W ? len[r.at(k)] : len_s[r.at(k)];
         } else {
 #pragma unroll
             for (uint32_t k = 0; k < S; ++k) {
-                const uint32_t L = W ? fd.len[k < m ? r.at(k) : 0u] : len_s[k < m ? r.at(k) : 0u];
+                const uint32_t L = W ? len[k < m ? r.at(k) : 0u] : len_s[k < m ? r.at(k) : 0u];
                 bits += k < m ? L : 0u;
             }
         }
         bits = wave_sum_u32(bits);
-        if (lane_id() == 0) {
-            fd.hbits[u.c] = bits;
-            wcnt[fd.hch_base + u.c] = (bits + 31) / 32;
-        }
+        if (lane_id() == 0) wcnt[u.e.hch + u.c] = (bits + 31) / 32;
     }
 };
 
@@ -227,8 +246,8 @@ __global__ __launch_bounds__(kBlock) void k_huff_bits(const FieldDesc* __restric
     __shared__ uint8_t len_s[W ? 1 : kMaxBins];
     __shared__ RleShared sh;
     if (rt_units) rle_count_tiles(F, nf, rcnt, rt_units, sh);
-    BitsProc<S, W> proc{F, wcnt, len_s, -1};
-    enc_pipeline<S>(F, nf, units, which, proc);
+    BitsProc<S, W> proc{F, wcnt, len_s, -1, nullptr};
+    enc_pipeline<S>(F, nf, units, which, nullptr, proc);
 }
 
 // append the low `take` (<= 32) bits of v to a window that starts on a word
@@ -278,6 +297,17 @@ __device__ __forceinline__ void or_bits(uint32_t* wbuf, uint32_t b, uint64_t v, 
     }
 }
 
+// OR a codeword of 1 <= L <= 56 bits into words in memory at bit b
+__device__ __forceinline__ void or_long(EBC_G uint32_t* w, uint32_t b, uint64_t cw, uint32_t L)
+{
+    const uint64_t x = cw << (64 - L);
+    const uint32_t hi = (uint32_t)(x >> 32), lo = (uint32_t)x, s = b & 31;
+    w += b >> 5;
+    atomicOr((uint32_t*)w, hi >> s);
+    if (s + L > 32) atomicOr((uint32_t*)w + 1, __builtin_amdgcn_alignbit(hi, lo, s));
+    if (s + L > 64) atomicOr((uint32_t*)w + 2, __builtin_amdgcn_alignbit(lo, 0u, s));
+}
+
 // append a codeword of L <= 32 bits given left-aligned in cw
 __device__ __forceinline__ void put_left(uint64_t& acc, uint32_t& nacc, uint32_t& w, uint32_t* wbuf,
                                          uint32_t cw, uint32_t L)
@@ -299,8 +329,10 @@ struct WriteProc {
     uint64_t* lds64;
     int cur;
     bool fits;                  // field cur's archive fits into its buffer
-    EBC_G uint32_t* words;      // its sections
+    EBC_G uint32_t* words;      // its sections (words: from word offset 0 of the batch on)
     EBC_G uint16_t* sbits;
+    const EBC_G uint64_t* code;
+    uint32_t tab;               // entries of the LDS code table
     // Lanes of up to 16 symbols keep their table entries in registers and join
     // them by shifts before they touch the word buffer; wider lanes look them up
     // twice and append them one by one.
@@ -309,9 +341,9 @@ struct WriteProc {
     {
         return kKeep ? join_entry(packed) : write_entry(packed);
     }
-    __device__ __forceinline__ uint64_t entry(const FieldDesc& fd, const uint64_t* code_s, uint32_t sym) const
+    __device__ __forceinline__ uint64_t entry(const uint64_t* code_s, uint32_t sym) const
     {
-        return W ? make_entry(fd.code[sym]) : code_s[sym];
+        return W ? make_entry(code[sym]) : code_s[sym];
     }
     // The lane's symbols as pieces of neighbours: pairs of at most 32 bits, fours
     // and eights of at most 64.  A wave whose pieces all fit ORs one (S <= 8) or
@@ -342,49 +374,47 @@ struct WriteProc {
     __device__ __forceinline__ void operator()(const EncUnit& u, const SymRaw<S>& r)
     {
         if (!u.ok) return;
-        const FieldDesc& fd = F[u.f];
-        const auto* dy = kconst(fd.dyn);
-        const uint32_t nb = fd.n_bins, hc = fd.hc;
+        constexpr uint32_t hc = 64 * S, hs = hc < kSubMax ? hc : kSubMax;
         uint64_t* code_s = lds64;
+        if (u.e.f != cur) {
+            const FieldDesc& fd = F[u.e.f];
+            const Layout y = layout_of(fd, kconst(fd.dyn)->codec, soff, woff, roff);
+            fits = y.total <= fd.arc_cap;
+            words = (EBC_G uint32_t*)(fd.arc + y.off_words) - kcount(woff, u.e.hch);
+            sbits = (EBC_G uint16_t*)(fd.arc + y.off_sbits);
+            code = fd.code;
+            tab = W ? 0u : fd.n_bins;
+            if (!W) {
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < tab; s += kWave * huff_cpw(hc)) code_s[s] = make_entry(code[s]);
+                __syncthreads();
+            }
+            cur = u.e.f;
+        }
+        if (!fits) return;
         // Each wave packs its chunk in a word buffer of its own, and a wave's
         // LDS accesses complete in order, so clearing, packing and copying
         // out need no barrier; only a new field's code table (shared by the
         // workgroup, whose waves all work on one field) does.
-        uint32_t* wbuf = (uint32_t*)(lds64 + (W ? 0 : nb)) + (threadIdx.x / kWave) * 2 * hc;
-        if (u.f != cur) {
-            const Layout y = layout_of(fd, dy->codec, soff, woff, roff);
-            fits = y.total <= fd.arc_cap;
-            words = (EBC_G uint32_t*)(fd.arc + y.off_words);
-            sbits = (EBC_G uint16_t*)(fd.arc + y.off_sbits);
-            if (!W) {
-                __syncthreads();
-                for (uint32_t s = threadIdx.x; s < nb; s += kWave * huff_cpw(64 * S))
-                    code_s[s] = make_entry(fd.code[s]);
-                __syncthreads();
-            }
-            cur = u.f;
-        }
-        if (!fits) return;
-        const bool live = u.c < u.nch;
-        const uint32_t cbits = live ? kconst(fd.hbits)[u.c] : 0u;
-        const uint32_t nw = (cbits + 31) / 32;
+        uint32_t* wbuf = (uint32_t*)(lds64 + tab) + (threadIdx.x / kWave) * huff_buf_words(hc);
+        const bool live = u.c < u.e.nch;
         const uint64_t lo = (uint64_t)u.c * hc + (uint64_t)lane_id() * S;
         // symbols past the stream's end take the empty entry
-        const uint32_t m = live && lo < u.cnt ? (uint32_t)min<uint64_t>(S, u.cnt - lo) : 0u;
+        const uint32_t m = live && lo < u.e.cnt ? (uint32_t)min<uint64_t>(S, u.e.cnt - lo) : 0u;
         uint64_t e[kKeep ? S : 1];
         uint32_t mybits = 0;
         if (__all(m == S)) {
             // every lane holds S symbols (all chunks but a field's last)
 #pragma unroll
             for (uint32_t k = 0; k < S; ++k) {
-                const uint64_t v = entry(fd, code_s, r.at(k));
+                const uint64_t v = entry(code_s, r.at(k));
                 if (kKeep) e[kKeep ? k : 0] = v;
                 else mybits += (uint32_t)v & 0xFFu;
             }
         } else {
 #pragma unroll
             for (uint32_t k = 0; k < S; ++k) {
-                const uint64_t v0 = entry(fd, code_s, k < m ? r.at(k) : 0u);
+                const uint64_t v0 = entry(code_s, k < m ? r.at(k) : 0u);
                 const uint64_t v = k < m ? v0 : 0ull;
                 if (kKeep) e[kKeep ? k : 0] = v;
                 else mybits += (uint32_t)v & 0xFFu;
@@ -395,72 +425,82 @@ struct WriteProc {
         uint32_t l4[kFours];
         bool joined = false;
         if constexpr (kKeep) joined = __all(join(e, p4, l4, mybits));
+        if (!live) return;
+        const uint32_t incl = wave_incl_scan_u32(mybits);
+        const uint32_t b0 = incl - mybits;
+        const uint32_t nw = ((uint32_t)__builtin_amdgcn_readlane((int)incl, 63) + 31) / 32;  // the chunk's words
+        EBC_G uint32_t* dst = words + u.wo;
+        // sub-chunk bit counts (u16): one per kSubMax symbols of the chunk, or
+        // one for the whole chunk when it is shorter; a sub-chunk's count is
+        // the scan at its last lane minus b0 at its first
+        constexpr uint32_t kLps = kSubMax / S < 64 ? kSubMax / S : 64u;
+        const uint32_t sb = (uint32_t)__shfl((int)incl, (int)min<uint32_t>(lane_id() + kLps - 1, 63)) - b0;
+        const uint64_t sub = (uint64_t)u.c * (hc / hs) + lane_id() / kLps;
+        if (lane_id() % kLps == 0 && lo < u.e.cnt && sub < u.e.nsub) sbits[sub] = (uint16_t)sb;
+        if (__builtin_expect(nw > hc, 0)) {
+            // more than 32 bits per symbol: packed in place
+            for (uint32_t i = lane_id(); i < nw; i += kWave) dst[i] = 0;
+            __threadfence();
+            uint32_t b = b0;
+            for (uint32_t k = 0; k < m; ++k) {
+                const uint64_t cw = code[u.e.src[lo + k]];
+                const uint32_t L = (uint32_t)(cw >> 56);
+                or_long(dst, b, cw & ((1ull << 56) - 1), L);
+                b += L;
+            }
+            return;
+        }
         for (uint32_t i = lane_id(); i < nw; i += kWave) wbuf[i] = 0;
-        uint32_t sb = 0;
-        if (live) {
-            const uint32_t incl = wave_incl_scan_u32(mybits);
-            const uint32_t b0 = incl - mybits;
-            // bit count of the sub-chunk that starts at this lane (lanes_per_sub
-            // lanes of S symbols each): the scan at its last lane minus b0
-            constexpr uint32_t kLps = kSubMax / S < 64 ? kSubMax / S : 64u;
-            sb = (uint32_t)__shfl((int)incl, (int)min<uint32_t>(lane_id() + kLps - 1, 63)) - b0;
-            if (joined) {
-                uint32_t b = b0;
-                uint32_t longest = 0;
+        if (joined) {
+            uint32_t b = b0;
+            uint32_t longest = 0;
 #pragma unroll
-                for (uint32_t g = 0; g + 1 < kFours; g += 2) longest = max(longest, l4[g] + l4[g + 1]);
-                if (kFours > 1 && __all(longest <= 64)) {
+            for (uint32_t g = 0; g + 1 < kFours; g += 2) longest = max(longest, l4[g] + l4[g + 1]);
+            if (kFours > 1 && __all(longest <= 64)) {
 #pragma unroll
-                    for (uint32_t g = 0; g < kFours; g += 2) {
-                        const uint32_t g1 = g + 1 < kFours ? g + 1 : g;
-                        const uint32_t L = l4[g] + l4[g1];
-                        // (a second four of 64 bits leaves none for the first)
-                        const uint64_t v = (l4[g1] < 64 ? p4[g] << (l4[g1] & 63) : 0ull) | p4[g1];
-                        or_bits(wbuf, b, v, L);
-                        b += L;
-                    }
-                } else {
-#pragma unroll
-                    for (uint32_t g = 0; g < kFours; ++g) {
-                        or_bits(wbuf, b, p4[g], l4[g]);
-                        b += l4[g];
-                    }
+                for (uint32_t g = 0; g < kFours; g += 2) {
+                    const uint32_t g1 = g + 1 < kFours ? g + 1 : g;
+                    const uint32_t L = l4[g] + l4[g1];
+                    // (a second four of 64 bits leaves none for the first)
+                    const uint64_t v = (l4[g1] < 64 ? p4[g] << (l4[g1] & 63) : 0ull) | p4[g1];
+                    or_bits(wbuf, b, v, L);
+                    b += L;
                 }
             } else {
-                uint32_t w = b0 >> 5, nacc = b0 & 31;
-                uint64_t acc = 0;
 #pragma unroll
-                for (uint32_t k = 0; k < S; ++k) {
-                    const uint64_t v = kKeep ? e[kKeep ? k : 0] : (k < m ? entry(fd, code_s, r.at(k)) : 0ull);
-                    const uint32_t L = (uint32_t)v & 0xFFu;
-                    if (L <= 32) {
-                        const uint32_t c = (uint32_t)(v >> 32);
-                        put_left(acc, nacc, w, wbuf, kKeep ? (L ? c << (32 - L) : 0u) : c, L);
-                    } else {
-                        const uint64_t cw = fd.code[r.at(k)] & ((1ull << 56) - 1);
-                        put_bits(acc, nacc, w, wbuf, cw >> 32, L - 32);
-                        put_bits(acc, nacc, w, wbuf, cw & 0xFFFFFFFFull, 32);
-                    }
+                for (uint32_t g = 0; g < kFours; ++g) {
+                    or_bits(wbuf, b, p4[g], l4[g]);
+                    b += l4[g];
                 }
-                if (nacc) atomicOr(&wbuf[w], (uint32_t)(acc >> 32));
             }
+        } else {
+            uint32_t w = b0 >> 5, nacc = b0 & 31;
+            uint64_t acc = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < S; ++k) {
+                const uint64_t v = kKeep ? e[kKeep ? k : 0] : (k < m ? entry(code_s, r.at(k)) : 0ull);
+                const uint32_t L = (uint32_t)v & 0xFFu;
+                if (L <= 32) {
+                    const uint32_t c = (uint32_t)(v >> 32);
+                    put_left(acc, nacc, w, wbuf, kKeep ? (L ? c << (32 - L) : 0u) : c, L);
+                } else {
+                    const uint64_t cw = code[r.at(k)] & ((1ull << 56) - 1);
+                    put_bits(acc, nacc, w, wbuf, cw >> 32, L - 32);
+                    put_bits(acc, nacc, w, wbuf, cw & 0xFFFFFFFFull, 32);
+                }
+            }
+            if (nacc) atomicOr(&wbuf[w], (uint32_t)(acc >> 32));
         }
-        if (live) {
-            const auto* wk = (const __attribute__((address_space(4))) uint32_t*)woff;
-            const uint32_t wo = wk[fd.hch_base + u.c] - wk[fd.hch_base];
-            EBC_G uint32_t* dst = words + wo;
-            for (uint32_t i = lane_id(); i < nw; i += kWave) dst[i] = wbuf[i];
-            // sub-chunk bit counts (u16): one per kSubMax symbols of the
-            // chunk, or one for the whole chunk when it is shorter
-            constexpr uint32_t kLps = kSubMax / S < 64 ? kSubMax / S : 64u;
-            const uint32_t hs = fd.hs;
-            const uint64_t sub = (uint64_t)u.c * (hc / hs) + lane_id() / kLps;
-            if (lane_id() % kLps == 0 && lo < u.cnt && sub < u.nsub)
-                sbits[sub] = (uint16_t)sb;
-        }
+        for (uint32_t i = lane_id(); i < nw; i += kWave) dst[i] = wbuf[i];
     }
 };
 
+// A wave looks up its chunk's codewords, packs them in LDS and copies the words out.
+// Bound by latency (table and word buffer in LDS, an atomic OR per piece) at 20
+// waves per CU; 25 KB of LDS per workgroup of 1024 bins and the field's pointers kept
+// from unit to unit gave 100 -> 88 us on 512^3 against 40 KB and a walk through the
+// descriptors for every unit, the fifth workgroup per CU 80 us (two bytes per symbol
+// read at the copy rate: 52).  64M walk 30 -> 23, batch of 16 fields 67 -> 58.
 template <uint32_t S, bool W>
 __global__ __launch_bounds__(kBlock) void k_huff_write(const FieldDesc* __restrict__ F, int nf,
                                                        const uint32_t* __restrict__ soff,
@@ -468,8 +508,8 @@ __global__ __launch_bounds__(kBlock) void k_huff_write(const FieldDesc* __restri
                                                        const uint32_t* __restrict__ roff, uint32_t units)
 {
     extern __shared__ uint64_t lds64[];
-    WriteProc<S, W> proc{F, soff, woff, roff, lds64, -1, false, nullptr, nullptr};
-    enc_pipeline<S>(F, nf, units, 2, proc);
+    WriteProc<S, W> proc{F, soff, woff, roff, lds64, -1, false, nullptr, nullptr, nullptr, 0};
+    enc_pipeline<S>(F, nf, units, 2, woff, proc);
 }
 
 // ------------------------------------------------ chunks longer than kPassHc
@@ -482,7 +522,22 @@ __global__ __launch_bounds__(kBlock) void k_huff_write(const FieldDesc* __restri
 constexpr uint32_t kPassPerLane = kPassHc / kWave;  // 64 symbols
 static_assert(kSubMax % kPassPerLane == 0, "a sub-chunk is a whole number of lanes");
 
-__device__ __forceinline__ void load_pass(const EncUnit& u, uint64_t lo, uint32_t sym[kPassPerLane])
+// a work unit: one chunk
+struct LongUnit {
+    int f;
+    uint32_t c;
+    bool ok;
+    const EBC_G uint16_t* src;
+    uint64_t cnt;
+    uint32_t nch;
+};
+__device__ __forceinline__ LongUnit long_unit(const FieldDesc* __restrict__ F, int nf, uint32_t t, int which)
+{
+    const EncField e = enc_field(F, nf, t, which);
+    return LongUnit{e.f, t - e.lo, e.ok, e.src, e.cnt, e.nch};
+}
+
+__device__ __forceinline__ void load_pass(const LongUnit& u, uint64_t lo, uint32_t sym[kPassPerLane])
 {
     const uint64_t i0 = lo + (uint64_t)lane_id() * kPassPerLane;
     if (i0 + kPassPerLane <= u.cnt) {
@@ -507,7 +562,7 @@ __global__ __launch_bounds__(kWave) void k_huff_bits_long(const FieldDesc* __res
     __shared__ uint8_t len_s[W ? 1 : kMaxBins];
     int cur = -1;
     for (uint32_t t = blockIdx.x; t < units; t += gridDim.x) {
-        const EncUnit u = enc_unit<kPassPerLane>(F, nf, t, which);
+        const LongUnit u = long_unit(F, nf, t, which);
         if (!u.ok) continue;
         const FieldDesc& fd = F[u.f];
         if (!W && u.f != cur) {
@@ -528,7 +583,6 @@ __global__ __launch_bounds__(kWave) void k_huff_bits_long(const FieldDesc* __res
             bits += wave_sum_u32(b);
         }
         if (lane_id() == 0) {
-            fd.hbits[u.c] = (uint32_t)bits;
             wcnt[fd.hch_base + u.c] = (uint32_t)((bits + 31) / 32);
         }
     }
@@ -544,7 +598,7 @@ __global__ __launch_bounds__(kWave) void k_huff_write_long(const FieldDesc* __re
     extern __shared__ uint64_t lds64[];
     int cur = -1;
     for (uint32_t t = blockIdx.x; t < units; t += gridDim.x) {
-        const EncUnit u = enc_unit<kPassPerLane>(F, nf, t, 2);
+        const LongUnit u = long_unit(F, nf, t, 2);
         if (!u.ok) continue;
         const FieldDesc& fd = F[u.f];
         const auto* dy = kconst(fd.dyn);
@@ -982,6 +1036,8 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     default: return hipErrorInvalidValue;                                                   \
     }
 
+constexpr uint32_t kCus = 256;
+
 // persistent grid: enough workgroups to fill the device several times over
 static uint32_t persistent_grid(uint32_t units) { return units < kPersistentBlocks ? units : kPersistentBlocks; }
 
@@ -1019,8 +1075,12 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
 {
     if (!units) return hipSuccess;
     const bool wide = n_bins > kMaxBins;
-    const dim3 g(persistent_grid(units));
     const size_t sh = huff_write_lds_bytes(n_bins, hc);
+    // The short-chunk kernels' registers allow five workgroups per CU: with up to
+    // five workgroups' tables and buffers in a CU's LDS the grid is as many (512^3:
+    // 80 us, with four 88, with eight and thus a second, partial round 86).
+    const bool five = hc <= 1024 && 5 * sh <= 160u * 1024;
+    const dim3 g(min(units, five ? 5 * kCus : kPersistentBlocks));
     if (hc > kPassHc) {
         if (wide) hipLaunchKernelGGL(k_huff_write_long<true>, g, dim3(kWave), sh, s, F, nf, soff, woff, roff, units);
         else hipLaunchKernelGGL(k_huff_write_long<false>, g, dim3(kWave), sh, s, F, nf, soff, woff, roff, units);
@@ -1048,7 +1108,6 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
 // (1800x3600: 58 us).
 void huff_decode_split(uint64_t n_sub, uint32_t* per_wave, uint32_t* lanes, uint32_t* groups)
 {
-    constexpr uint32_t kCus = 256;
     *per_wave = n_sub <= 32 * 4 * 2 * kCus ? 32 : 64;
     const uint64_t n_grp = (n_sub + *per_wave - 1) / *per_wave;
     if (n_grp <= 2 * kCus * 4) *lanes = 256, *groups = 4;
