@@ -582,98 +582,111 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __rest
     }
 }
 
-// eight consecutive elements of a chunk row
-__device__ __forceinline__ void store_row8(EBC_G float* o, const uint32_t s[8], double ebx2)
-{
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (float)((double)(int32_t)s[e] * ebx2);
-    *(EBC_G f32x4_a4*)o = f32x4{v[0], v[1], v[2], v[3]};
-    *(EBC_G f32x4_a4*)(o + 4) = f32x4{v[4], v[5], v[6], v[7]};
-}
-__device__ __forceinline__ void store_row8(EBC_G double* o, const uint32_t s[8], double ebx2)
-{
-#pragma unroll
-    for (int e = 0; e < 8; e += 2)
-        *(EBC_G f64x2_a8*)(o + e) = f64x2{(double)(int32_t)s[e] * ebx2, (double)(int32_t)s[e + 1] * ebx2};
-}
-
 // One wave's share of the fix-up: the flagged ones of eight 8x8x8 chunks along
-// x.  Lane (z, chunk) = (l % 8, l / 8) owns the rows of 8 x of one plane of
-// its chunk and walks y: the x pass is in-lane, the y pass a running sum, the
-// z pass a scan over the 8 lanes of a chunk.  All codes and deltas are loaded
-// before any is used (the kernel is bound by that one round trip when few
-// chunks are flagged, by the traffic when many are).  Returns the lane's
-// outlier count.
+// x.  Lane (g, xq) = (l / 16, l % 16) owns a quad along x of the planes 2g and
+// 2g + 1, so a row of the wave's 64 x is one contiguous piece of memory, and walks
+// y: the x pass is in-lane plus the total of the pair lane, the y pass a running
+// sum, the z pass a sum of the lane's two planes and a scan over the four g.  All
+// codes and deltas are loaded before any is used, behind one branch.  Bound by the
+// memory pipeline: with a lane per row of 8 x, each access of a wave touched 64
+// places (fp64 field of 100x500x500, nearly every chunk flagged: 114 us, now 81;
+// with a branch per row 86, and 29 instead of 18 us where few chunks are flagged).
+// Returns the lane's outlier count.
 template <class OT>
 __device__ __forceinline__ uint32_t fix_wave(const FieldDesc& fd, bool flagged, uint32_t x0, uint32_t y0,
                                              uint32_t z0, double ebx2)
 {
     const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    const uint32_t zl = lane_id() & 7, zz = z0 + zl;
-    const uint32_t nv = flagged && zz < nz && x0 < nx ? min<uint32_t>(8, nx - x0) : 0u;
+    const uint32_t g = lane_id() >> 4, zz = z0 + 2 * g;
+    const int nv = flagged && x0 < nx ? (int)min<uint32_t>(4, nx - x0) : 0;
     const uint32_t r = fd.n_bins / 2;
     const EBC_G uint16_t* __restrict__ q = fd.q;
     const EBC_G int32_t* __restrict__ dsc = fd.dsc;
     EBC_G OT* __restrict__ out = field_out<OT>(fd);
-    const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0;
-    u32x4 c[8], da[8], db[8];
+    const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0, plane = (uint64_t)ny * nx;
+    const bool full = nv == 4 && zz + 1 < nz;
+    const int nvz[2] = {zz < nz ? nv : 0, zz + 1 < nz ? nv : 0};
+    u32x2 c[2][8];
+    u32x4 d[2][8];
 #pragma unroll
     for (uint32_t y = 0; y < 8; ++y) {
-        c[y] = u32x4{0x00010001u, 0x00010001u, 0x00010001u, 0x00010001u};
-        da[y] = db[y] = u32x4{0u, 0u, 0u, 0u};
-        if (y0 + y >= ny) continue;  // uniform
-        const uint64_t i = i0 + (uint64_t)y * nx;
-        if (nv == 8) {
-            c[y] = *(const EBC_G u32x4_a2*)(q + i);
-            da[y] = *(const EBC_G u32x4_a4*)(dsc + i);
-            db[y] = *(const EBC_G u32x4_a4*)(dsc + i + 4);
-        } else {
-            // the field's last, partial chunk along x
-            for (uint32_t e = 0; e < nv; ++e) {
-                const uint32_t sh = 16 * (e & 1), cv = q[i + e], dv = (uint32_t)dsc[i + e];
 #pragma unroll
-                for (uint32_t k = 0; k < 8; ++k)
-                    if (k == e) {
-                        c[y][k / 2] = (c[y][k / 2] & ~(0xFFFFu << sh)) | (cv << sh);
-                        if (k < 4) da[y][k & 3] = dv;
-                        else db[y][k & 3] = dv;
-                    }
+        for (int p = 0; p < 2; ++p) {
+            c[p][y] = u32x2{0x00010001u, 0x00010001u};
+            d[p][y] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    if (full) {
+#pragma unroll
+        for (uint32_t y = 0; y < 8; ++y) {
+            if (y0 + y >= ny) break;  // uniform
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                c[p][y] = *(const EBC_G u32x2_a2*)(q + i0 + p * plane + (uint64_t)y * nx);
+                d[p][y] = *(const EBC_G u32x4_a4*)(dsc + i0 + p * plane + (uint64_t)y * nx);
+            }
+        }
+    } else if (nvz[0] > 0) {
+        // the field's last, partial quad along x, or its last plane
+#pragma unroll
+        for (uint32_t y = 0; y < 8; ++y) {
+            if (y0 + y >= ny) break;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint64_t i = i0 + p * plane + (uint64_t)y * nx;
+                uint32_t e[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    e[k] = k < nvz[p] ? q[i + k] : 1u;
+                    d[p][y][k] = k < nvz[p] ? (uint32_t)dsc[i + k] : 0u;
+                }
+                c[p][y] = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
             }
         }
     }
-    uint32_t yprev[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t yprev[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     uint32_t zeros = 0;
-    const uint32_t m1 = zl >= 1 ? ~0u : 0u, m2 = zl >= 2 ? ~0u : 0u, m4 = zl >= 4 ? ~0u : 0u;
+    const uint32_t odd = lane_id() & 1 ? ~0u : 0u, g1 = g & 1 ? ~0u : 0u, g2 = g & 2 ? ~0u : 0u;
 #pragma unroll
     for (uint32_t y = 0; y < 8; ++y) {
         if (y0 + y >= ny) continue;  // uniform
-        uint32_t s[8];
+        uint32_t s[2][4];
 #pragma unroll
-        for (uint32_t e = 0; e < 8; ++e) {
-            const uint32_t cv = (c[y][e / 2] >> (16 * (e & 1))) & 0xFFFFu;
-            const uint32_t dv = e < 4 ? da[y][e & 3] : db[y][e & 3];
-            zeros += cv == 0;
-            s[e] = cv == 0 ? dv : cv - r;
+        for (int p = 0; p < 2; ++p) {
+            uint32_t cv[4];
+            unpack4(c[p][y], cv);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                zeros += cv[k] == 0;
+                s[p][k] = cv[k] == 0 ? d[p][y][k] : cv[k] - r;
+            }
+            s[p][1] += s[p][0], s[p][2] += s[p][1], s[p][3] += s[p][2];  // x pass within the quad
+            const uint32_t left = dpp_shr_u<1>(s[p][3]) & odd;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                s[p][k] += left + yprev[p][k];  // y pass
+                yprev[p][k] = s[p][k];
+            }
         }
 #pragma unroll
-        for (int e = 1; e < 8; ++e) s[e] += s[e - 1];  // x pass
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            s[e] += yprev[e];  // y pass
-            yprev[e] = s[e];
-            // z pass: inclusive scan over the chunk's 8 lanes
-            s[e] += dpp_shr_u<1>(s[e]) & m1;
-            s[e] += dpp_shr_u<2>(s[e]) & m2;
-            s[e] += dpp_shr_u<4>(s[e]) & m4;
+        for (int k = 0; k < 4; ++k) {
+            s[1][k] += s[0][k];
+            // z pass: the totals of the lanes with a lower g
+            const auto t = __builtin_amdgcn_permlane16_swap(s[1][k], s[1][k], false, false);
+            const uint32_t both = t[0] + t[1];
+            const uint32_t below = (t[0] & g1) + (__builtin_amdgcn_permlane32_swap(both, both, false, false)[0] & g2);
+            s[0][k] += below, s[1][k] += below;
         }
         const uint64_t i = i0 + (uint64_t)y * nx;
-        if (nv == 8) {
-            store_row8(out + i, s, ebx2);
-        } else {
-#pragma unroll
-            for (uint32_t e = 0; e < 8; ++e)
-                if (e < nv) out[i + e] = (OT)((double)(int32_t)s[e] * ebx2);
+        OT v[2][4];
+        dequant4(s[0], ebx2, v[0]);
+        dequant4(s[1], ebx2, v[1]);
+        if (full) {
+            store_quad<false>(out, i, 4, v[0]);
+            store_quad<false>(out, i + plane, 4, v[1]);
+        } else if (nvz[0] > 0) {
+            store_quad<false>(out, i, nvz[0], v[0]);
+            store_quad<false>(out, i + plane, nvz[1], v[1]);
         }
     }
     return zeros;
@@ -698,9 +711,9 @@ __global__ __launch_bounds__(kBlock) void k_recon3_fix(const FieldDesc* __restri
     if (bits == 0) return;
     const uint32_t nxb = fd.nxb, nyw = fd.nyb * kWavesPerBlock;
     const uint32_t xb = b % nxb, yw = (b / nxb) % nyw, zb = b / (nxb * nyw);
-    const uint32_t ch = lane_id() >> 3;
-    const bool flagged = ((bits >> (2 * ch)) & 3u) != 0;
-    const uint32_t x0 = xb * 256 + w * 64 + ch * 8;
+    const uint32_t xq = lane_id() & 15;
+    const bool flagged = ((bits >> (xq & 14u)) & 3u) != 0;  // either lane of the chunk's pair
+    const uint32_t x0 = xb * 256 + w * 64 + xq * 4;
     const uint32_t zeros = fd.dtype == 1 ? fix_wave<double>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2)
                                          : fix_wave<float>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2);
     const uint32_t zs = wave_sum_u32(zeros);
