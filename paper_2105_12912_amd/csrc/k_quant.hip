@@ -92,6 +92,8 @@ __device__ __forceinline__ double key_double(uint64_t k)
     return __longlong_as_double((long long)b);
 }
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
 __global__ __launch_bounds__(kBlock) void k_range64(const FieldDesc* __restrict__ F, int nf)
 {
     const uint32_t u = blockIdx.x;
@@ -102,16 +104,25 @@ __global__ __launch_bounds__(kBlock) void k_range64(const FieldDesc* __restrict_
     const EBC_G double* __restrict__ in = fd.in64;
     uint64_t kmin = ~0ull, kmax = 0ull;
     uint32_t bad = 0u;
-    for (uint64_t i = lo + 2u * threadIdx.x; i < hi; i += 2u * kBlock) {
-        for (int k = 0; k < 2; ++k) {
-            if (i + k < hi) {
-                const double v = in[i + k];
-                bad |= !isfinite(v);
-                const uint64_t key = double_key(v);
-                kmin = min(kmin, key);
-                kmax = max(kmax, key);
-            }
+    auto take = [&](double v) {
+        bad |= !isfinite(v);
+        const uint64_t key = double_key(v);
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+    };
+    // whole units of pairs on the 16-byte grid: all loads in flight at once
+    if (((uintptr_t)in & 15u) == 0 && hi - lo == kRangeUnit) {
+        constexpr uint32_t kPairs = kRangeUnit / (2 * kBlock), kAhead = kPairs < 8 ? kPairs : 8;
+        const EBC_G f64x2* __restrict__ p = (const EBC_G f64x2*)(in + lo) + threadIdx.x;
+        for (uint32_t j = 0; j < kPairs; j += kAhead) {
+            f64x2 v[kAhead];
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) v[k] = __builtin_nontemporal_load(p + (j + k) * kBlock);
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) take(v[k].x), take(v[k].y);
         }
+    } else {
+        for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) take(in[i]);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -250,7 +261,6 @@ __global__ __launch_bounds__(kBlock) void k_params(const FieldDesc* __restrict__
 }
 
 // ------------------------------------------------------ Lorenzo construct
-typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef f64x2 f64x2_a8 __attribute__((aligned(8)));
 
 // fp64 quads: two 16-byte loads (VEC: 16-byte aligned rows)
