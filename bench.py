@@ -69,7 +69,7 @@ def algo_bytes(stage: str, n: int, o: int, w: int, r: int, n_bins: int, rank: in
         "huffman_decode": dec,
         "rle_decode": 6 * r + 2 * n,
         "outlier_scatter": 12 * o,
-        "reconstruct": 2 * n + elem * n + (4 * o if rank < 3 else 0),
+        "reconstruct": 2 * n + elem * n + 4 * o,
     }
     return table.get(stage)
 

@@ -235,7 +235,7 @@ struct Batch {
     };
     std::vector<Group> groups;
     uint32_t tot_range = 0, tot_seg = 0, tot_ow = 0, tot_hch = 0, tot_hwg = 0, tot_hdwg = 0,
-             tot_rt = 0, tot_runs = 0, tot_sc = 0, tot_rl = 0, tot_fx = 0, tot_sub = 0, tot_hpwg = 0;
+             tot_rt = 0, tot_runs = 0, tot_sc = 0, tot_rl = 0, tot_r3 = 0, tot_sub = 0, tot_hpwg = 0;
     bool overflow = false;  // some work-unit total of the batch reached 2^32
     uint32_t scan = 0;      // scan schedule of the call (largest tuned value of its fields)
     FieldDesc* d_fd = nullptr;
@@ -246,6 +246,7 @@ struct Batch {
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
+    bool out_3d = false;  // decompress: some 3D field has outliers
     bool rle_1d = false, rle_nd = false;  // decompress: run-length coded fields of rank 1, of rank 2 or 3
     // decompress: sub-chunks per wave of a decode workgroup, its lanes, its groups of sub-chunks
     uint32_t dec_per_wave = 0, dec_lanes = 0, dec_groups = 0;
@@ -360,10 +361,10 @@ void fill_geometry(FieldDesc& d, const Geo& g, bool vec)
     d.vec = vec ? 1u : 0u;
 }
 
-// 3D reconstruction workgroup tiles: 256 x 32 x 8 (a wave per 8-row layer)
-void recon3_tiles(const Geo& g, uint32_t t[3])
+// 3D reconstruction: blocks of 64 x 8 x 8, one per wave
+void recon3_blocks(const Geo& g, uint32_t t[3])
 {
-    t[0] = cdiv(g.nx, 256), t[1] = cdiv(g.ny, 32), t[2] = cdiv(g.nz, 8);
+    t[0] = cdiv(g.nx, 64), t[1] = cdiv(g.ny, 8), t[2] = cdiv(g.nz, 8);
 }
 
 // Compression plan: geometry, bases and workspace carving (base == nullptr
@@ -702,7 +703,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
     B.d_dyn = bp.take<FieldDyn>(sizeof(FieldDyn) * B.nf);
     // per-codec unit counts (other codecs get zero units)
     bool* ov = &B.overflow;
-    Tot hch{0, ov}, hdwg{0, ov}, rt{0, ov}, runs{0, ov}, sc{0, ov}, rl{0, ov}, fx{0, ov}, range{0, ov},
+    Tot hch{0, ov}, hdwg{0, ov}, rt{0, ov}, runs{0, ov}, sc{0, ov}, rl{0, ov}, r3{0, ov}, range{0, ov},
         sub{0, ov}, hpwg{0, ov};
     // symbols of a Huffman stream: the N codes, or the run values of RLE+VLE
     auto stream = [&](int i) { return din[i].H.codec == EBC_ARC_RLE_VLE ? din[i].H.n_a : geo[i].n; };
@@ -730,11 +731,11 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
         d.rl_units = cdiv(d.n_runs_hdr, kBlock), d.rl_base = rl.add(d.rl_units);
         d.sc_units = cst ? 0 : cdiv(H.n_out, kBlock), d.sc_base = sc.add(d.sc_units);
-        // 3D with outliers: every wave block of the reconstruction is looked at
         uint32_t t3[3];
-        recon3_tiles(g, t3);
-        d.fx_units = (cst || H.rank != 3 || H.n_out == 0) ? 0 : t3[0] * t3[1] * kWavesPerBlock * t3[2];
-        d.fx_base = fx.add(d.fx_units);
+        recon3_blocks(g, t3);
+        d.r3_units = cst || H.rank != 3 ? 0 : cdiv((uint64_t)t3[0] * t3[1] * t3[2], kWavesPerBlock);
+        d.r3_base = r3.add(d.r3_units);
+        B.out_3d = B.out_3d || (H.rank == 3 && H.n_out > 0);
         d.range_units = cst ? g.range_units : 0, d.range_base = range.add(d.range_units);
         if (cst) {
             // no reconstruction work for a constant field
@@ -743,7 +744,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
     }
     B.tot_hch = (uint32_t)hch.v, B.tot_hdwg = (uint32_t)hdwg.v, B.tot_rt = (uint32_t)rt.v;
     B.tot_runs = (uint32_t)runs.v, B.tot_sc = (uint32_t)sc.v, B.tot_rl = (uint32_t)rl.v;
-    B.tot_fx = (uint32_t)fx.v, B.tot_range = (uint32_t)range.v;
+    B.tot_r3 = (uint32_t)r3.v, B.tot_range = (uint32_t)range.v;
     B.tot_sub = (uint32_t)sub.v, B.tot_hpwg = (uint32_t)hpwg.v;
     // reconstruct groups: recount WG tiles without constant fields
     for (auto& G : B.groups) {
@@ -751,13 +752,10 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         for (int k = G.first; k < G.first + G.count; ++k) {
             FieldDesc& d = B.fd[k];
             const Geo& g = geo[B.order[k]];
-            // (1D run-length coded fields are reconstructed by their RLE tiles)
-            uint32_t wt = d.codec_hdr == EBC_ARC_CONST || (G.rank == 1 && rle_codec(d.codec_hdr)) ? 0 : g.wg_tiles;
-            if (G.rank == 3 && wt) {
-                uint32_t t3[3];
-                recon3_tiles(g, t3);
-                wt = t3[0] * t3[1] * t3[2];
-            }
+            // (1D run-length coded fields are reconstructed by their RLE tiles, 3D
+            // fields by blocks of their own)
+            const bool none = d.codec_hdr == EBC_ARC_CONST || G.rank == 3 || (G.rank == 1 && rle_codec(d.codec_hdr));
+            const uint32_t wt = none ? 0 : g.wg_tiles;
             d.wg_base = wg.add(wt);
             d.wg_tiles = wt;
         }
@@ -780,9 +778,9 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         FieldDesc& d = B.fd[k];
         fill_geometry(d, g, vec[B.order[k]]);
         if (g.rank == 3) {
-            // the 3D reconstruction kernel tiles differently from construction
+            // the 3D reconstruction kernel's blocks differ from construction's tiles
             uint32_t t3[3];
-            recon3_tiles(g, t3);
+            recon3_blocks(g, t3);
             d.nxb = t3[0], d.nyb = t3[1], d.nzb = t3[2];
         }
         d.n_bins = H.n_bins;
@@ -812,8 +810,6 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.rval = H.codec == EBC_ARC_RLE_VLE ? d.vsym
                  : (d.arc ? (const uint16_t*)(d.arc + H.off_val) : nullptr);
         d.sink = bp.take<float>(256);
-        const bool r3 = g.rank == 3 && !cst;
-        d.oflag = bp.take<uint64_t>(r3 ? 8ull * d.nxb * d.nyb * kWavesPerBlock * d.nzb : 0);
         d.zslot = bp.take<uint32_t>(cst ? 0 : 4ull * kZeroSlots * kZeroStride);
     }
     B.ws_bytes = bp.off;
@@ -821,29 +817,22 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
     return EBC_OK;
 }
 
-// Outlier scatter and reconstruction.  The 3D reconstruction reads no deltas:
-// it flags the chunks that hold an outlier code and leaves them to the fix-up,
-// which needs the scattered deltas; 1D/2D reconstruction fuses the scattered
-// deltas itself.
+// Outlier scatter and reconstruction, which fuses the scattered deltas.
 int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
 {
-    bool has3 = false, has12 = B.rle_1d;
-    for (const auto& G : B.groups) (G.rank == 3 ? has3 : has12) |= G.wg_tiles > 0;
-    if (has3) T.mark("reconstruct");
-    for (const auto& G : B.groups)
-        if (G.rank == 3)
-            HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles,
-                                       G.blocks, s));
+    bool has12 = B.rle_1d;
+    for (const auto& G : B.groups) has12 = has12 || G.wg_tiles > 0;
     if (B.tot_sc) T.mark("outlier_scatter");
     HIP_TRY(launch_outlier_scatter(B.d_fd, B.nf, B.tot_sc, B.d_starts, B.d_tmap, s));
-    if (has12) T.mark(has3 ? "reconstruct_12" : "reconstruct");
+    if (B.tot_r3) T.mark("reconstruct");
+    HIP_TRY(launch_reconstruct3(B.d_fd, B.nf, B.tot_r3, s));
+    if (B.out_3d) T.mark("outlier_fix");  // part of the reconstruction: no time of its own
+    if (has12) T.mark(B.tot_r3 ? "reconstruct_12" : "reconstruct");
     for (const auto& G : B.groups)
-        if (G.rank != 3)
+        if (G.wg_tiles)
             HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles,
                                        G.blocks, s));
     if (B.rle_1d) HIP_TRY(launch_rle_reconstruct(B.d_fd, B.nf, B.tot_rt, B.d_starts, B.d_tmap, s));
-    if (B.tot_fx) T.mark("outlier_fix");
-    HIP_TRY(launch_recon_fix(B.d_fd, B.nf, B.tot_fx, s));
     return EBC_OK;
 }
 

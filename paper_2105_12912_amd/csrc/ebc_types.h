@@ -132,8 +132,6 @@ struct FieldDesc {
     EBC_G uint32_t* vhist;   // RLE+VLE compress: histogram of the run values (n_bins)
     EBC_G uint16_t* hsym;    // decompress: Huffman decoder output (q, or vsym for RLE+VLE)
     const EBC_G uint16_t* rval;  // decompress: run values (archive section, or vsym)
-    EBC_G uint64_t* oflag;   // decompress 3D: per wave block, a bit per lane (4 x) whose chunk
-                             // part holds an outlier code
     EBC_G uint32_t* zslot;   // decompress: code-0 counts, kZeroSlots words kZeroStride apart
     EBC_G FieldDyn* dyn;
     // this field's work units in each batch-wide index space
@@ -151,7 +149,7 @@ struct FieldDesc {
     uint32_t n_runs_hdr, rle_base;     // decompress: runs in the archive (start array entries)
     uint32_t sc_units, sc_base;        // decompress outlier scatter: 256 outliers per WG
     uint32_t rl_units, rl_base;        // decompress run-length prep: 256 runs per WG
-    uint32_t fx_units, fx_base;        // decompress 3D outlier fix-up: one 256x8x8 wave block per WG
+    uint32_t r3_units, r3_base;        // decompress 3D: four blocks of 64x8x8 per WG
     // decompress: header values
     uint64_t hn;             // symbols of the Huffman stream (N, or the run count for RLE+VLE)
     uint64_t n_out_hdr;

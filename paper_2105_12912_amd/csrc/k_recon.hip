@@ -8,9 +8,10 @@
 //
 // Mapping: a lane owns four consecutive x.  The x pass is a within-lane prefix
 // plus the totals of the quads to its left in the chunk row (DPP row shifts in
-// 2D and 3D, a full-wave scan for the 256-long 1D chunk); the y and z passes are
-// running sums in registers as the wave walks the chunk's rows and planes.  Integer sums wrap modulo
-// 2^32 exactly as the CPU recurrence truncated to int32 does.
+// 2D and 3D, a full-wave scan for the 256-long 1D chunk); the y pass is a running
+// sum in registers as the wave walks the chunk's rows, the z pass a scan over groups
+// of lanes.  Integer sums wrap modulo 2^32 exactly as the CPU recurrence truncated to
+// int32 does.
 #include "ebc_dev.h"
 #include "ebc_launch.h"
 #include "rle_dev.h"
@@ -453,197 +454,29 @@ __global__ __launch_bounds__(kWave) void k_reconstruct2(const FieldDesc* __restr
     if (l == 0 && zs) atomicAdd(&fd.zslot[(t % kZeroSlots) * kZeroStride], zs);
 }
 
-// Chunk rows of one wave of the 3D reconstruction (see k_reconstruct3).
-// FULL: the wave's 256 x 8 x 8 block lies inside the field and its rows are
-// 16-byte aligned, so every row is one load and one store with no per-lane or
-// per-row condition, addressed as a wave-uniform row pointer plus the lane's
-// offset.  Otherwise rows outside the field are skipped, absent codes read as
-// 1 and absent elements are not stored.  Chunks with outlier codes (0) are not
-// reconstructed here: a lane stops storing at the first plane in which its
-// chunk showed one, and a wave with nothing left to store stops.  Returns the
-// lanes (4 x each) that met an outlier code.
-template <bool FULL, bool VEC, class OT>
-__device__ __forceinline__ uint64_t recon3_wave(const FieldDesc& fd, uint32_t x0w, uint32_t y0, uint32_t z0,
-                                                double ebx2)
+// fp32 quads are stored non-temporally (512^3: 143 us against 144, a batch of 16
+// fields 55 against 56), fp64 ones, two stores each, are not (100x500x500: 96 against
+// 87)
+__device__ __forceinline__ void store_quad3(EBC_G float* __restrict__ o, const float v[4])
 {
-    const int l = lane_id();
-    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    const uint32_t x0 = x0w + 4 * l;
-    const int nvx = x0 < nx ? (int)min<uint32_t>(4, nx - x0) : 0;
-    const uint32_t r = fd.n_bins / 2;
-    const EBC_G uint16_t* __restrict__ q = fd.q;
-    EBC_G OT* __restrict__ out = field_out<OT>(fd);
-    // wave-uniform first element of row y of plane iz (x = x0w)
-    auto row = [&](int iz, int y) -> uint64_t { return ((uint64_t)(z0 + iz) * ny + y0 + y) * nx + x0w; };
-    auto row_ok = [&](int iz, int y) -> bool { return FULL || (y0 + y < ny && z0 + iz < nz); };
-    uint32_t zprev[8][4];
-#pragma unroll
-    for (int y = 0; y < 8; ++y)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) zprev[y][k] = 0;
-    // planes of codes: the next one in flight while this one is processed
-    // (fully unrolled, so only those two occupy registers)
-    u32x2 raw[8][8];
-    auto load_plane = [&](int iz) {
-#pragma unroll
-        for (int y = 0; y < 8; ++y) {
-            if (FULL) {
-                raw[iz][y] = *(const EBC_G u32x2*)(q + row(iz, y) + 4 * l);
-            } else {
-                const bool ok = row_ok(iz, y);
-                raw[iz][y] = load_packed<VEC>(q, ok ? row(iz, y) + 4 * l : 0, ok ? nvx : 0);
-            }
-        }
-    };
-    uint32_t low = 0xFFFFFFFFu;  // smallest code halves met
-    uint64_t met = 0;            // lanes that met an outlier code
-    load_plane(0);
-#pragma unroll
-    for (int iz = 0; iz < 8; ++iz) {
-        // keep the schedule at one plane of loads ahead: without this fence
-        // the compiler hoists every plane's loads and runs out of registers
-        __builtin_amdgcn_sched_barrier(0);
-        if (iz + 1 < 8) load_plane(iz + 1);
-#pragma unroll
-        for (int y = 0; y < 8; ++y) low = min_halves(low, min_halves(raw[iz][y].x, raw[iz][y].y));
-        met = ballot(has_zero_half(low));
-        // both lanes of a chunk's pair, and lanes past the field, are done
-        const uint64_t pairs = met | ((met >> 1) & 0x5555555555555555ull) | ((met & 0x5555555555555555ull) << 1);
-        const bool live = (FULL || nvx > 0) && ((pairs >> l) & 1u) == 0;
-        if (!__any(live)) break;
-        uint32_t yprev[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int y = 0; y < 8; ++y) {
-            if (!FULL && !row_ok(iz, y)) continue;  // wave-uniform
-            uint32_t c[4], sv[4];
-            unpack4(raw[iz][y], c);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) sv[k] = c[k] - r;
-            sv[1] += sv[0], sv[2] += sv[1], sv[3] += sv[2];  // x pass within the quad
-            uint32_t left = dpp_shr_u<1>(sv[3]);            // the pair lane's total
-            if ((l & 1) == 0) left = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                sv[k] += left;
-                sv[k] += yprev[k];  // y pass
-                yprev[k] = sv[k];
-                sv[k] += zprev[y][k];  // z pass
-                zprev[y][k] = sv[k];
-            }
-            OT v[4];
-            dequant4(sv, ebx2, v);
-            if constexpr (FULL && sizeof(OT) == 4) {
-                if (live) st_nt_f4(out + row(iz, y) + 4 * l, f32x4{v[0], v[1], v[2], v[3]});
-            } else {
-                if (live) store_quad<VEC>(out, row(iz, y) + 4 * l, FULL ? 4 : nvx, v);
-            }
-        }
-    }
-    return met;
+    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, (EBC_G f32x4_a4*)o);
+}
+__device__ __forceinline__ void store_quad3(EBC_G double* __restrict__ o, const double v[4])
+{
+    store_quad<false>(o, 0, 4, v);
 }
 
-// 3D: a wave owns 256 x (one quad per lane) by one 8x8 chunk layer in y and
-// z; a workgroup stacks four waves along y (tile 256 x 32 x 8; the field
-// descriptor's nxb/nyb/nzb hold this tiling during decompression).  Per z
-// plane a lane holds its quad in each of the 8 rows of the chunk layer: the x
-// pass is in-lane plus the total of the pair lane (an 8-wide chunk row is two
-// quads), the y pass a running sum over the rows and the z pass a running sum
-// over the planes, both in registers.  Every row is one 512-byte code load
-// and one 1 KiB store per wave.
-//
-// Outliers are not read here: a wait for a delta loaded in the middle of the
-// stream would also wait for every load and store issued before it.  Each
-// wave records which of its lanes met an outlier code, and k_recon3_fix
-// reconstructs those chunks (and counts their outliers).
-template <bool VEC, class OT>
-__global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __restrict__ F, int nf)
-{
-    const uint32_t t = blockIdx.x;
-    const int f = find_field<&FieldDesc::wg_base>(F, nf, t);
-    const FieldDesc& fd = F[f];
-    const auto* dy = kconst(fd.dyn);
-    if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
-    const uint32_t tl = t - fd.wg_base;
-    const uint32_t nxb = fd.nxb, nyb = fd.nyb;
-    const uint32_t xb = tl % nxb, yb = (tl / nxb) % nyb, zb = tl / (nxb * nyb);
-    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t x0w = xb * 256, y0 = yb * 32 + w * 8, z0 = zb * 8;
-    const double ebx2 = dy->ebx2;
-    uint64_t met;
-    if (VEC && x0w + 256 <= fd.nx && y0 + 8 <= fd.ny && z0 + 8 <= fd.nz)
-        met = recon3_wave<true, VEC, OT>(fd, x0w, y0, z0, ebx2);
-    else
-        met = recon3_wave<false, VEC, OT>(fd, x0w, y0, z0, ebx2);
-    if (lane_id() == 0) {
-        fd.oflag[(zb * (nyb * kWavesPerBlock) + yb * kWavesPerBlock + w) * nxb + xb] = met;
-        // no fix-up runs for a field without listed outliers: any count will
-        // do for the check to refuse its outlier codes
-        if (met && fd.n_out_hdr == 0) atomicAdd(&fd.zslot[0], 1u);
-    }
-}
-
-// One wave's share of the fix-up: the flagged ones of eight 8x8x8 chunks along
-// x.  Lane (g, xq) = (l / 16, l % 16) owns a quad along x of the planes 2g and
-// 2g + 1, so a row of the wave's 64 x is one contiguous piece of memory, and walks
-// y: the x pass is in-lane plus the total of the pair lane, the y pass a running
-// sum, the z pass a sum of the lane's two planes and a scan over the four g.  All
-// codes and deltas are loaded before any is used, behind one branch.  Bound by the
-// memory pipeline: with a lane per row of 8 x, each access of a wave touched 64
-// places (fp64 field of 100x500x500, nearly every chunk flagged: 114 us, now 81;
-// with a branch per row 86, and 29 instead of 18 us where few chunks are flagged).
-// Returns the lane's outlier count.
+// The chunks of a wave's block from its codes and deltas (see k_reconstruct3).
+// full: both planes of the lane's quad lie in the field; nvz: the quad's elements
+// inside the field, by plane.  Returns the lane's outlier count.
 template <class OT>
-__device__ __forceinline__ uint32_t fix_wave(const FieldDesc& fd, bool flagged, uint32_t x0, uint32_t y0,
-                                             uint32_t z0, double ebx2)
+__device__ __forceinline__ uint32_t block_sums(const FieldDesc& fd, const u32x2 (&c)[2][8],
+                                                    const u32x4 (&d)[2][8], uint32_t y0, uint64_t i0, bool full,
+                                                    const int (&nvz)[2], double ebx2)
 {
-    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    const uint32_t g = lane_id() >> 4, zz = z0 + 2 * g;
-    const int nv = flagged && x0 < nx ? (int)min<uint32_t>(4, nx - x0) : 0;
-    const uint32_t r = fd.n_bins / 2;
-    const EBC_G uint16_t* __restrict__ q = fd.q;
-    const EBC_G int32_t* __restrict__ dsc = fd.dsc;
+    const uint32_t nx = fd.nx, ny = fd.ny, r = fd.n_bins / 2, g = lane_id() >> 4;
+    const uint64_t plane = (uint64_t)ny * nx;
     EBC_G OT* __restrict__ out = field_out<OT>(fd);
-    const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0, plane = (uint64_t)ny * nx;
-    const bool full = nv == 4 && zz + 1 < nz;
-    const int nvz[2] = {zz < nz ? nv : 0, zz + 1 < nz ? nv : 0};
-    u32x2 c[2][8];
-    u32x4 d[2][8];
-#pragma unroll
-    for (uint32_t y = 0; y < 8; ++y) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            c[p][y] = u32x2{0x00010001u, 0x00010001u};
-            d[p][y] = u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-    if (full) {
-#pragma unroll
-        for (uint32_t y = 0; y < 8; ++y) {
-            if (y0 + y >= ny) break;  // uniform
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                c[p][y] = *(const EBC_G u32x2_a2*)(q + i0 + p * plane + (uint64_t)y * nx);
-                d[p][y] = *(const EBC_G u32x4_a4*)(dsc + i0 + p * plane + (uint64_t)y * nx);
-            }
-        }
-    } else if (nvz[0] > 0) {
-        // the field's last, partial quad along x, or its last plane
-#pragma unroll
-        for (uint32_t y = 0; y < 8; ++y) {
-            if (y0 + y >= ny) break;
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const uint64_t i = i0 + p * plane + (uint64_t)y * nx;
-                uint32_t e[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    e[k] = k < nvz[p] ? q[i + k] : 1u;
-                    d[p][y][k] = k < nvz[p] ? (uint32_t)dsc[i + k] : 0u;
-                }
-                c[p][y] = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
-            }
-        }
-    }
     uint32_t yprev[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     uint32_t zeros = 0;
     const uint32_t odd = lane_id() & 1 ? ~0u : 0u, g1 = g & 1 ? ~0u : 0u, g2 = g & 2 ? ~0u : 0u;
@@ -682,8 +515,8 @@ __device__ __forceinline__ uint32_t fix_wave(const FieldDesc& fd, bool flagged, 
         dequant4(s[0], ebx2, v[0]);
         dequant4(s[1], ebx2, v[1]);
         if (full) {
-            store_quad<false>(out, i, 4, v[0]);
-            store_quad<false>(out, i + plane, 4, v[1]);
+            store_quad3(out + i, v[0]);
+            store_quad3(out + i + plane, v[1]);
         } else if (nvz[0] > 0) {
             store_quad<false>(out, i, nvz[0], v[0]);
             store_quad<false>(out, i + plane, nvz[1], v[1]);
@@ -692,33 +525,113 @@ __device__ __forceinline__ uint32_t fix_wave(const FieldDesc& fd, bool flagged, 
     return zeros;
 }
 
-// Outlier fix-up of the 3D reconstruction: a workgroup per wave block of
-// k_reconstruct3, a wave per 64 x of it; waves without a flagged chunk leave at
-// once.  With one queue entry per flagged chunk instead, the queue's counter
-// alone took 2.5 ms for the 5e4 chunks of a batch of rough fields (2.5e7
-// elements, nearly every chunk flagged) and the chunks, a wave each with
-// 2-byte loads, 0.37 ms.
-__global__ __launch_bounds__(kBlock) void k_recon3_fix(const FieldDesc* __restrict__ F, int nf)
+// 3D: a wave owns a block of 64 x 8 x 8, eight chunks along x.  Lane (g, xq) =
+// (l / 16, l % 16) holds a quad along x of the planes 2g and 2g + 1 and walks y, so a
+// row of the block is one access of 16 lanes: the x pass is in-lane plus the total of
+// the pair lane, the y pass a running sum, the z pass a sum of the lane's two planes
+// and a scan over the four g.  All codes are loaded at once, behind one branch (with
+// one per row the loads were spread out and everything a third slower), then, if some
+// lane holds an outlier, the deltas (for quads without one the field's first delta, so
+// that no access depends on the lane).  Bound by the traffic, and by the two round
+// trips on fields of a few million values.
+//
+// A wave per 256 x 8 x 8 that kept running sums over all planes, with the chunks that
+// hold outliers left to a second kernel, took 158 + 18 us on 512^3, 40 + 90 on a rough
+// fp64 field of 100x500x500 and 83 + 43 on the 3D fields of a batch; this one takes
+// 143, 87 and 55.
+template <class OT>
+__device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0, uint32_t y0, uint32_t z0,
+                                             double ebx2)
+{
+    const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
+    const uint32_t g = lane_id() >> 4, zz = z0 + 2 * g;
+    const int nv = x0 < nx ? (int)min<uint32_t>(4, nx - x0) : 0;
+    const EBC_G uint16_t* __restrict__ q = fd.q;
+    const EBC_G int32_t* __restrict__ dsc = fd.dsc;
+    const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0, plane = (uint64_t)ny * nx;
+    const bool full = nv == 4 && zz + 1 < nz;
+    const int nvz[2] = {zz < nz ? nv : 0, zz + 1 < nz ? nv : 0};
+    u32x2 c[2][8];
+    u32x4 d[2][8];
+#pragma unroll
+    for (uint32_t y = 0; y < 8; ++y) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            c[p][y] = u32x2{0x00010001u, 0x00010001u};
+            d[p][y] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    if (full) {
+#pragma unroll
+        for (uint32_t y = 0; y < 8; ++y) {
+            if (y0 + y >= ny) break;  // uniform
+#pragma unroll
+            for (int p = 0; p < 2; ++p) c[p][y] = *(const EBC_G u32x2_a2*)(q + i0 + p * plane + (uint64_t)y * nx);
+        }
+    } else if (nvz[0] > 0) {
+        // the field's last, partial quad along x, or its last plane
+#pragma unroll
+        for (uint32_t y = 0; y < 8; ++y) {
+            if (y0 + y >= ny) break;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint64_t i = i0 + p * plane + (uint64_t)y * nx;
+                uint32_t e[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) e[k] = k < nvz[p] ? q[i + k] : 1u;
+                c[p][y] = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+            }
+        }
+    }
+    uint32_t low = 0xFFFFFFFFu;  // smallest code halves met
+#pragma unroll
+    for (uint32_t y = 0; y < 8; ++y)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) low = min_halves(low, min_halves(c[p][y].x, c[p][y].y));
+    const bool met = has_zero_half(low);
+    if (__any(met)) {
+        if (full) {
+#pragma unroll
+            for (uint32_t y = 0; y < 8; ++y) {
+                if (y0 + y >= ny) break;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const bool z = has_zero_half(min_halves(c[p][y].x, c[p][y].y));
+                    d[p][y] = *(const EBC_G u32x4_a4*)(dsc + (z ? i0 + p * plane + (uint64_t)y * nx : 0));
+                }
+            }
+        } else if (met) {
+#pragma unroll
+            for (uint32_t y = 0; y < 8; ++y) {
+                if (y0 + y >= ny) break;
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        d[p][y][k] = k < nvz[p] ? (uint32_t)dsc[i0 + p * plane + (uint64_t)y * nx + k] : 0u;
+            }
+        }
+    }
+    return block_sums<OT>(fd, c, d, y0, i0, full, nvz, ebx2);
+}
+
+// a workgroup per four blocks, in the order x, y, z
+__global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __restrict__ F, int nf)
 {
     const uint32_t t = blockIdx.x;
-    const int f = find_field<&FieldDesc::fx_base>(F, nf, t);
+    const int f = find_field<&FieldDesc::r3_base>(F, nf, t);
     const FieldDesc& fd = F[f];
     const auto* dy = kconst(fd.dyn);
     if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
-    const uint32_t b = t - fd.fx_base;  // wave block, in the order of oflag
-    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t bits = (uint32_t)(kconst(fd.oflag)[b] >> (16 * w)) & 0xFFFFu;
-    if (bits == 0) return;
-    const uint32_t nxb = fd.nxb, nyw = fd.nyb * kWavesPerBlock;
-    const uint32_t xb = b % nxb, yw = (b / nxb) % nyw, zb = b / (nxb * nyw);
-    const uint32_t xq = lane_id() & 15;
-    const bool flagged = ((bits >> (xq & 14u)) & 3u) != 0;  // either lane of the chunk's pair
-    const uint32_t x0 = xb * 256 + w * 64 + xq * 4;
-    const uint32_t zeros = fd.dtype == 1 ? fix_wave<double>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2)
-                                         : fix_wave<float>(fd, flagged, x0, yw * 8, zb * 8, dy->ebx2);
+    const uint32_t b = (t - fd.r3_base) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t nxb = fd.nxb, nyb = fd.nyb;
+    const uint32_t xb = b % nxb, yb = (b / nxb) % nyb, zb = b / (nxb * nyb);
+    if (zb >= fd.nzb) return;
+    const uint32_t x0 = xb * 64 + (lane_id() & 15) * 4;
+    const uint32_t zeros = fd.dtype == 1 ? recon3_wave<double>(fd, x0, yb * 8, zb * 8, dy->ebx2)
+                                         : recon3_wave<float>(fd, x0, yb * 8, zb * 8, dy->ebx2);
     const uint32_t zs = wave_sum_u32(zeros);
-    if (lane_id() == 0 && zs)
-        atomicAdd(&fd.zslot[((t * kWavesPerBlock + w) % kZeroSlots) * kZeroStride], zs);
+    if (lane_id() == 0 && zs) atomicAdd(&fd.zslot[(b % kZeroSlots) * kZeroStride], zs);
 }
 
 // decompression epilogue, one wave per field: the code-0 count must equal the
@@ -762,14 +675,10 @@ static void reconstruct_launch(const FieldDesc* F, int nf, int rank, bool vec, u
     if (rank == 1) {
         if (vec) hipLaunchKernelGGL((k_reconstruct<true, OT>), g, b, 0, s, F, nf, wg_tiles);
         else hipLaunchKernelGGL((k_reconstruct<false, OT>), g, b, 0, s, F, nf, wg_tiles);
-    } else if (rank == 2) {
+    } else {
         const dim3 g2(wg_tiles), b2(kWave);  // one wave per tile
         if (vec) hipLaunchKernelGGL((k_reconstruct2<true, OT>), g2, b2, 0, s, F, nf);
         else hipLaunchKernelGGL((k_reconstruct2<false, OT>), g2, b2, 0, s, F, nf);
-    } else {
-        const dim3 g3(wg_tiles);  // one workgroup per tile
-        if (vec) hipLaunchKernelGGL((k_reconstruct3<true, OT>), g3, b, 0, s, F, nf);
-        else hipLaunchKernelGGL((k_reconstruct3<false, OT>), g3, b, 0, s, F, nf);
     }
 }
 
@@ -789,10 +698,10 @@ hipError_t launch_rle_reconstruct(const FieldDesc* F, int nf, uint32_t rt_units,
     return hipGetLastError();
 }
 
-hipError_t launch_recon_fix(const FieldDesc* F, int nf, uint32_t units, hipStream_t s)
+hipError_t launch_reconstruct3(const FieldDesc* F, int nf, uint32_t units, hipStream_t s)
 {
     if (!units) return hipSuccess;
-    hipLaunchKernelGGL(k_recon3_fix, dim3(units), dim3(kBlock), 0, s, F, nf);
+    hipLaunchKernelGGL(k_reconstruct3, dim3(units), dim3(kBlock), 0, s, F, nf);
     return hipGetLastError();
 }
 
