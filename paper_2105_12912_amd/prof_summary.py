@@ -36,16 +36,19 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = {
     "k_construct": ["paper_2105_12912_amd/csrc/k_quant.hip"],
     "k_reconstruct": ["paper_2105_12912_amd/csrc/k_recon.hip"],
+    "k_reconstruct2": ["paper_2105_12912_amd/csrc/k_recon.hip"],
     "k_reconstruct3": ["paper_2105_12912_amd/csrc/k_recon.hip"],
     "k_huff_decode": ["paper_2105_12912_amd/csrc/k_huffman.hip"],
     "k_huff_write": ["paper_2105_12912_amd/csrc/k_huffman.hip"],
     "k_huff_bits": ["paper_2105_12912_amd/csrc/k_huffman.hip"],
     "k_range": ["paper_2105_12912_amd/csrc/k_quant.hip"],
-    "k_rle_count": ["paper_2105_12912_amd/csrc/k_rle.hip"],
+    "k_rle_reconstruct": ["paper_2105_12912_amd/csrc/k_recon.hip", "paper_2105_12912_amd/csrc/rle_dev.h"],
     "k_rle_write": ["paper_2105_12912_amd/csrc/k_rle.hip"],
-    "k_rle_expand": ["paper_2105_12912_amd/csrc/k_rle.hip"],
+    "k_rle_expand": ["paper_2105_12912_amd/csrc/k_rle.hip", "paper_2105_12912_amd/csrc/rle_dev.h"],
+    "k_finish": ["paper_2105_12912_amd/csrc/k_outlier.hip"],
 }
-COMMON_SOURCES = ["paper_2105_12912_amd/csrc/ebc_dev.h", "paper_2105_12912_amd/csrc/ebc_types.h"]
+COMMON_SOURCES = ["paper_2105_12912_amd/csrc/ebc_dev.h", "paper_2105_12912_amd/csrc/ebc_types.h",
+                  "paper_2105_12912_amd/csrc/encode_dev.h"]
 
 
 def source_hash(kernel: str) -> str | None:
