@@ -568,8 +568,15 @@ __device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0
 #pragma unroll
             for (int p = 0; p < 2; ++p) c[p][y] = *(const EBC_G u32x2_a2*)(q + i0 + p * plane + (uint64_t)y * nx);
         }
+    } else if (nvz[0] == 4) {
+        // the field's last plane
+#pragma unroll
+        for (uint32_t y = 0; y < 8; ++y) {
+            if (y0 + y >= ny) break;
+            c[0][y] = *(const EBC_G u32x2_a2*)(q + i0 + (uint64_t)y * nx);
+        }
     } else if (nvz[0] > 0) {
-        // the field's last, partial quad along x, or its last plane
+        // the field's last, partial quad along x
 #pragma unroll
         for (uint32_t y = 0; y < 8; ++y) {
             if (y0 + y >= ny) break;

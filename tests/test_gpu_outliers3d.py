@@ -66,3 +66,17 @@ def test_outlier_code_without_a_listed_outlier_is_refused(E, shape):
     with pytest.raises(E.EbcError) as ei:
         E.debug_reconstruct(torch.from_numpy(q).cuda(), none, none, 3, shape[::-1], 64, 1.0)
     assert ei.value.status == E.EBC_ERR_ARCHIVE
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("density", [0.0, 0.05])
+@pytest.mark.parametrize("shape", [(1, 16, 512), (1, 9, 261), (2, 8, 66), (3, 7, 63), (9, 1, 4), (5, 3, 1), (1, 1, 70)])
+def test_few_planes_rows_and_columns(E, shape, density, dtype):
+    """A last plane without its pair, blocks of one row, quads that the field cuts."""
+    x = field((16, 16, 512), density, dtype)[tuple(slice(0, n) for n in shape)].copy()
+    x.flat[0], x.flat[-1] = -50.0, 50.0
+    want = O.compress(x, 0.01, "abs", n_bins=64)
+    a = E.compress(torch.from_numpy(x).cuda(), 0.01, "abs", n_bins=64)
+    assert a.cpu().numpy().tobytes() == want
+    y = E.decompress(a).cpu().numpy()
+    assert y.tobytes() == O.decompress(want).tobytes()
