@@ -162,6 +162,11 @@ __device__ __forceinline__ uint64_t run_flags64(const FieldDesc& fd, uint64_t i0
     return fd.n - i0 < 64 ? m & ((1ull << (fd.n - i0)) - 1) : m;
 }
 
+// Runs of a tile from which the wave writes them 64 codes at a time instead of a lane
+// its own: a lane's runs follow each other, each a load and two stores of their own.
+// (A compression of 4M noise values, nearly each a run: 238 us without, 145 with.)
+constexpr uint32_t kDenseRuns = 1024;
+
 // Write pass: (value, length) of the runs that start in each tile, a wave per
 // tile and 64 codes per lane, so that waves need no barrier and many tiles are
 // in flight (the pass is a chain of short loads: a workgroup per tile took 53 us
@@ -231,6 +236,25 @@ __device__ __forceinline__ void rle_write_tiles(const FieldDesc* __restrict__ F,
         if (later) after = nl;
         EBC_G uint16_t* val = val_arc ? (EBC_G uint16_t*)(fd.arc + kHdr) : fd.vsym;
         EBC_G uint32_t* len = (EBC_G uint32_t*)(fd.arc + off_rlen);
+        if (b - a > kDenseRuns) {
+            // 64 consecutive codes per step, so that loads and stores are contiguous
+            uint32_t at = a - r0;
+#pragma unroll 4
+            for (uint32_t g = 0; g < kWave; ++g) {
+                const uint64_t mg = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m >> 32), g) << 32 |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)m, g);
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)after, g);
+                const uint32_t p = tl * kRleTile + g * 64 + lane;
+                if ((mg >> lane) & 1u) {
+                    const uint64_t next = mg >> lane >> 1;
+                    const uint32_t o = at + __popcll(mg & ((1ull << lane) - 1));
+                    if (val_arc || val_sym) val[o] = fd.q[p];
+                    if (lens) len[o] = (next ? p + 1 + __builtin_ctzll(next) : end) - p;
+                }
+                at += __popcll(mg);
+            }
+            continue;
+        }
         while (m) {
             const uint32_t k = __builtin_ctzll(m);
             m &= m - 1;

@@ -58,3 +58,17 @@ def test_runs(E, n, kind, n_bins, hc, codec):
 @pytest.mark.parametrize("n_bins", [16, 1024])
 def test_flags_on_a_large_field(E, n_bins):
     check(E, field((1 << 24) + 4099, "rare"), codec="rle", n_bins=n_bins)
+
+
+@pytest.mark.parametrize("codec", ["rle", "rle_vle"])
+@pytest.mark.parametrize("runs", [1022, 1024, 1026, 4096])
+@pytest.mark.parametrize("n", [8191, 8192, 30_001])
+def test_runs_of_one_tile(E, n, runs, codec):
+    """Tiles of few runs around one of as many as given, which picks who writes them."""
+    d = np.zeros(n)
+    d[4096:min(n, 4096 + runs):2] = 1.0
+    d[0] = 3.0
+    x = np.zeros(n)
+    for a in range(0, n, 256):
+        x[a:a + 256] = np.cumsum(d[a:a + 256])
+    check(E, (x * 0.02).astype(np.float32), codec=codec)
