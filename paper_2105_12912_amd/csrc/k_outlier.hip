@@ -92,7 +92,12 @@ __device__ __forceinline__ void outlier_unit(const FieldDesc& fd, uint32_t t, co
     EBC_G int32_t* const oval = to.oval;
     const EBC_G uint16_t* __restrict__ q = fd.q;
     const EBC_G int32_t* __restrict__ dsc = fd.dsc;
-    const uint32_t g = fd.xs / kSegLane;  // lanes per segment: 4 .. 32
+    // lanes per segment: as the segment's width asks for, 1 .. 32; rows shorter than a
+    // segment take fewer (4M rows of 2: 79 us with xs / 8 lanes each, 37 so)
+    const uint32_t row = fd.rank == 1 || fd.nx >= fd.xs ? fd.xs
+                         : fd.nx <= kSegLane            ? kSegLane
+                                                        : 1u << (32 - __builtin_clz(fd.nx - 1));
+    const uint32_t g = row / kSegLane;
     // outliers in more than one of 16 elements: nearly every lane needs its deltas
     const bool dense = 16 * (uint64_t)(kcount(soff, (uint64_t)fd.seg_base + fd.n_seg) - kcount(soff, fd.seg_base)) > fd.n;
     const uint32_t sub = threadIdx.x / g, gl = threadIdx.x % g, per = kBlock / g;

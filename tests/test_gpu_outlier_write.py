@@ -28,3 +28,14 @@ def test_outlier_list(E, shape, density):
     want = O.compress(x, 0.5, "abs", n_bins=64)
     got = E.compress(torch.from_numpy(x).cuda(), 0.5, "abs", n_bins=64).cpu().numpy().tobytes()
     assert got == want
+
+
+@pytest.mark.parametrize("shape", [(900, 2), (900, 8), (700, 9), (300, 16), (300, 17), (9, 40, 1), (9, 40, 8), (10, 33, 15)])
+def test_short_rows(E, shape):
+    """Rows shorter than a segment, one to four lanes each."""
+    rng = np.random.default_rng(12)
+    x = rng.standard_normal(shape).astype(np.float32)
+    x[rng.random(shape) < 0.4] *= np.float32(1e4)
+    want = O.compress(x, 0.5, "abs", n_bins=64)
+    got = E.compress(torch.from_numpy(x).cuda(), 0.5, "abs", n_bins=64).cpu().numpy().tobytes()
+    assert got == want
