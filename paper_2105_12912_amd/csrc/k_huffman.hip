@@ -329,8 +329,9 @@ struct WriteProc {
     uint64_t* lds64;
     int cur;
     bool fits;                  // field cur's archive fits into its buffer
-    EBC_G uint32_t* words;      // its sections (words: from word offset 0 of the batch on)
+    EBC_G uint32_t* words;      // its sections
     EBC_G uint16_t* sbits;
+    uint32_t wfirst;            // scanned word offset of its first chunk
     const EBC_G uint64_t* code;
     uint32_t tab;               // entries of the LDS code table
     // Lanes of up to 16 symbols keep their table entries in registers and join
@@ -380,7 +381,8 @@ struct WriteProc {
             const FieldDesc& fd = F[u.e.f];
             const Layout y = layout_of(fd, kconst(fd.dyn)->codec, soff, woff, roff);
             fits = y.total <= fd.arc_cap;
-            words = (EBC_G uint32_t*)(fd.arc + y.off_words) - kcount(woff, u.e.hch);
+            words = (EBC_G uint32_t*)(fd.arc + y.off_words);
+            wfirst = kcount(woff, u.e.hch);
             sbits = (EBC_G uint16_t*)(fd.arc + y.off_sbits);
             code = fd.code;
             tab = W ? 0u : fd.n_bins;
@@ -429,7 +431,10 @@ struct WriteProc {
         const uint32_t incl = wave_incl_scan_u32(mybits);
         const uint32_t b0 = incl - mybits;
         const uint32_t nw = ((uint32_t)__builtin_amdgcn_readlane((int)incl, 63) + 31) / 32;  // the chunk's words
-        EBC_G uint32_t* dst = words + u.wo;
+        // Offsets count modulo 2^32, from whatever the counts scanned before this
+        // field's add up to (those of a field that is not coded are never written):
+        // only the difference of two offsets of one field is a place.
+        EBC_G uint32_t* dst = words + (uint32_t)(u.wo - wfirst);
         // sub-chunk bit counts (u16): one per kSubMax symbols of the chunk, or
         // one for the whole chunk when it is shorter; a sub-chunk's count is
         // the scan at its last lane minus b0 at its first
@@ -508,7 +513,7 @@ __global__ __launch_bounds__(kBlock) void k_huff_write(const FieldDesc* __restri
                                                        const uint32_t* __restrict__ roff, uint32_t units)
 {
     extern __shared__ uint64_t lds64[];
-    WriteProc<S, W> proc{F, soff, woff, roff, lds64, -1, false, nullptr, nullptr, nullptr, 0};
+    WriteProc<S, W> proc{F, soff, woff, roff, lds64, -1, false, nullptr, nullptr, 0, nullptr, 0};
     enc_pipeline<S>(F, nf, units, 2, woff, proc);
 }
 
