@@ -361,10 +361,18 @@ void fill_geometry(FieldDesc& d, const Geo& g, bool vec)
     d.vec = vec ? 1u : 0u;
 }
 
-// 3D reconstruction: blocks of 64 x 8 x 8, one per wave
+// 3D reconstruction: blocks of 64 x 8 x 8, one per wave; in a last layer of few
+// planes two or four along x
 void recon3_blocks(const Geo& g, uint32_t t[3])
 {
     t[0] = cdiv(g.nx, 64), t[1] = cdiv(g.ny, 8), t[2] = cdiv(g.nz, 8);
+}
+uint64_t recon3_waves(const Geo& g)
+{
+    uint32_t t[3];
+    recon3_blocks(g, t);
+    const uint32_t gp = recon3_groups((uint32_t)(g.nz - 8ull * (t[2] - 1)));
+    return (uint64_t)t[1] * ((uint64_t)t[0] * (t[2] - 1) + cdiv(t[0], 4 / gp));
 }
 
 // Compression plan: geometry, bases and workspace carving (base == nullptr
@@ -731,9 +739,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         d.n_runs_hdr = rle ? (uint32_t)H.n_a : 0, d.rle_base = runs.add(d.n_runs_hdr);
         d.rl_units = cdiv(d.n_runs_hdr, kBlock), d.rl_base = rl.add(d.rl_units);
         d.sc_units = cst ? 0 : cdiv(H.n_out, kBlock), d.sc_base = sc.add(d.sc_units);
-        uint32_t t3[3];
-        recon3_blocks(g, t3);
-        d.r3_units = cst || H.rank != 3 ? 0 : cdiv((uint64_t)t3[0] * t3[1] * t3[2], kWavesPerBlock);
+        d.r3_units = cst || H.rank != 3 ? 0 : cdiv(recon3_waves(g), kWavesPerBlock);
         d.r3_base = r3.add(d.r3_units);
         B.out_3d = B.out_3d || (H.rank == 3 && H.n_out > 0);
         d.range_units = cst ? g.range_units : 0, d.range_base = range.add(d.range_units);

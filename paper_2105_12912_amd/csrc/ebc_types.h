@@ -149,7 +149,7 @@ struct FieldDesc {
     uint32_t n_runs_hdr, rle_base;     // decompress: runs in the archive (start array entries)
     uint32_t sc_units, sc_base;        // decompress outlier scatter: 256 outliers per WG
     uint32_t rl_units, rl_base;        // decompress run-length prep: 256 runs per WG
-    uint32_t r3_units, r3_base;        // decompress 3D: four blocks of 64x8x8 per WG
+    uint32_t r3_units, r3_base;        // decompress 3D: four waves per WG, a block of 64x8x8 or more each
     // decompress: header values
     uint64_t hn;             // symbols of the Huffman stream (N, or the run count for RLE+VLE)
     uint64_t n_out_hdr;
@@ -200,6 +200,10 @@ struct DecTab {
 // chunks per encode workgroup (one per wave); chunks longer than kPassHc
 // symbols are encoded by one wave in passes of kPassHc
 __host__ __device__ constexpr uint32_t huff_cpw(uint32_t hc) { return hc <= 1024 ? 4 : hc <= kPassHc ? kPassHc / hc : 1; }
+
+// 3D reconstruction: 16-lane groups that a block with this many planes left has work
+// for (two planes each)
+__host__ __device__ constexpr uint32_t recon3_groups(uint32_t planes) { return planes <= 2 ? 1 : planes <= 4 ? 2 : 4; }
 
 // histogram slots a construction workgroup keeps in LDS for n_bins bins
 __host__ __device__ constexpr uint32_t hist_slots(uint32_t nb) { return nb > kMaxBins ? kHistWin : nb; }

@@ -466,15 +466,15 @@ __device__ __forceinline__ void store_quad3(EBC_G double* __restrict__ o, const 
     store_quad<false>(o, 0, 4, v);
 }
 
-// The chunks of a wave's block from its codes and deltas (see k_reconstruct3).
-// full: both planes of the lane's quad lie in the field; nvz: the quad's elements
-// inside the field, by plane.  Returns the lane's outlier count.
-template <class OT>
+// The chunks of a wave's blocks from their codes and deltas (see k_reconstruct3).
+// full: both planes of the lane's quad lie in the field, single: the first does; nvz:
+// the quad's elements inside the field, by plane.  Returns the lane's outlier count.
+template <class OT, uint32_t GP>
 __device__ __forceinline__ uint32_t block_sums(const FieldDesc& fd, const u32x2 (&c)[2][8],
                                                     const u32x4 (&d)[2][8], uint32_t y0, uint64_t i0, bool full,
-                                                    const int (&nvz)[2], double ebx2)
+                                                    bool single, const int (&nvz)[2], double ebx2)
 {
-    const uint32_t nx = fd.nx, ny = fd.ny, r = fd.n_bins / 2, g = lane_id() >> 4;
+    const uint32_t nx = fd.nx, ny = fd.ny, r = fd.n_bins / 2, g = (lane_id() >> 4) % GP;
     const uint64_t plane = (uint64_t)ny * nx;
     EBC_G OT* __restrict__ out = field_out<OT>(fd);
     uint32_t yprev[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -504,11 +504,16 @@ __device__ __forceinline__ uint32_t block_sums(const FieldDesc& fd, const u32x2 
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             s[1][k] += s[0][k];
-            // z pass: the totals of the lanes with a lower g
-            const auto t = __builtin_amdgcn_permlane16_swap(s[1][k], s[1][k], false, false);
-            const uint32_t both = t[0] + t[1];
-            const uint32_t below = (t[0] & g1) + (__builtin_amdgcn_permlane32_swap(both, both, false, false)[0] & g2);
-            s[0][k] += below, s[1][k] += below;
+            // z pass: the totals of the block's lanes with a lower g
+            if constexpr (GP > 1) {
+                const auto t = __builtin_amdgcn_permlane16_swap(s[1][k], s[1][k], false, false);
+                uint32_t below = t[0] & g1;
+                if constexpr (GP > 2) {
+                    const uint32_t both = t[0] + t[1];
+                    below += __builtin_amdgcn_permlane32_swap(both, both, false, false)[0] & g2;
+                }
+                s[0][k] += below, s[1][k] += below;
+            }
         }
         const uint64_t i = i0 + (uint64_t)y * nx;
         OT v[2][4];
@@ -517,6 +522,8 @@ __device__ __forceinline__ uint32_t block_sums(const FieldDesc& fd, const u32x2 
         if (full) {
             store_quad3(out + i, v[0]);
             store_quad3(out + i + plane, v[1]);
+        } else if (single) {
+            store_quad3(out + i, v[0]);
         } else if (nvz[0] > 0) {
             store_quad<false>(out, i, nvz[0], v[0]);
             store_quad<false>(out, i + plane, nvz[1], v[1]);
@@ -539,17 +546,24 @@ __device__ __forceinline__ uint32_t block_sums(const FieldDesc& fd, const u32x2 
 // hold outliers left to a second kernel, took 158 + 18 us on 512^3, 40 + 90 on a rough
 // fp64 field of 100x500x500 and 83 + 43 on the 3D fields of a batch; this one takes
 // 143, 87 and 55.
-template <class OT>
-__device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0, uint32_t y0, uint32_t z0,
+//
+// GP: 16-lane groups per block.  A last layer of one or two planes has work for one
+// group of a block, of three or four for two: the wave then takes the four or two
+// next blocks along x (recon3_groups).  With one block per wave in every layer such
+// fields took 79 us (1x4096x4096), 85 (2), 112 (3) and 227 (9 planes), longer than a
+// wave per 256 x 8 had (35, 44, 58, 181); so they take 25, 42, 65 and 182.
+template <class OT, uint32_t GP>
+__device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t xb, uint32_t yb, uint32_t zb,
                                              double ebx2)
 {
     const uint32_t nx = fd.nx, ny = fd.ny, nz = fd.nz;
-    const uint32_t g = lane_id() >> 4, zz = z0 + 2 * g;
+    const uint32_t l4 = lane_id() >> 4, zz = zb * 8 + 2 * (l4 % GP), y0 = yb * 8;
+    const uint32_t x0 = (xb * (4 / GP) + l4 / GP) * 64 + (lane_id() & 15) * 4;
     const int nv = x0 < nx ? (int)min<uint32_t>(4, nx - x0) : 0;
     const EBC_G uint16_t* __restrict__ q = fd.q;
     const EBC_G int32_t* __restrict__ dsc = fd.dsc;
     const uint64_t i0 = ((uint64_t)zz * ny + y0) * nx + x0, plane = (uint64_t)ny * nx;
-    const bool full = nv == 4 && zz + 1 < nz;
+    const bool full = nv == 4 && zz + 1 < nz, single = nv == 4 && zz + 1 == nz;
     const int nvz[2] = {zz < nz ? nv : 0, zz + 1 < nz ? nv : 0};
     u32x2 c[2][8];
     u32x4 d[2][8];
@@ -568,7 +582,7 @@ __device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0
 #pragma unroll
             for (int p = 0; p < 2; ++p) c[p][y] = *(const EBC_G u32x2_a2*)(q + i0 + p * plane + (uint64_t)y * nx);
         }
-    } else if (nvz[0] == 4) {
+    } else if (single) {
         // the field's last plane
 #pragma unroll
         for (uint32_t y = 0; y < 8; ++y) {
@@ -597,7 +611,7 @@ __device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0
         for (int p = 0; p < 2; ++p) low = min_halves(low, min_halves(c[p][y].x, c[p][y].y));
     const bool met = has_zero_half(low);
     if (__any(met)) {
-        if (full) {
+        if (full || single) {  // (an absent plane holds no outlier code)
 #pragma unroll
             for (uint32_t y = 0; y < 8; ++y) {
                 if (y0 + y >= ny) break;
@@ -619,10 +633,25 @@ __device__ __forceinline__ uint32_t recon3_wave(const FieldDesc& fd, uint32_t x0
             }
         }
     }
-    return block_sums<OT>(fd, c, d, y0, i0, full, nvz, ebx2);
+    return block_sums<OT, GP>(fd, c, d, y0, i0, full, single, nvz, ebx2);
 }
 
-// a workgroup per four blocks, in the order x, y, z
+// wave b of a field: its blocks in the order x, y, z, a last layer of few planes with
+// several blocks per wave
+template <class OT>
+__device__ __forceinline__ uint32_t recon3_blocks(const FieldDesc& fd, uint32_t b, double ebx2)
+{
+    const uint32_t nxb = fd.nxb, nyb = fd.nyb, layer = nxb * nyb;
+    const uint32_t zb = min(b / layer, fd.nzb - 1), gp = recon3_groups(fd.nz - zb * 8);
+    b -= zb * layer;
+    const uint32_t w = (nxb + 4 / gp - 1) / (4 / gp);  // waves along x
+    const uint32_t xb = b % w, yb = b / w;
+    if (yb >= nyb) return 0;
+    if (gp == 4) return recon3_wave<OT, 4>(fd, xb, yb, zb, ebx2);
+    if (gp == 2) return recon3_wave<OT, 2>(fd, xb, yb, zb, ebx2);
+    return recon3_wave<OT, 1>(fd, xb, yb, zb, ebx2);
+}
+
 __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __restrict__ F, int nf)
 {
     const uint32_t t = blockIdx.x;
@@ -631,12 +660,8 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct3(const FieldDesc* __rest
     const auto* dy = kconst(fd.dyn);
     if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
     const uint32_t b = (t - fd.r3_base) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t nxb = fd.nxb, nyb = fd.nyb;
-    const uint32_t xb = b % nxb, yb = (b / nxb) % nyb, zb = b / (nxb * nyb);
-    if (zb >= fd.nzb) return;
-    const uint32_t x0 = xb * 64 + (lane_id() & 15) * 4;
-    const uint32_t zeros = fd.dtype == 1 ? recon3_wave<double>(fd, x0, yb * 8, zb * 8, dy->ebx2)
-                                         : recon3_wave<float>(fd, x0, yb * 8, zb * 8, dy->ebx2);
+    const uint32_t zeros =
+        fd.dtype == 1 ? recon3_blocks<double>(fd, b, dy->ebx2) : recon3_blocks<float>(fd, b, dy->ebx2);
     const uint32_t zs = wave_sum_u32(zeros);
     if (lane_id() == 0 && zs) atomicAdd(&fd.zslot[(b % kZeroSlots) * kZeroStride], zs);
 }
