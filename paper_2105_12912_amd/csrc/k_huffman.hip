@@ -806,7 +806,12 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     const int f = find_field<&FieldDesc::hdwg_base>(F, nf, t);
     const FieldDesc& fd = F[f];
     EBC_G FieldDyn* dy = fd.dyn;
-    if (dy->status != ST_OK || !huff_codec(dy->codec)) return;
+    // One thread reads the status for all waves: workgroups of the field that find
+    // the archive corrupt change it while this launch runs, and a wave that left by
+    // itself would be missed at loading the tables.
+    if (threadIdx.x == 0) sm.next = dy->status == ST_OK && huff_codec(dy->codec) ? 0u : 1u;
+    __syncthreads();
+    if (sm.next != 0) return;  // (the queue starts behind the next barrier)
     // the chunks' words must add up to the header's count
     const uint32_t tot = woff[fd.hch_base + fd.n_hch] - woff[fd.hch_base];
     if ((uint64_t)tot != fd.n_words_hdr) {
@@ -828,7 +833,6 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
             sm.off[i] = T->offset[i];
         }
     }
-    if (threadIdx.x == 0) sm.next = 0;
     const uint32_t maxl = T->max_len;
     __syncthreads();
     // from here on LDS is also reached by byte address (EBC_LDS)
