@@ -865,7 +865,7 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
         if (gi >= n_grp || g >= n_grp) break;
         const uint32_t sub0 = g * per_wave;
         const uint32_t sub = sub0 + lane;
-        const bool live = lane < per_wave && sub < fd.n_sub;
+        bool live = lane < per_wave && sub < fd.n_sub;
         const uint32_t c = live ? sub / per : 0;
         const uint32_t nbits = live ? ((const EBC_G uint16_t*)(arc + fd.off_sbits))[sub] : 0u;
         // start bit of the sub-chunk inside the field's word stream
@@ -873,13 +873,16 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
                                        soff[fd.sub_base + sub]
                                  : 0ull;
         const uint64_t lo = (uint64_t)sub * hs;
-        const uint32_t want = live ? (uint32_t)min<uint64_t>(hs, fd.hn - lo) : 0u;
-        const uint32_t w0 = (uint32_t)(b0 >> 5);
         const uint32_t skip = (uint32_t)(b0 & 31);
         const uint32_t nwl = live ? (skip + nbits + 31) / 32 : 0u;  // words the lane may read
-        // the chunks' words add up to the archive's word count, and a sub-chunk
-        // ends inside its chunk by construction of the offsets
-        const EBC_G uint32_t* __restrict__ words = stream + w0;
+        // The sum of the chunks' words was checked modulo 2^32 only; with stored
+        // counts that wrap it, a sub-chunk may lie anywhere.
+        if (live && (b0 >> 5) + nwl > fd.n_words_hdr) {
+            atomicMin(&dy->status, (int32_t)ST_ERR_ARCHIVE);
+            live = false;
+        }
+        const uint32_t want = live ? (uint32_t)min<uint64_t>(hs, fd.hn - lo) : 0u;
+        const EBC_G uint32_t* __restrict__ words = stream + (live ? (uint32_t)(b0 >> 5) : 0u);
 
         // Stream position: pm = (bit position) - 1, counted from the first bit
         // of block A, so that the window from the next bit on is two funnel
