@@ -21,7 +21,7 @@ namespace ebc {
 
 
 // words of a wave's buffer in the write pass: 32 bits per symbol of a chunk (a
-// chunk of more is packed in place, in memory: that takes a field of some 1e8
+// chunk of more is packed in two rounds: that takes a field of some 1e8
 // elements, most of one code); the passes of chunks longer than kPassHc keep room
 // for 64
 __host__ __device__ constexpr uint32_t huff_buf_words(uint32_t hc) { return hc <= kPassHc ? hc + 2 : 2 * kPassHc; }
@@ -297,15 +297,16 @@ __device__ __forceinline__ void or_bits(uint32_t* wbuf, uint32_t b, uint64_t v, 
     }
 }
 
-// OR a codeword of 1 <= L <= 56 bits into words in memory at bit b
-__device__ __forceinline__ void or_long(EBC_G uint32_t* w, uint32_t b, uint64_t cw, uint32_t L)
+// OR the part of a codeword of 1 <= L <= 56 bits at bit b that lies in the n words
+// from word `from` on into a buffer of those words
+__device__ __forceinline__ void or_long(uint32_t* wbuf, uint32_t from, uint32_t n, uint32_t b, uint64_t cw, uint32_t L)
 {
     const uint64_t x = cw << (64 - L);
     const uint32_t hi = (uint32_t)(x >> 32), lo = (uint32_t)x, s = b & 31;
-    w += b >> 5;
-    atomicOr((uint32_t*)w, hi >> s);
-    if (s + L > 32) atomicOr((uint32_t*)w + 1, __builtin_amdgcn_alignbit(hi, lo, s));
-    if (s + L > 64) atomicOr((uint32_t*)w + 2, __builtin_amdgcn_alignbit(lo, 0u, s));
+    const uint32_t w = (b >> 5) - from;  // (words before `from` wrap to large values)
+    if (w < n) atomicOr(wbuf + w, hi >> s);
+    if (s + L > 32 && w + 1 < n) atomicOr(wbuf + (w + 1), __builtin_amdgcn_alignbit(hi, lo, s));
+    if (s + L > 64 && w + 2 < n) atomicOr(wbuf + (w + 2), __builtin_amdgcn_alignbit(lo, 0u, s));
 }
 
 // append a codeword of L <= 32 bits given left-aligned in cw
@@ -443,15 +444,17 @@ struct WriteProc {
         const uint64_t sub = (uint64_t)u.c * (hc / hs) + lane_id() / kLps;
         if (lane_id() % kLps == 0 && lo < u.e.cnt && sub < u.e.nsub) sbits[sub] = (uint16_t)sb;
         if (__builtin_expect(nw > hc, 0)) {
-            // more than 32 bits per symbol: packed in place
-            for (uint32_t i = lane_id(); i < nw; i += kWave) dst[i] = 0;
-            __threadfence();
-            uint32_t b = b0;
-            for (uint32_t k = 0; k < m; ++k) {
-                const uint64_t cw = code[u.e.src[lo + k]];
-                const uint32_t L = (uint32_t)(cw >> 56);
-                or_long(dst, b, cw & ((1ull << 56) - 1), L);
-                b += L;
+            // more than 32 bits per symbol: as many words as the buffer has at a time
+            for (uint32_t from = 0; from < nw; from += hc) {
+                for (uint32_t i = lane_id(); i < hc; i += kWave) wbuf[i] = 0;
+                uint32_t b = b0;
+                for (uint32_t k = 0; k < m; ++k) {
+                    const uint64_t cw = code[u.e.src[lo + k]];
+                    const uint32_t L = (uint32_t)(cw >> 56);
+                    or_long(wbuf, from, hc, b, cw & ((1ull << 56) - 1), L);
+                    b += L;
+                }
+                for (uint32_t i = lane_id(); i < min(nw - from, hc); i += kWave) dst[from + i] = wbuf[i];
             }
             return;
         }
