@@ -314,8 +314,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(const FieldDesc* __restrict__
     const int f = find_field<&FieldDesc::ow_base>(F, nf, t);
     const FieldDesc& fd = F[f];
     const auto* dy = kconst(fd.dyn);
-    const int32_t codec = dy->codec;
-    if (dy->status != ST_OK || codec == ARC_CONST) return;
+    const int32_t codec = dy->codec, status = dy->status;
+    // (the header's workgroup may report a small buffer while the waves of this one
+    // get here: they all go on, and find that out by themselves)
+    if ((status != ST_OK && status != ST_ERR_OUT_TOO_SMALL) || codec == ARC_CONST) return;
     outlier_unit(fd, t, soff, sm, [&] {
         const Layout y = layout_of(fd, codec, soff, woff, roff);
         return OutlierOut{(EBC_G uint32_t*)(fd.arc + y.off_oidx), (EBC_G int32_t*)(fd.arc + y.off_oval),
