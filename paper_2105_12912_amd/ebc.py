@@ -489,6 +489,7 @@ def decompress(a, out=None, stream=None, stats: bool | str = False, workspace=No
         # memory instead of a copy: a 256x256 field in 117 us instead of 130.  A
         # call that fails is repeated below, which says why.
         _, ptr, status = _pinned(a.device)
+        status.value = EBC_ERR_HIP  # until this call's last kernel stores its own
         s = torch.cuda.current_stream()
         if ebc_decompress_async(hdr, a.data_ptr(), a.numel(), out.data_ptr(), out.numel(), wptr, wlen,
                                 ptr + HDR_BYTES, int(s.cuda_stream)) == EBC_OK:
