@@ -242,7 +242,10 @@ struct Batch {
     FieldDyn* d_dyn = nullptr;
     uint32_t *d_seg = nullptr, *d_wcnt = nullptr, *d_rcnt = nullptr, *d_starts = nullptr, *d_tmap = nullptr,
              *d_tmp = nullptr, *d_soff = nullptr;
-    uint32_t tot_scan = 0;  // compress: entries of the array that starts at d_seg
+    // compress: the counts behind d_seg are one array of tot_scan entries (joint), or
+    // d_wcnt and d_rcnt arrays of their own and tot_scan the outlier counts
+    bool joint = true;
+    uint32_t tot_scan = 0;
     uint8_t* d_tabs = nullptr;
     size_t tab_stride = 0;  // decompress: decoder table bytes per field (largest n_bins of the batch)
     uint32_t max_bins = 0;
@@ -401,17 +404,21 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
     B.d_fd = bp.take<FieldDesc>(sizeof(FieldDesc) * B.nf);
     B.d_dyn = bp.take<FieldDyn>(sizeof(FieldDyn) * B.nf);
     // The outlier, word and run counts lie behind each other and are scanned as
-    // one array (only differences of two offsets of one field are used).  With
-    // VLE the run counts are needed before the word counts exist: an array of
-    // their own.
+    // one array (only differences of two offsets of one field are used), unless
+    // together they are too many to index.  With VLE the run counts are needed
+    // before the word counts exist: an array of their own.
     const bool vle = P.codec == EBC_CODEC_RLE_VLE || P.codec == EBC_CODEC_AUTO_VLE;
     const uint64_t n_scan = (uint64_t)B.tot_seg + B.tot_hch + (vle ? 0 : B.tot_rt);
-    if (n_scan >= 0xFFFFFFFFull) B.overflow = true;
-    B.tot_scan = (uint32_t)n_scan;
-    B.d_seg = bp.take<uint32_t>(4ull * (n_scan + 1));
-    B.d_wcnt = B.d_seg ? B.d_seg + B.tot_seg : nullptr;
-    B.d_rcnt = vle ? bp.take<uint32_t>(4ull * (B.tot_rt + 1)) : B.d_seg ? B.d_wcnt + B.tot_hch : nullptr;
-    B.d_tmp = bp.take<uint32_t>(4ull * std::max(scan_tmp_words(B.tot_scan), scan_tmp_words(B.tot_rt)));
+    B.joint = n_scan < 0xFFFFFFFFull;
+    B.tot_scan = B.joint ? (uint32_t)n_scan : B.tot_seg;
+    B.d_seg = bp.take<uint32_t>(4ull * ((uint64_t)B.tot_scan + 1));
+    auto counts = [&](uint32_t* behind, uint32_t n, bool own) {
+        return own ? bp.take<uint32_t>(4ull * ((uint64_t)n + 1)) : behind;
+    };
+    B.d_wcnt = counts(B.d_seg ? B.d_seg + B.tot_seg : nullptr, B.tot_hch, !B.joint);
+    B.d_rcnt = counts(B.d_wcnt ? B.d_wcnt + B.tot_hch : nullptr, B.tot_rt, !B.joint || vle);
+    B.d_tmp = bp.take<uint32_t>(4ull * std::max({scan_tmp_words(B.tot_scan), scan_tmp_words(B.tot_hch),
+                                                 scan_tmp_words(B.tot_rt)}));
     B.d_est = bp.take<EstDev>(sizeof(EstDev) * B.nf);
     for (int k = 0; k < B.nf; ++k) {
         const int i = B.order[k];
@@ -549,6 +556,10 @@ int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, uint64_
     }
     T.mark("encode_scan");
     HIP_TRY(launch_scan(B.d_seg, B.tot_scan, B.d_tmp, s, B.scan));
+    if (!B.joint) {
+        HIP_TRY(launch_scan(B.d_wcnt, B.tot_hch, B.d_tmp, s, B.scan));
+        if (rt && !vle) HIP_TRY(launch_scan(B.d_rcnt, B.tot_rt, B.d_tmp, s, B.scan));
+    }
     T.mark("encode_write");
     HIP_TRY(launch_huff_write(B.d_fd, nf, B.tot_hwg, P.hc, P.n_bins, B.d_seg, B.d_wcnt, B.d_rcnt, s));
     T.mark("finish");

@@ -292,13 +292,14 @@ __device__ __forceinline__ void write_header(const FieldDesc& fd, const uint32_t
 // outlier lists.  One launch of small pieces: each by itself is a launch of 3 to
 // 8 us that most fields need little of.
 __global__ __launch_bounds__(kBlock) void k_finish(const FieldDesc* __restrict__ F, int nf, uint32_t rt_blocks,
-                                                   uint32_t rt_units, const uint32_t* __restrict__ soff,
+                                                   uint32_t rt_units, uint32_t first,
+                                                   const uint32_t* __restrict__ soff,
                                                    const uint32_t* __restrict__ woff,
                                                    const uint32_t* __restrict__ roff,
                                                    uint64_t* __restrict__ res)
 {
     __shared__ OutlierLds sm;
-    uint32_t t = blockIdx.x;
+    uint32_t t = first + blockIdx.x;
     if (t < (uint32_t)nf) {
         write_header(F[t], soff, woff, roff, res);
         return;
@@ -367,8 +368,17 @@ hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t
 {
     // a wave per tile, with as many workgroups as the device holds
     const uint32_t rb = min((rt_units + kWavesPerBlock - 1) / kWavesPerBlock, kEncBlocks);
-    hipLaunchKernelGGL(k_finish, dim3(nf + rb + ow_units), dim3(kBlock), 0, s, F, nf, rb, rt_units, soff, woff, roff,
-                       res);
+    // A launch holds less than 2^32 threads: the outlier lists of a field of nearly as
+    // many segments go by themselves.
+    const uint64_t all = (uint64_t)nf + rb + ow_units;
+    const uint32_t one = all * kBlock < (1ull << 32) ? (uint32_t)all : nf + rb;
+    hipLaunchKernelGGL(k_finish, dim3(one), dim3(kBlock), 0, s, F, nf, rb, rt_units, 0u, soff, woff, roff, res);
+    if (one < all) {
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_finish, dim3(ow_units), dim3(kBlock), 0, s, F, nf, rb, rt_units, one, soff, woff, roff,
+                           res);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,39 @@
+"""A field whose outlier, word and run counts together are more than 2^32: compressed
+and read back within the bound (17 GB of input, about 70 GB on the device)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("codec", ["huffman", "auto"])
+def test_one_column(codec):
+    from paper_2105_12912_amd import ebc as E
+
+    n, eb = 4_294_000_000, 1e-2
+    if torch.cuda.mem_get_info()[0] < 100e9:
+        pytest.skip("needs 100 GB of free device memory")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    block = torch.randn(1 << 20, generator=g, device="cuda").cumsum(0) / 300
+    if codec == "auto":  # long runs
+        block[:-70000] = 0.0
+    x = torch.zeros(n, device="cuda")
+    for a in range(0, n, block.numel()):
+        x[a:a + block.numel()] = block[:n - a] * (1 if (a >> 20) % 3 else -1)
+    p = E.make_params(eb, "abs", codec=codec)
+    out = torch.empty(6 << 30, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(E.ebc_compress_workspace_size(2, (1, n), p), dtype=torch.uint8, device="cuda")
+    st, size = E.ebc_compress(x.data_ptr(), 2, (1, n), p, out.data_ptr(), out.numel(), ws.data_ptr(), ws.numel(),
+                              E._stream_handle())
+    assert st == 0 and size > 0
+    del ws
+    torch.cuda.empty_cache()
+    print("compressed", size, flush=True)
+    a = out[:size]
+    assert E.ebc_archive_info(E.archive_header(a))["codec"] == (0 if codec == "huffman" else 1)
+    y = E.decompress(a, workspace=E.Workspace("cuda")).reshape(-1)
+    for k in range(0, n, 1 << 28):
+        assert float((y[k:k + (1 << 28)] - x[k:k + (1 << 28)]).abs().max()) <= eb
+    del x, y, out
+    torch.cuda.empty_cache()
