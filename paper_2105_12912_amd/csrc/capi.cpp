@@ -405,11 +405,11 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
     B.d_dyn = bp.take<FieldDyn>(sizeof(FieldDyn) * B.nf);
     // The outlier, word and run counts lie behind each other and are scanned as
     // one array (only differences of two offsets of one field are used), unless
-    // together they are too many to index.  With VLE the run counts are needed
-    // before the word counts exist: an array of their own.
+    // together they are too many to index (the scan rounds up to whole tiles).  With
+    // VLE the run counts are needed before the word counts exist: an array of their own.
     const bool vle = P.codec == EBC_CODEC_RLE_VLE || P.codec == EBC_CODEC_AUTO_VLE;
     const uint64_t n_scan = (uint64_t)B.tot_seg + B.tot_hch + (vle ? 0 : B.tot_rt);
-    B.joint = n_scan < 0xFFFFFFFFull;
+    B.joint = n_scan <= kScanMax;
     B.tot_scan = B.joint ? (uint32_t)n_scan : B.tot_seg;
     B.d_seg = bp.take<uint32_t>(4ull * ((uint64_t)B.tot_scan + 1));
     auto counts = [&](uint32_t* behind, uint32_t n, bool own) {

@@ -20,6 +20,7 @@ struct DescBlob {
 };
 
 // scan
+constexpr uint32_t kScanMax = 0xFFFFF000u;  // longest array (a multiple of the scan's tile)
 uint32_t scan_tmp_words(uint32_t n);
 // exclusive scan, total in a[n]; direct_max: tile count up to which each
 // tile's workgroup adds the sums of the tiles before it (0: the default),

@@ -18,6 +18,7 @@ namespace ebc {
 
 constexpr int kScanItems = 16;
 constexpr uint32_t kScanTile = kBlock * kScanItems;
+static_assert(kScanMax % kScanTile == 0, "a rounded count stays below 2^32");
 constexpr uint32_t kScanDirect = 1024;  // default: tiles up to which the tile sums are not scanned first
 
 // exclusive scan of one value per thread over the block; *total = block sum
