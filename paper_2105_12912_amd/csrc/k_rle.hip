@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kBlock) void k_rle_map(const FieldDesc* __restrict_
     // (each step waits for a load: 14 us one after the other on 120M elements, 10 here)
     uint32_t a = 0, b = fd.n_runs_hdr - 1, c = 0, d = b;
     while (a < b || c < d) {
-        const uint32_t m = (a + b + 1) >> 1, k = (c + d + 1) >> 1;
+        const uint32_t m = a + ((b - a + 1) >> 1), k = c + ((d - c + 1) >> 1);  // (the sums may pass 2^32)
         const uint32_t sm = S[m] - s0, sk = S[k] - s0;
         if (a < b) {
             if ((uint64_t)sm <= lo) a = m;

@@ -56,7 +56,7 @@ __device__ __forceinline__ uint16_t run_value(const FieldDesc& fd, uint32_t i, c
     uint32_t a = tmap[2 * t], b = a + tmap[2 * t + 1] - 1;
     if (b == a) return (uint16_t)a;
     while (a < b) {
-        const uint32_t m = (a + b + 1) >> 1;
+        const uint32_t m = a + ((b - a + 1) >> 1);
         if (S[m] - s0 <= i) a = m;
         else b = m - 1;
     }

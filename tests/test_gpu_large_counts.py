@@ -37,3 +37,31 @@ def test_one_column(n, codec):
         assert float((y[k:k + (1 << 28)] - x[k:k + (1 << 28)]).abs().max()) <= eb
     del x, y, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [2_300_000_000])
+def test_runs_of_one(n):
+    """Run indices above 2^31 in the searches of decompression, for the tiles and for
+    the codes of outliers (about 80 GB on the device)."""
+    from paper_2105_12912_amd import ebc as E
+
+    eb = 0.4
+    if torch.cuda.mem_get_info()[0] < 150e9:
+        pytest.skip("needs 150 GB of free device memory")
+    x = torch.zeros(n, device="cuda")
+    x[1::2] = 1.0
+    x[n - 100] = x[n // 3] = x[7] = 2000.0
+    p = E.make_params(eb, "abs", codec="rle")
+    out = torch.empty(E.HDR_BYTES + 6 * n + 4096, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(E.ebc_compress_workspace_size(1, (n,), p), dtype=torch.uint8, device="cuda")
+    st, size = E.ebc_compress(x.data_ptr(), 1, (n,), p, out.data_ptr(), out.numel(), ws.data_ptr(), ws.numel(),
+                              E._stream_handle())
+    assert st == 0 and size > 6 * n - 4096
+    del ws
+    torch.cuda.empty_cache()
+    print("compressed", size, flush=True)
+    y = E.decompress(out[:size], workspace=E.Workspace("cuda"))
+    for k in range(0, n, 1 << 28):
+        assert float((y[k:k + (1 << 28)] - x[k:k + (1 << 28)]).abs().max()) <= eb
+    del x, y, out
+    torch.cuda.empty_cache()
