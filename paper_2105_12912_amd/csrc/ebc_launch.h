@@ -12,6 +12,8 @@ namespace ebc {
 // Records a failure detail for ebc_last_error() (calling thread) and returns status.
 int set_error(int status, const char* fmt, ...);
 
+constexpr uint64_t kMaxThreads = 1ull << 32;  // a launch has to have fewer
+
 constexpr int kDescPerLaunch = 8;
 struct DescBlob {
     int first;

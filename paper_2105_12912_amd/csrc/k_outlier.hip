@@ -368,10 +368,9 @@ hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t
 {
     // a wave per tile, with as many workgroups as the device holds
     const uint32_t rb = min((rt_units + kWavesPerBlock - 1) / kWavesPerBlock, kEncBlocks);
-    // A launch holds less than 2^32 threads: the outlier lists of a field of nearly as
-    // many segments go by themselves.
+    // the outlier lists of a field of nearly 2^32 segments go by themselves
     const uint64_t all = (uint64_t)nf + rb + ow_units;
-    const uint32_t one = all * kBlock < (1ull << 32) ? (uint32_t)all : nf + rb;
+    const uint32_t one = all * kBlock < kMaxThreads ? (uint32_t)all : nf + rb;
     hipLaunchKernelGGL(k_finish, dim3(one), dim3(kBlock), 0, s, F, nf, rb, rt_units, 0u, soff, woff, roff, res);
     if (one < all) {
         const hipError_t e = hipGetLastError();

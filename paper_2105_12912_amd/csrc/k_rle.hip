@@ -209,8 +209,16 @@ hipError_t launch_rle_decode(const FieldDesc* F, int nf, uint32_t rl_units, uint
     hipLaunchKernelGGL(k_rle_prep, dim3(rl_units), dim3(kBlock), 0, s, F, nf, starts);
     hipError_t e = launch_scan(starts, n_starts, tmp, s, scan_direct);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rle_map, dim3(rl_units + (rt_units + kBlock - 1) / kBlock), dim3(kBlock), 0, s, F, nf,
-                       rl_units, rt_units, starts, tmap);
+    const uint32_t maps = (rt_units + kBlock - 1) / kBlock;
+    if (((uint64_t)rl_units + maps) * kBlock < kMaxThreads) {
+        hipLaunchKernelGGL(k_rle_map, dim3(rl_units + maps), dim3(kBlock), 0, s, F, nf, rl_units, rt_units, starts,
+                           tmap);
+    } else {  // nearly 2^32 runs: the checks by themselves
+        hipLaunchKernelGGL(k_rle_map, dim3(rl_units), dim3(kBlock), 0, s, F, nf, rl_units, rt_units, starts, tmap);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_rle_map, dim3(maps), dim3(kBlock), 0, s, F, nf, 0u, rt_units, starts, tmap);
+    }
     if (rt_units && expand)
         hipLaunchKernelGGL(k_rle_expand, dim3(rt_units), dim3(kBlock), 0, s, F, nf, starts, tmap);
     return hipGetLastError();
