@@ -355,7 +355,11 @@ template <> __device__ __forceinline__ const EBC_G double* field_in<double>(cons
 // the codes lo .. lo + kHistWin - 2 around the centre; any other code is
 // counted straight into the field histogram in HBM (rare for a predictable
 // field, whose deltas cluster around zero).
-template <bool WIDE>
+// QUADS: the field has whole quads, and the deltas of one with an outlier go as one
+// store (those of the other elements are never read): a store per element took a
+// rough fp64 field of 100x500x500 91.5 us, this 86.5.  Rows of one to three elements
+// have none, and the branches for them cost 384 instead of 364 us on 8M rows of one.
+template <bool WIDE, bool QUADS>
 __device__ __forceinline__ uint32_t postquant4(const int32_t dl[4], int nvalid, QuantCtx& qc,
                                                uint32_t c[4], EBC_G int32_t* __restrict__ dsc,
                                                uint64_t i, uint32_t* sh_hist)
@@ -366,7 +370,10 @@ __device__ __forceinline__ uint32_t postquant4(const int32_t dl[4], int nvalid, 
         const bool in = dl[k] > -qc.r && dl[k] < qc.r;
         c[k] = in ? (uint32_t)(dl[k] + qc.r) : 0u;
         if (k < nvalid) {
-            if (!in) om |= 1u << k;
+            if (!in) {
+                om |= 1u << k;
+                if (!QUADS) dsc[i + k] = dl[k];
+            }
             if (c[k] == (uint32_t)qc.r) {
                 qc.center++;
             } else if (!WIDE) {
@@ -381,10 +388,7 @@ __device__ __forceinline__ uint32_t postquant4(const int32_t dl[4], int nvalid, 
             }
         }
     }
-    if (om) {
-        // the deltas of a quad with an outlier go as one store (those of the other
-        // elements are never read): a store per element took a rough fp64 field of
-        // 100x500x500 91.5 us, this 86.5
+    if (QUADS && om) {
         if (nvalid == 4) {
             *(EBC_G i32x4_a4*)(dsc + i) = i32x4{dl[0], dl[1], dl[2], dl[3]};
         } else {
@@ -410,7 +414,7 @@ __device__ __forceinline__ uint32_t row_count(uint32_t om, uint64_t rowmask)
 
 // One workgroup tile: quantise, record outliers, count codes into the LDS
 // histogram and outlier counts per row segment into `s_cnt` (2D/3D).
-template <int RANK, bool VEC, class T, bool WIDE>
+template <int RANK, bool VEC, class T, bool WIDE, bool QUADS>
 __device__ __forceinline__ void construct_tile(const FieldDesc& fd, uint32_t tl, QuantCtx& qc,
                                                uint32_t* sh_hist, uint32_t* s_cnt,
                                                uint32_t* __restrict__ segs)
@@ -443,7 +447,7 @@ __device__ __forceinline__ void construct_tile(const FieldDesc& fd, uint32_t tl,
                 if (l == 0) left = 0;
                 dl[0] = d[0] - left, dl[1] = d[1] - d[0], dl[2] = d[2] - d[1], dl[3] = d[3] - d[2];
                 uint32_t code[4];
-                const uint32_t om = postquant4<WIDE>(dl, nv, qc, code, dsc, i0, sh_hist);
+                const uint32_t om = postquant4<WIDE, QUADS>(dl, nv, qc, code, dsc, i0, sh_hist);
                 if (VEC && nv == 4) store_codes<true>(qo, i0, 4, code);
                 else store_codes<false>(qo, i0, nv, code);
                 const uint32_t cnt = row_count(om, ~0ull);
@@ -501,7 +505,7 @@ __device__ __forceinline__ void construct_tile(const FieldDesc& fd, uint32_t tl,
                     fprev[k] = fy;
                 }
                 uint32_t code[4];
-                const uint32_t om = postquant4<WIDE>(dl, nv, qc, code, dsc, i0, sh_hist);
+                const uint32_t om = postquant4<WIDE, QUADS>(dl, nv, qc, code, dsc, i0, sh_hist);
                 store_codes<VEC>(qo, i0, nv, code);
                 const uint32_t cnt = row_count(om, rowmask);
                 if (xq == 0 && cnt) atomicAdd(&s_cnt[wyi * 64 + iz * 8 + y], cnt);
@@ -535,7 +539,7 @@ __device__ __forceinline__ void construct_tile(const FieldDesc& fd, uint32_t tl,
 #pragma unroll
                 for (int k = 0; k < 4; ++k) dl[k] = e[k] - dpp_keep(dpp_shr<1>(e[k]));  // y = 0 reads 0
                 uint32_t code[4];
-                const uint32_t om = postquant4<WIDE>(dl, nv, qc, code, dsc, i0, sh_hist);
+                const uint32_t om = postquant4<WIDE, QUADS>(dl, nv, qc, code, dsc, i0, sh_hist);
                 store_codes<VEC>(qo, i0, nv, code);
                 rowcnt += row_count(om, rowmask);
             }
@@ -601,7 +605,10 @@ __global__ __launch_bounds__(kBlock) void k_construct(const FieldDesc* __restric
         }
         const uint32_t tl = t - fd.wg_base;
         uint32_t* cnt = s_cnt[par];
-        construct_tile<RANK, VEC, T, WIDE>(fd, tl, qc, sh_hist, cnt, seg_cnt + fd.seg_base);
+        if (RANK >= 2 && !VEC && fd.nx < 4)
+            construct_tile<RANK, VEC, T, WIDE, false>(fd, tl, qc, sh_hist, cnt, seg_cnt + fd.seg_base);
+        else
+            construct_tile<RANK, VEC, T, WIDE, true>(fd, tl, qc, sh_hist, cnt, seg_cnt + fd.seg_base);
         if (RANK >= 2) {
             __syncthreads();
             // one outlier count per row segment of this tile; the buffer is
