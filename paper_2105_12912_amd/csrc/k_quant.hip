@@ -94,6 +94,13 @@ __device__ __forceinline__ double key_double(uint64_t k)
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
+// fp64 values up to which the range pass leaves the field in the last-level cache (256
+// MB, from which construction then reads it: range + construction of 250x250x250 69 us,
+// with non-temporal loads 75, of 18M values 75 and 78).  A larger field pushes itself
+// out, and non-temporal loads are the faster (30M values: 105 us, without 107; 839 MB:
+// 350 and 360).
+constexpr uint64_t kRangeKeep = 20000000;
+
 __global__ __launch_bounds__(kBlock) void k_range64(const FieldDesc* __restrict__ F, int nf)
 {
     const uint32_t u = blockIdx.x;
@@ -114,13 +121,17 @@ __global__ __launch_bounds__(kBlock) void k_range64(const FieldDesc* __restrict_
     if (((uintptr_t)in & 15u) == 0 && hi - lo == kRangeUnit) {
         constexpr uint32_t kPairs = kRangeUnit / (2 * kBlock), kAhead = kPairs < 8 ? kPairs : 8;
         const EBC_G f64x2* __restrict__ p = (const EBC_G f64x2*)(in + lo) + threadIdx.x;
-        for (uint32_t j = 0; j < kPairs; j += kAhead) {
-            f64x2 v[kAhead];
+        auto pairs = [&](auto load) {
+            for (uint32_t j = 0; j < kPairs; j += kAhead) {
+                f64x2 v[kAhead];
 #pragma unroll
-            for (uint32_t k = 0; k < kAhead; ++k) v[k] = __builtin_nontemporal_load(p + (j + k) * kBlock);
+                for (uint32_t k = 0; k < kAhead; ++k) v[k] = load(p + (j + k) * kBlock);
 #pragma unroll
-            for (uint32_t k = 0; k < kAhead; ++k) take(v[k].x), take(v[k].y);
-        }
+                for (uint32_t k = 0; k < kAhead; ++k) take(v[k].x), take(v[k].y);
+            }
+        };
+        if (fd.n <= kRangeKeep) pairs([](const EBC_G f64x2* a) { return *a; });
+        else pairs([](const EBC_G f64x2* a) { return __builtin_nontemporal_load(a); });
     } else {
         for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) take(in[i]);
     }
