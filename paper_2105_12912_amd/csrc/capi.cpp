@@ -1,7 +1,7 @@
 // capi.cpp -- C ABI of the compressor: validation, planning, workspace
 // carving and the kernel sequences for compression and decompression.
 //
-// Every call is a batch: fields are grouped by (rank, 16-byte row alignment)
+// Every call is a batch: fields are grouped by data type, rank and row layout
 // so each construct / reconstruct launch is specialised, and every other
 // kernel covers all fields in one grid.  The host never looks at data between
 // kernels: the codec decision, the outlier count, section offsets and the
@@ -223,11 +223,11 @@ struct Bump {
 
 struct Batch {
     int nf = 0;
-    std::vector<FieldDesc> fd;    // sorted by (rank, vec)
+    std::vector<FieldDesc> fd;    // sorted by (data type, rank, rows)
     std::vector<int> order;       // fd[k] is caller field order[k]
     struct Group {
         int rank;
-        bool vec;
+        int rows;  // kRows*
         bool f64;
         int first, count;
         uint32_t wg_tiles;
@@ -259,23 +259,23 @@ struct Batch {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Group fields by (rank, vec) and assign every work-unit base.
+// Group fields by data type, rank and rows and assign every work-unit base.
 // Default persistent construction grid for a (rank, layout) variant: the
 // workgroups the device holds at once, cached per device and bin count.
-uint32_t resident_grid(int rank, bool vec, uint32_t n_bins, bool f64)
+uint32_t resident_grid(int rank, int rows, uint32_t n_bins, bool f64)
 {
     static std::mutex mu;
     static std::vector<std::pair<uint64_t, uint32_t>> cache;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const uint64_t key = ((uint64_t)dev << 32) | ((uint64_t)n_bins << 4) | (f64 ? 8u : 0u) |
-                         (uint64_t)(rank * 2 + (vec ? 1 : 0));
+    const uint64_t key = ((uint64_t)dev << 32) | ((uint64_t)n_bins << 8) | (f64 ? 16u : 0u) |
+                         (uint64_t)(rank * 4 + rows);
     {
         std::lock_guard<std::mutex> lk(mu);
         for (const auto& kv : cache)
             if (kv.first == key) return kv.second;
     }
-    uint32_t g = construct_resident_blocks(rank, vec, n_bins, f64);
+    uint32_t g = construct_resident_blocks(rank, rows, n_bins, f64);
     if (g == 0) g = kConstructBlocks;
     std::lock_guard<std::mutex> lk(mu);
     cache.push_back({key, g});
@@ -303,8 +303,13 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
     const int nf = B.nf;
     std::vector<int> idx(nf);
     for (int i = 0; i < nf; ++i) idx[i] = i;
-    // groups of one (data type, rank, row alignment): one specialised launch each
-    auto key = [&](int i) { return dt[i] * 8 + geo[i].rank * 2 + (vec[i] ? 1 : 0); };
+    // groups of one (data type, rank, rows): one specialised launch each (short rows
+    // matter to construction only)
+    auto rows = [&](int i) {
+        if (vec[i]) return (int)kRowsVec;
+        return n_bins && geo[i].rank > 1 && geo[i].nx < 4 ? (int)kRowsShort : (int)kRowsAny;
+    };
+    auto key = [&](int i) { return dt[i] * 16 + geo[i].rank * 4 + rows(i); };
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return key(a) < key(b); });
     B.order = idx;
     B.groups.clear();
@@ -314,9 +319,9 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         sub{0, ov}, hpwg{0, ov};
     for (int k = 0; k < nf; ++k) {
         const Geo& g = geo[idx[k]];
-        const bool v = vec[idx[k]];
+        const int v = rows(idx[k]);
         const bool f64 = dt[idx[k]] == 1;
-        if (B.groups.empty() || B.groups.back().rank != g.rank || B.groups.back().vec != v ||
+        if (B.groups.empty() || B.groups.back().rank != g.rank || B.groups.back().rows != v ||
             B.groups.back().f64 != f64) {
             B.groups.push_back({g.rank, v, f64, k, 0, 0, 0});
             wg.v = 0;
@@ -345,7 +350,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
     for (auto& G : B.groups) {
         uint32_t grid = 0;
         for (int k = G.first; k < G.first + G.count; ++k) grid = std::max(grid, geo[B.order[k]].grid);
-        if (grid == 0) grid = n_bins ? resident_grid(G.rank, G.vec, n_bins, G.f64) : kConstructBlocks;
+        if (grid == 0) grid = n_bins ? resident_grid(G.rank, G.rows, n_bins, G.f64) : kConstructBlocks;
         G.blocks = std::min(G.wg_tiles, grid);
         for (int k = G.first; k < G.first + G.count; ++k)
             B.fd[k].hrows = std::min(B.fd[k].wg_tiles, G.blocks);
@@ -525,7 +530,7 @@ int enqueue_compress(Batch& B, const Params& P, hipStream_t s, Timer& T, uint64_
     HIP_TRY(launch_params(B.d_fd, nf, s));
     T.mark("construct");
     for (const auto& G : B.groups)
-        HIP_TRY(launch_construct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles, G.blocks,
+        HIP_TRY(launch_construct(B.d_fd + G.first, G.count, G.rank, G.rows, G.f64, G.wg_tiles, G.blocks,
                                  P.n_bins, B.d_seg, s));
     // small fields: the codebook adds their few partial histograms itself
     bool direct = !debug_stop && P.n_bins <= kMaxBins;
@@ -847,7 +852,7 @@ int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
     if (has12) T.mark(B.tot_r3 ? "reconstruct_12" : "reconstruct");
     for (const auto& G : B.groups)
         if (G.wg_tiles)
-            HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.vec, G.f64, G.wg_tiles,
+            HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.rows == kRowsVec, G.f64, G.wg_tiles,
                                        G.blocks, s));
     if (B.rle_1d) HIP_TRY(launch_rle_reconstruct(B.d_fd, B.nf, B.tot_rt, B.d_starts, B.d_tmap, s));
     return EBC_OK;

@@ -32,8 +32,10 @@ hipError_t launch_scan(uint32_t* a, uint32_t n, uint32_t* tmp, hipStream_t s, ui
 // quantisation
 hipError_t launch_range(const FieldDesc* F, int nf, uint32_t units, bool f64, hipStream_t s);
 hipError_t launch_params(const FieldDesc* F, int nf, hipStream_t s);
-uint32_t construct_resident_blocks(int rank, bool vec, uint32_t n_bins, bool f64);
-hipError_t launch_construct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,
+// a field's rows: shorter than a quad (rank 2 and 3), any, 16-byte aligned
+enum { kRowsShort = 0, kRowsAny = 1, kRowsVec = 2 };
+uint32_t construct_resident_blocks(int rank, int rows, uint32_t n_bins, bool f64);
+hipError_t launch_construct(const FieldDesc* F, int nf, int rank, int rows, bool f64, uint32_t wg_tiles,
                             uint32_t blocks, uint32_t n_bins, uint32_t* seg_cnt, hipStream_t s);
 hipError_t launch_hist_reduce(const FieldDesc* F, int nf, uint32_t n_bins, hipStream_t s);
 

@@ -369,7 +369,9 @@ template <> __device__ __forceinline__ const EBC_G double* field_in<double>(cons
 // QUADS: the field has whole quads, and the deltas of one with an outlier go as one
 // store (those of the other elements are never read): a store per element took a
 // rough fp64 field of 100x500x500 91.5 us, this 86.5.  Rows of one to three elements
-// have none, and the branches for them cost 384 instead of 364 us on 8M rows of one.
+// have none (kRowsShort), and the branches for them cost 384 instead of 364 us on 8M
+// rows of one.  They get launches of their own: with both kinds of tile in one kernel
+// 800000x5 took 50.5 us instead of 47.8.
 template <bool WIDE, bool QUADS>
 __device__ __forceinline__ uint32_t postquant4(const int32_t dl[4], int nvalid, QuantCtx& qc,
                                                uint32_t c[4], EBC_G int32_t* __restrict__ dsc,
@@ -586,7 +588,7 @@ __device__ __forceinline__ void flush_hist(const FieldDesc& fd, QuantCtx& qc, ui
 // that the occupancy query reports, and the grid's last workgroups start when others
 // have ended (with 82 to 87 of them and 16384 bins, fp32: 250x250x250 47 us instead of
 // 41, 10M values of 1D 25 instead of 22).
-template <int RANK, bool VEC, class T, bool WIDE>
+template <int RANK, int ROWS, class T, bool WIDE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k_construct(const FieldDesc* __restrict__ F, int nf,
                                                       uint32_t n_tiles, uint32_t* __restrict__ seg_cnt)
 {
@@ -620,10 +622,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k
         }
         const uint32_t tl = t - fd.wg_base;
         uint32_t* cnt = s_cnt[par];
-        if (RANK >= 2 && !VEC && fd.nx < 4)
-            construct_tile<RANK, VEC, T, WIDE, false>(fd, tl, qc, sh_hist, cnt, seg_cnt + fd.seg_base);
-        else
-            construct_tile<RANK, VEC, T, WIDE, true>(fd, tl, qc, sh_hist, cnt, seg_cnt + fd.seg_base);
+        construct_tile<RANK, ROWS == kRowsVec, T, WIDE, ROWS != kRowsShort>(fd, tl, qc, sh_hist, cnt,
+                                                                           seg_cnt + fd.seg_base);
         if (RANK >= 2) {
             __syncthreads();
             // one outlier count per row segment of this tile; the buffer is
@@ -684,66 +684,49 @@ hipError_t launch_params(const FieldDesc* F, int nf, hipStream_t s)
     return hipGetLastError();
 }
 
-template <class T, bool W>
-static hipError_t occupancy(int rank, bool vec, size_t sh, int* per)
+using ConstructFn = void (*)(const FieldDesc*, int, uint32_t, uint32_t*);
+template <int RANK, class T, bool W>
+static ConstructFn construct_rows(int rows)
 {
-    if (rank == 1)
-        return vec ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<1, true, T, W>, kBlock, sh)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<1, false, T, W>, kBlock, sh);
-    if (rank == 2)
-        return vec ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<2, true, T, W>, kBlock, sh)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<2, false, T, W>, kBlock, sh);
-    return vec ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<3, true, T, W>, kBlock, sh)
-               : hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_construct<3, false, T, W>, kBlock, sh);
+    if (rows == kRowsVec) return k_construct<RANK, kRowsVec, T, W>;
+    if constexpr (RANK > 1)
+        if (rows == kRowsShort) return k_construct<RANK, kRowsShort, T, W>;
+    return k_construct<RANK, kRowsAny, T, W>;
+}
+template <class T, bool W>
+static ConstructFn construct_rank(int rank, int rows)
+{
+    return rank == 1   ? construct_rows<1, T, W>(rows)
+           : rank == 2 ? construct_rows<2, T, W>(rows)
+                       : construct_rows<3, T, W>(rows);
+}
+static ConstructFn construct_fn(int rank, int rows, bool f64, uint32_t n_bins)
+{
+    if (n_bins > kMaxBins) return f64 ? construct_rank<double, true>(rank, rows) : construct_rank<float, true>(rank, rows);
+    return f64 ? construct_rank<double, false>(rank, rows) : construct_rank<float, false>(rank, rows);
 }
 
 // Workgroups of one construction variant that the device holds at once (the
 // default persistent grid); 0 if the query fails.
-uint32_t construct_resident_blocks(int rank, bool vec, uint32_t n_bins, bool f64)
+uint32_t construct_resident_blocks(int rank, int rows, uint32_t n_bins, bool f64)
 {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     const size_t sh = (size_t)hist_slots(n_bins) * sizeof(uint32_t);
-    const bool w = n_bins > kMaxBins;
-    const hipError_t e = f64 ? (w ? occupancy<double, true>(rank, vec, sh, &per)
-                                  : occupancy<double, false>(rank, vec, sh, &per))
-                             : (w ? occupancy<float, true>(rank, vec, sh, &per)
-                                  : occupancy<float, false>(rank, vec, sh, &per));
+    const hipError_t e =
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, construct_fn(rank, rows, f64, n_bins), kBlock, sh);
     if (e != hipSuccess || per <= 0 || cus <= 0) return 0;
     return (uint32_t)(per * cus);
 }
 
-template <class T, bool W>
-static void construct_launch(const FieldDesc* F, int nf, int rank, bool vec, uint32_t wg_tiles,
-                             dim3 g, size_t sh, uint32_t* seg_cnt, hipStream_t s)
-{
-    const dim3 b(kBlock);
-    if (rank == 1) {
-        if (vec) hipLaunchKernelGGL((k_construct<1, true, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-        else hipLaunchKernelGGL((k_construct<1, false, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-    } else if (rank == 2) {
-        if (vec) hipLaunchKernelGGL((k_construct<2, true, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-        else hipLaunchKernelGGL((k_construct<2, false, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-    } else {
-        if (vec) hipLaunchKernelGGL((k_construct<3, true, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-        else hipLaunchKernelGGL((k_construct<3, false, T, W>), g, b, sh, s, F, nf, wg_tiles, seg_cnt);
-    }
-}
-
-hipError_t launch_construct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,
+hipError_t launch_construct(const FieldDesc* F, int nf, int rank, int rows, bool f64, uint32_t wg_tiles,
                             uint32_t blocks, uint32_t n_bins, uint32_t* seg_cnt, hipStream_t s)
 {
     if (wg_tiles == 0) return hipSuccess;
     const size_t sh = (size_t)hist_slots(n_bins) * sizeof(uint32_t);
-    const dim3 g(blocks);
-    if (n_bins > kMaxBins) {
-        if (f64) construct_launch<double, true>(F, nf, rank, vec, wg_tiles, g, sh, seg_cnt, s);
-        else construct_launch<float, true>(F, nf, rank, vec, wg_tiles, g, sh, seg_cnt, s);
-    } else {
-        if (f64) construct_launch<double, false>(F, nf, rank, vec, wg_tiles, g, sh, seg_cnt, s);
-        else construct_launch<float, false>(F, nf, rank, vec, wg_tiles, g, sh, seg_cnt, s);
-    }
+    const ConstructFn k = construct_fn(rank, rows, f64, n_bins);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), sh, s, F, nf, wg_tiles, seg_cnt);
     return hipGetLastError();
 }
 
