@@ -809,6 +809,12 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     const int f = find_field<&FieldDesc::hdwg_base>(F, nf, t);
     const FieldDesc& fd = F[f];
     EBC_G FieldDyn* dy = fd.dyn;
+    // EBC_LDS counts from the start of LDS: static LDS of this kernel, which there must
+    // be none of, would come first
+    if ((uint32_t)(uintptr_t)lds64 != 0) {
+        if (threadIdx.x == 0) atomicMin(&dy->status, (int32_t)ST_ERR_UNSUPPORTED);
+        return;
+    }
     // One thread reads the status for all waves: workgroups of the field that find
     // the archive corrupt change it while this launch runs, and a wave that left by
     // itself would be missed at loading the tables.
