@@ -166,7 +166,7 @@ struct Geo {
     uint32_t grid;  // persistent construction grid (workgroups)
     uint32_t scan;  // scan schedule: direct down-sweep up to this many tiles (0: default)
     uint32_t n_seg, range_units, ow_units, ow_segs, n_hch, hwg_units, n_rt;
-    uint32_t hs, n_sub, hpwg_units;
+    uint32_t hs, n_sub;
 };
 
 Geo make_geo(int rank, const uint64_t dims[3], uint32_t hc)
@@ -203,7 +203,6 @@ Geo make_geo(int rank, const uint64_t dims[3], uint32_t hc)
     g.hwg_units = cdiv(g.n_hch, huff_cpw(hc));
     g.hs = std::min(hc, kSubMax);
     g.n_sub = cdiv(g.n, g.hs);
-    g.hpwg_units = cdiv(g.n_hch, kBlock);
     g.n_rt = cdiv(g.n, kRleTile);
     return g;
 }
@@ -316,7 +315,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
     B.overflow = false;
     bool* ov = &B.overflow;
     Tot range{0, ov}, seg{0, ov}, ow{0, ov}, hch{0, ov}, hwg{0, ov}, rt{0, ov}, wg{0, ov},
-        sub{0, ov}, hpwg{0, ov};
+        sub{0, ov};
     for (int k = 0; k < nf; ++k) {
         const Geo& g = geo[idx[k]];
         const int v = rows(idx[k]);
@@ -339,12 +338,11 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
         d.hwg_base = hwg.add(g.hwg_units), d.hwg_units = g.hwg_units;
         d.hs = g.hs;
         d.sub_base = sub.add(g.n_sub), d.n_sub = g.n_sub;
-        d.hpwg_base = hpwg.add(g.hpwg_units), d.hpwg_units = g.hpwg_units;
         d.rt_base = rt.add(g.n_rt), d.n_rt = g.n_rt;
     }
     B.tot_range = (uint32_t)range.v, B.tot_seg = (uint32_t)seg.v, B.tot_ow = (uint32_t)ow.v;
     B.tot_hch = (uint32_t)hch.v, B.tot_hwg = (uint32_t)hwg.v;
-    B.tot_rt = (uint32_t)rt.v, B.tot_sub = (uint32_t)sub.v, B.tot_hpwg = (uint32_t)hpwg.v;
+    B.tot_rt = (uint32_t)rt.v, B.tot_sub = (uint32_t)sub.v;
     B.scan = 0;
     for (int k = 0; k < nf; ++k) B.scan = std::max(B.scan, geo[k].scan);
     for (auto& G : B.groups) {
@@ -357,7 +355,7 @@ void assign_bases(Batch& B, const std::vector<Geo>& geo, const std::vector<bool>
     }
 }
 
-void fill_geometry(FieldDesc& d, const Geo& g, bool vec)
+void fill_geometry(FieldDesc& d, const Geo& g)
 {
     d.n = g.n;
     d.nx = (uint32_t)g.nx, d.ny = (uint32_t)g.ny, d.nz = (uint32_t)g.nz;
@@ -366,7 +364,6 @@ void fill_geometry(FieldDesc& d, const Geo& g, bool vec)
     d.xs = g.xs;
     d.nxb = g.nxb, d.nyb = g.nyb, d.nzb = g.nzb;
     d.n_wave_tiles = g.n_wave_tiles;
-    d.vec = vec ? 1u : 0u;
 }
 
 // 3D reconstruction: blocks of 64 x 8 x 8, one per wave; in a last layer of few
@@ -429,7 +426,7 @@ int plan_compress(Batch& B, const std::vector<CompressIn>& fin, const Params& P,
         const int i = B.order[k];
         const Geo& g = geo[i];
         FieldDesc& d = B.fd[k];
-        fill_geometry(d, g, vec[i]);
+        fill_geometry(d, g);
         d.n_bins = P.n_bins;
         d.hc = P.hc;
         d.eb_mode = P.eb_mode;
@@ -782,7 +779,6 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
             d.wg_tiles = wt;
         }
         G.wg_tiles = (uint32_t)wg.v;
-        G.blocks = G.wg_tiles;  // one workgroup per tile
     }
     B.d_wcnt = bp.take<uint32_t>(4ull * (B.tot_hch + 1));
     B.d_soff = bp.take<uint32_t>(4ull * (B.tot_sub + 1));
@@ -798,7 +794,7 @@ int plan_decompress(Batch& B, const std::vector<DecompressIn>& din, uint8_t* ws)
         const Header& H = D.H;
         const Geo& g = geo[B.order[k]];
         FieldDesc& d = B.fd[k];
-        fill_geometry(d, g, vec[B.order[k]]);
+        fill_geometry(d, g);
         if (g.rank == 3) {
             // the 3D reconstruction kernel's blocks differ from construction's tiles
             uint32_t t3[3];
@@ -853,7 +849,7 @@ int enqueue_reconstruct(Batch& B, hipStream_t s, Timer& T)
     for (const auto& G : B.groups)
         if (G.wg_tiles)
             HIP_TRY(launch_reconstruct(B.d_fd + G.first, G.count, G.rank, G.rows == kRowsVec, G.f64, G.wg_tiles,
-                                       G.blocks, s));
+                                       s));
     if (B.rle_1d) HIP_TRY(launch_rle_reconstruct(B.d_fd, B.nf, B.tot_rt, B.d_starts, B.d_tmap, s));
     return EBC_OK;
 }

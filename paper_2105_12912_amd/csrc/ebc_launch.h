@@ -89,7 +89,7 @@ hipError_t launch_outlier_scatter(const FieldDesc* F, int nf, uint32_t units, co
 
 // reconstruction
 hipError_t launch_reconstruct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,
-                              uint32_t blocks, hipStream_t s);
+                              hipStream_t s);
 hipError_t launch_reconstruct3(const FieldDesc* F, int nf, uint32_t units, hipStream_t s);
 // st: statuses in the caller's order (device), or NULL
 hipError_t launch_recon_check(const FieldDesc* F, int nf, int32_t* st, hipStream_t s);

@@ -106,7 +106,6 @@ struct FieldDesc {
     uint32_t xs;             // x extent of a workgroup tile = outlier segment length
     uint32_t nxb, nyb, nzb;  // workgroup-tile grid (2D/3D)
     uint32_t n_wave_tiles;   // 1D wave tiles
-    uint32_t vec;            // 1: rows 16-byte aligned, quads never straddle rows
     uint32_t slot;           // position of this field in the caller's arrays
     // buffers (device)
     const EBC_G float* in;   // compress input (fp32 field)
@@ -187,7 +186,6 @@ struct DecTab {
     uint64_t first[65];   // first code of each length
     uint64_t endv[65];    // (first[L] + count[L]) << (64 - L): a left-aligned window w holds a
                           // code of length <= L iff w < endv[L] (defined for L < max_len)
-    uint32_t count[65];   // codes of each length
     uint32_t offset[65];  // index of the first symbol of each length in perm
     uint32_t max_len;
     uint32_t l2k;             // bits resolved by the second level (0: no second level)

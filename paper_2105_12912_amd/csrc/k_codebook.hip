@@ -655,7 +655,6 @@ __device__ __forceinline__ void build_dectab(const FieldDesc& fd, DecTab* T)
         // left-aligned ends of the code space of lengths <= L (monotone in L)
         T->endv[L] = L >= 1 && L < maxl ? (first[L] + cntL[L]) << (64 - L) : ~0ull;
         T->first[L] = first[L];
-        T->count[L] = L ? cntL[L] : 0u;
         T->offset[L] = offs[L];
         if (L <= (uint32_t)kLutBits) end1[L] = L ? (uint32_t)(first[L] + cntL[L]) << (kLutBits - L) : 0u;
         else if (L <= kLutBits + l2k) end2[L - kLutBits] = (uint32_t)(first[L] + cntL[L]) << (kLutBits + l2k - L);

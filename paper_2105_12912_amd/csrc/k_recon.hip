@@ -21,10 +21,8 @@ namespace ebc {
 // Four codes kept packed (two per 32-bit word) so that a whole tile's loads
 // fit in few registers; codes of absent elements read as 1 (never the
 // outlier placeholder).
-template <bool VEC>
 __device__ __forceinline__ u32x2 load_packed(const EBC_G uint16_t* __restrict__ q, uint64_t i, int nvalid)
 {
-    if (VEC && nvalid == 4) return ld_nt_u2(q + i);
     if (nvalid == 4 && (i & 1) == 0) return *(const EBC_G u32x2_a4*)(q + i);  // dword-aligned
     uint32_t c[4];
 #pragma unroll
@@ -148,7 +146,7 @@ __device__ __forceinline__ void rtile_load(const FieldDesc& fd, uint32_t tl, RTi
         int nv;
         rquad(fd, tl, k, i0, nv);
         if (VEC) T.raw[k] = ld_nt_u2(fd.q + (nv > 0 ? i0 : 0));
-        else T.raw[k] = load_packed<false>(fd.q, i0, nv);
+        else T.raw[k] = load_packed(fd.q, i0, nv);
     }
 }
 
@@ -194,11 +192,9 @@ __device__ __forceinline__ void rtile_process(const FieldDesc& fd, uint32_t tl, 
 
 // Zero codes seen by this workgroup for field fd, added to one of the field's
 // counters (their sum is checked against the outlier count by k_recon_check).
-__device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t& zeros, uint32_t* s_z)
+__device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t zeros, uint32_t* s_z)
 {
     const uint32_t zs = wave_sum_u32(zeros);
-    zeros = 0;
-    __syncthreads();
     if (lane_id() == 0) s_z[threadIdx.x / kWave] = zs;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -207,57 +203,22 @@ __device__ __forceinline__ void flush_zeros(const FieldDesc& fd, uint32_t& zeros
     }
 }
 
-// 1D: grid-stride over the workgroup tiles of one layout group, with the
-// next tile's codes in flight while the current tile is reconstructed (two
-// static buffers).  Launched with one workgroup per tile, which measured
-// faster than a resident-size grid; the stride loop serves tuned grids.
+// 1D: one workgroup per tile, which measured faster than a resident-size grid that
+// strides over the tiles with the next one's codes in flight.
 template <bool VEC, class OT>
-__global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restrict__ F, int nf,
-                                                        uint32_t n_tiles)
+__global__ __launch_bounds__(kBlock) void k_reconstruct(const FieldDesc* __restrict__ F, int nf)
 {
     __shared__ uint32_t s_z[kWavesPerBlock];
-    uint32_t t = blockIdx.x;
-    if (t >= n_tiles) return;
-    RTile A, B;
-    int fa = find_field<&FieldDesc::wg_base>(F, nf, t), fb;
-    rtile_load<VEC>(F[fa], t - F[fa].wg_base, A);
-    int cur = -1;
+    const uint32_t t = blockIdx.x;
+    const FieldDesc& fd = F[find_field<&FieldDesc::wg_base>(F, nf, t)];
+    const uint32_t tl = t - fd.wg_base;
+    RTile T;
+    rtile_load<VEC>(fd, tl, T);  // on the way while the field's scalars are read
+    const auto* dy = kconst(fd.dyn);
+    if (dy->status != ST_OK || dy->codec == ARC_CONST) return;
     uint32_t zeros = 0;
-    for (;;) {
-        uint32_t tn = t + gridDim.x;
-        const uint32_t tb = tn < n_tiles ? tn : t;
-        fb = find_field<&FieldDesc::wg_base>(F, nf, tb);
-        if (tn < n_tiles) rtile_load<VEC>(F[fb], tb - F[fb].wg_base, B);
-        {
-            const FieldDesc& fd = F[fa];
-            const auto* dy = kconst(fd.dyn);
-            if (fa != cur) {
-                if (cur >= 0) flush_zeros(F[cur], zeros, s_z);
-                cur = fa;
-            }
-            if (dy->status == ST_OK && dy->codec != ARC_CONST)
-                rtile_process<VEC, OT>(fd, t - fd.wg_base, A, dy->ebx2, zeros);
-        }
-        t = tn;
-        if (t >= n_tiles) break;
-        tn = t + gridDim.x;
-        const uint32_t ta = tn < n_tiles ? tn : t;
-        fa = find_field<&FieldDesc::wg_base>(F, nf, ta);
-        if (tn < n_tiles) rtile_load<VEC>(F[fa], ta - F[fa].wg_base, A);
-        {
-            const FieldDesc& fd = F[fb];
-            const auto* dy = kconst(fd.dyn);
-            if (fb != cur) {
-                if (cur >= 0) flush_zeros(F[cur], zeros, s_z);
-                cur = fb;
-            }
-            if (dy->status == ST_OK && dy->codec != ARC_CONST)
-                rtile_process<VEC, OT>(fd, t - fd.wg_base, B, dy->ebx2, zeros);
-        }
-        t = tn;
-        if (t >= n_tiles) break;
-    }
-    if (cur >= 0) flush_zeros(F[cur], zeros, s_z);
+    rtile_process<VEC, OT>(fd, tl, T, dy->ebx2, zeros);
+    flush_zeros(fd, zeros, s_z);
 }
 
 // A tile inside one run, of code v (not the outlier placeholder): its chunks are
@@ -700,26 +661,26 @@ __global__ __launch_bounds__(kBlock) void k_fill_const(const FieldDesc* __restri
 }
 
 template <class OT>
-static void reconstruct_launch(const FieldDesc* F, int nf, int rank, bool vec, uint32_t wg_tiles,
-                               uint32_t blocks, hipStream_t s)
+static void reconstruct_launch(const FieldDesc* F, int nf, int rank, bool vec, uint32_t wg_tiles, hipStream_t s)
 {
-    const dim3 g(blocks), b(kBlock);
+    const dim3 g(wg_tiles);
     if (rank == 1) {
-        if (vec) hipLaunchKernelGGL((k_reconstruct<true, OT>), g, b, 0, s, F, nf, wg_tiles);
-        else hipLaunchKernelGGL((k_reconstruct<false, OT>), g, b, 0, s, F, nf, wg_tiles);
+        const dim3 b(kBlock);
+        if (vec) hipLaunchKernelGGL((k_reconstruct<true, OT>), g, b, 0, s, F, nf);
+        else hipLaunchKernelGGL((k_reconstruct<false, OT>), g, b, 0, s, F, nf);
     } else {
-        const dim3 g2(wg_tiles), b2(kWave);  // one wave per tile
-        if (vec) hipLaunchKernelGGL((k_reconstruct2<true, OT>), g2, b2, 0, s, F, nf);
-        else hipLaunchKernelGGL((k_reconstruct2<false, OT>), g2, b2, 0, s, F, nf);
+        const dim3 b(kWave);  // one wave per tile
+        if (vec) hipLaunchKernelGGL((k_reconstruct2<true, OT>), g, b, 0, s, F, nf);
+        else hipLaunchKernelGGL((k_reconstruct2<false, OT>), g, b, 0, s, F, nf);
     }
 }
 
 hipError_t launch_reconstruct(const FieldDesc* F, int nf, int rank, bool vec, bool f64, uint32_t wg_tiles,
-                              uint32_t blocks, hipStream_t s)
+                              hipStream_t s)
 {
     if (wg_tiles == 0) return hipSuccess;
-    if (f64) reconstruct_launch<double>(F, nf, rank, vec, wg_tiles, blocks, s);
-    else reconstruct_launch<float>(F, nf, rank, vec, wg_tiles, blocks, s);
+    if (f64) reconstruct_launch<double>(F, nf, rank, vec, wg_tiles, s);
+    else reconstruct_launch<float>(F, nf, rank, vec, wg_tiles, s);
     return hipGetLastError();
 }
 
