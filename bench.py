@@ -44,55 +44,57 @@ WORKLOADS = {
                  lambda s: s.sparse_background_1d(120_000_000), 1e-2),
 }
 
-# kernel stage -> algorithmic bytes per launch (n elements, o outliers, w words, r runs);
-# the 3D reconstruction reads no outlier deltas (its fix-up kernel does)
-def algo_bytes(stage: str, n: int, o: int, w: int, r: int, n_bins: int, rank: int = 3,
-               codec: int = 0, elem: int = 4) -> float | None:
+# kernel stage -> algorithmic bytes per launch (n elements, o outliers, w words, r runs)
+def algo_bytes(stage: str, n: int, o: int, w: int, r: int, rank: int = 3, codec: int = 0,
+               elem: int = 4) -> float | None:
     """Bytes a stage must move (the method's, not the kernels' actual traffic).
-    codec 0 Huffman, 1 RLE, 3 RLE+VLE; elem: bytes per input value."""
-    if codec == 0:
-        enc_count, enc_write = 2 * n, 2 * n + 4 * w
-        dec = 4 * w + 2 * n
-    elif codec == 1:
-        # run flags from the codes; (value, start) per run, then lengths
-        enc_count, enc_write = 2 * n, 2 * n + 6 * r + 8 * r
-        dec = None
-    else:
-        enc_count, enc_write = 2 * n, 2 * r + 4 * w + 8 * r
-        dec = 4 * w + 2 * r
+    codec 0 Huffman, 1 RLE, 3 RLE+VLE; elem: bytes per input value.  None: the
+    stage has nothing to move by this model."""
+    runs = codec in (1, 3)
+    # symbols of the Huffman stream: the codes, or the run values
+    syms = {0: n, 3: r}.get(codec, 0)
     table = {
         "range": elem * n,
-        "construct": elem * n + 2 * n + 8 * o,
-        "encode_count": enc_count,
-        "encode_write": enc_write,
-        "outlier_write": 8 * o,
-        "huffman_decode": dec,
-        "rle_decode": 6 * r + 2 * n,
+        "construct": elem * n + 2 * n + 4 * o,
+        "encode_count": 2 * n,
+        "encode_write": 2 * syms + 4 * w,
+        # run lengths (and values, which RLE+VLE has written before) and the outlier list
+        "finish": 12 * o + (6 * r if codec == 1 else 4 * r if codec == 3 else 0),
+        "huffman_decode": 4 * w + 2 * syms,
+        # 1D fields are reconstructed from their runs; 2D and 3D ones expand them first
+        "rle_decode": (4 * r if rank == 1 else 6 * r + 2 * n) if runs else 0,
         "outlier_scatter": 12 * o,
-        "reconstruct": 2 * n + elem * n + 4 * o,
+        "reconstruct": (6 * r if runs and rank == 1 else 2 * n) + elem * n + 4 * o,
     }
-    return table.get(stage)
+    return table.get(stage) or None
 
 
 # stage name -> kernel name in rocprofv3 output
-STAGE_KERNEL = {"construct": "k_construct", "reconstruct": "k_reconstruct3",
-                "huffman_decode": "k_huff_decode", "encode_write": "k_huff_write",
-                "encode_count": "k_huff_bits", "range": "k_range"}
+STAGE_KERNEL = {"construct": "k_construct", "huffman_decode": "k_huff_decode",
+                "encode_write": "k_huff_write", "encode_count": "k_huff_bits", "range": "k_range",
+                "finish": "k_finish"}
 
 
-def stage_kernel(stage: str, rank: int) -> str | None:
-    if stage == "reconstruct" and rank < 3:
-        return "k_reconstruct"
+def stage_kernel(stage: str, rank: int, codec: int) -> str | None:
+    if stage == "reconstruct":
+        if rank > 1:
+            return f"k_reconstruct{rank}"
+        return "k_rle_reconstruct" if codec in (1, 3) else "k_reconstruct"
     return STAGE_KERNEL.get(stage)
 
 
-def traffic_from_profiles(stage: str, workload: str, rank: int):
+def stage_times(side: str, st) -> dict:
+    """Stage times (ms) of one call by "side:stage"; outlier_fix, a name kept from
+    a kernel that is now part of the reconstruction, has no work of its own."""
+    return {f"{side}:{k}": v for k, v in st.stages().items() if k != "outlier_fix"}
+
+
+def traffic_from_profiles(kname: str | None, workload: str):
     """HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated) from the
     committed counter summary, if it was taken on the current kernel source."""
     from paper_2105_12912_amd import prof_summary
 
     path = os.path.join(ROOT, "profiles", "traffic.json")
-    kname = stage_kernel(stage, rank)
     if not kname or not os.path.exists(path):
         return None
     try:
@@ -177,11 +179,10 @@ def bench_field(xd, eb: float, codec: str = "auto", reps: int = 5, ref=None) -> 
     a, cs = ebc.compress(xd, eb, "rel", codec=codec, stats=True, workspace=ws, out=out)
     _, ds = ebc.decompress(a, out=y, stats=True, workspace=ws)
     n, o, w, r = xd.numel(), cs.n_outliers, cs.n_words, cs.n_runs
-    stages = {"c:" + k: v for k, v in cs.stages().items()}
-    stages.update({"d:" + k: v for k, v in ds.stages().items()})
+    stages = {**stage_times("c", cs), **stage_times("d", ds)}
     roof = {}
     for key, t in stages.items():
-        b = algo_bytes(key.split(":", 1)[1], n, o, w, r, 1024, xd.dim(), cs.codec, elem)
+        b = algo_bytes(key.split(":", 1)[1], n, o, w, r, xd.dim(), cs.codec, elem)
         if b is None or t <= 0:
             continue
         ach = b / (t / 1e3) / 1e9
@@ -536,15 +537,13 @@ def main():
         print(f"[bench] stage breakdown over {args.steps} steps", file=sys.stderr, flush=True)
         for _ in range(args.steps):
             a, y, cs, ds = step(True, True)
-            for k, v in cs.stages().items():
-                stage_sum["c:" + k] = stage_sum.get("c:" + k, 0.0) + v
-            for k, v in ds.stages().items():
-                stage_sum["d:" + k] = stage_sum.get("d:" + k, 0.0) + v
+            for k, v in {**stage_times("c", cs), **stage_times("d", ds)}.items():
+                stage_sum[k] = stage_sum.get(k, 0.0) + v
             last_cs = cs
         stages = {k: v / args.steps for k, v in stage_sum.items()}
         o, w, r = last_cs.n_outliers, last_cs.n_words, last_cs.n_runs
         cand = {k: t for k, t in stages.items()
-                if t > 0 and algo_bytes(k.split(":", 1)[1], n, o, w, r, 1024, x.ndim) is not None}
+                if t > 0 and algo_bytes(k.split(":", 1)[1], n, o, w, r, x.ndim, last_cs.codec) is not None}
         dom = max(cand, key=cand.get) if cand else None
     torch.cuda.synchronize()
     # timed region: plain round trips; only the dominant kernel's stage carries
@@ -609,7 +608,7 @@ def main():
         roof = {}
         for key, t in stages.items():
             name = key.split(":", 1)[1]
-            b = algo_bytes(name, n, o, w, r, 1024, x.ndim)
+            b = algo_bytes(name, n, o, w, r, x.ndim, last_cs.codec)
             if b is None or t <= 0:
                 continue
             ach = b / (t / 1e3) / 1e9
@@ -619,12 +618,13 @@ def main():
         if dom:
             name = dom.split(":", 1)[1]
             t = dom_sum / args.steps
-            ach = algo_bytes(name, n, o, w, r, 1024, x.ndim) / (t / 1e3) / 1e9
-            result["roofline"] = {"bound": "hbm", "kernel": stage_kernel(name, x.ndim) or name,
+            ach = algo_bytes(name, n, o, w, r, x.ndim, last_cs.codec) / (t / 1e3) / 1e9
+            kname = stage_kernel(name, x.ndim, last_cs.codec)
+            result["roofline"] = {"bound": "hbm", "kernel": kname or name,
                                   "stage": name, "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS,
                                   "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBPS, 4),
                                   "launch_ms": round(t, 5),
-                                  "traffic": traffic_from_profiles(name, args.workload, x.ndim)}
+                                  "traffic": traffic_from_profiles(kname, args.workload)}
     if not args.no_cpu_baseline and int(os.environ.get("RANK", "0")) == 0:
         print("[bench] cpu baseline (oracle)", file=sys.stderr, flush=True)
         cb, oarc, oy = cpu_baseline(x, eb, arc)
