@@ -30,7 +30,7 @@ CANDIDATES = {
 
 
 SCANS = (64, 1024, 16384)
-SCAN_STAGES = ("scan_outliers", "encode_scan", "decode_prep")
+SCAN_STAGES = ("encode_scan", "decode_prep")
 
 
 class TuningChangedBytes(AssertionError):
