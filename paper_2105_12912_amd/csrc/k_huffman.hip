@@ -786,13 +786,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Codewords longer than 32 bits leave for an exact path that reads windows
 // straight from the stream.  Flushed blocks are stored non-temporally: they
 // are not read before the kernel ends, and kept in the L2 they push out the
-// stream's lines, each of which a lane comes back to eight times (195 us
-// against 173 us on the 512^3 field).
+// stream's lines, each of which a lane comes back to eight times (22 us more on the
+// 512^3 field).
 //
 // With the former step (bit buffer topped up from an LDS ring, exact clipping
 // and both table levels in every step: about 60 vector instructions) a wave
 // needed 900 cycles per step by itself and the kernel 257-290 us on a 512^3
-// field at 3.8 bits per symbol, 82 us on 256x256; now 172 and 50 us.  What
+// field at 3.8 bits per symbol, 82 us on 256x256; now 178-212 and 50 us.  What
 // bounds it now is latency: a wave waits half of its time (table reads that
 // depend on each other, stream blocks), and the LDS rows allow 16 waves per CU.
 // Three, four or five steps per group make no difference on the large field.
@@ -1057,6 +1057,8 @@ __global__ __launch_bounds__(1024) void k_huff_decode(const FieldDesc* __restric
     default: return hipErrorInvalidValue;                                                   \
     }
 
+// Compute units of an MI355X as one partition; on a part of it the grids and splits
+// below are too large, which costs time only.
 constexpr uint32_t kCus = 256;
 
 // persistent grid: enough workgroups to fill the device several times over
@@ -1119,14 +1121,16 @@ hipError_t launch_huff_write(const FieldDesc* F, int nf, uint32_t units, uint32_
 // Decode workgroups of a call whose streams make n_sub sub-chunks: sub-chunks per
 // wave, lanes per workgroup, and waves' worth of work that a workgroup takes.  The
 // tables take 42 KB of LDS per workgroup and a lane 116 bytes, so a CU holds one
-// workgroup of 1024 lanes (16 waves) or two of 256.  A large call gets one
-// workgroup per CU, so that the tables are loaded once and the waves even out.  A
-// call of up to two workgroups of 256 lanes per CU is split over all of them, with
-// half of each wave's lanes idle: four waves load the tables, and a wave waits for
-// the slowest of 32 lanes only (one wave of 64 per workgroup: 256x256 55 us, here
-// 50; 1800x3600 44 and 40; 1501x2999 with 16384 bins 87 and 81).  16 sub-chunks per
-// wave gain nothing more on those, 8 lose once the workgroups do not fit at once
-// (1800x3600: 58 us).
+// workgroup of 1024 lanes (16 waves) or two of 256.  Above 4096 waves' worth of work
+// (64 sub-chunks each) a workgroup of 1024 lanes takes a 256th of the sum, so that the
+// tables are loaded once per CU and the waves even out; between 2048 and 4096, 16, and
+// some CUs stay idle.  Every field of a batch rounds up to whole workgroups of its own,
+// so there may be more of them than CUs.  A call of up to two workgroups of 256 lanes
+// per CU is split over all of them, up to 65536 sub-chunks with half of each wave's
+// lanes idle: four waves load the tables, and a wave waits for the slowest of 32 lanes
+// only (one wave of 64 per workgroup: 256x256 55 us, here 50; 1800x3600 44 and 40;
+// 1501x2999 with 16384 bins 87 and 81).  16 sub-chunks per wave gain nothing more on
+// those, 8 lose once the workgroups do not fit at once (1800x3600: 58 us).
 void huff_decode_split(uint64_t n_sub, uint32_t* per_wave, uint32_t* lanes, uint32_t* groups)
 {
     *per_wave = n_sub <= 32 * 4 * 2 * kCus ? 32 : 64;

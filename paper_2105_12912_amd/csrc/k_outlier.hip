@@ -17,11 +17,12 @@ namespace ebc {
 
 constexpr uint32_t kSegLane = 8;  // elements of a segment per lane
 
-// Segments per workgroup.  Most segments of a large field hold no outlier and a
-// workgroup's time is that of looking at them: 256, one per thread (18 us with
-// 64 against 10 us on the 1M segments of 512^3).  Smaller fields have too few
-// workgroups for that if many segments hold outliers (62 us against 37 us on
-// the 2e5 of a rough 100x500x500 field): 64.
+// Segments per workgroup.  Where most segments hold no outlier a workgroup's time is
+// that of looking at them: 256, one per thread (18 us with 64 against 10 us on the 1M
+// segments of 512^3).  Where many hold some, 64 (62 us against 37 us on the 2e5 of a
+// rough 100x500x500 field).  The host does not know the density, so the line is the
+// size at which 256 still make 2048 workgroups.  (A rough field above it was not
+// measured.)
 uint32_t outlier_write_segs(uint32_t n_seg) { return n_seg > (1u << 19) ? kBlock : kWave; }
 
 // element range [a, b) of segment s
