@@ -367,7 +367,7 @@ hipError_t launch_outlier_write(const FieldDesc* F, int nf, uint32_t units, cons
 hipError_t launch_finish(const FieldDesc* F, int nf, uint32_t rt_units, uint32_t ow_units, const uint32_t* soff,
                          const uint32_t* woff, const uint32_t* roff, uint64_t* res, hipStream_t s)
 {
-    // a wave per tile, with as many workgroups as the device holds
+    // a wave per tile; up to 2048 workgroups, of which the device holds 1792 at a time
     const uint32_t rb = min((rt_units + kWavesPerBlock - 1) / kWavesPerBlock, kEncBlocks);
     // the outlier lists of a field of nearly 2^32 segments go by themselves
     const uint64_t all = (uint64_t)nf + rb + ow_units;
